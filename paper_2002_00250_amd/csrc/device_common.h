@@ -4,15 +4,20 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fgs_internal.h"
+
 namespace fgs {
+
+__device__ __forceinline__ uint32_t div_by(uint32_t n, FastDiv d) { return __umulhi(n << 1, d.mul) >> d.shift; }
 
 // 8-bit depth code (Sec. 4.1-4.2): 0 = no depth; otherwise the round-half-up
 // rescale of millimetres to `full_scale_mm`, clamped to [1, 255].
-__device__ __forceinline__ uint32_t depth_code(uint32_t d_mm, uint32_t full_scale_mm) {
-    if (d_mm == 0u) return 0u;
-    uint32_t q = (__umul24(255u, d_mm) + (full_scale_mm >> 1)) / full_scale_mm;  // d_mm < 2^16
+__device__ __forceinline__ uint32_t depth_code(uint32_t d_mm, uint32_t full_scale_mm, FastDiv by_full_scale) {
+    // d_mm < 2^16 and full_scale_mm < 2^31: the dividend is below 2^31
+    uint32_t q = div_by(__umul24(255u, d_mm) + (full_scale_mm >> 1), by_full_scale);
     q = q < 1u ? 1u : q;
-    return q > 255u ? 255u : q;
+    q = q > 255u ? 255u : q;
+    return d_mm == 0u ? 0u : q;
 }
 
 // Depth (mm) seen by RGB pixel (x, y).  The depth map is either W x H, or dw x dh
@@ -20,11 +25,16 @@ __device__ __forceinline__ uint32_t depth_code(uint32_t d_mm, uint32_t full_scal
 // (Sec. 4.3: depth is upscaled to the RGB resolution when the two differ):
 // xd = floor((x + 1/2) dw / W), yd = floor((y + 1/2) dh / H).
 __device__ __forceinline__ uint32_t load_depth(const uint8_t* depth, int64_t stride, int x, int y,
-                                               int W, int H, int dw, int dh) {
+                                               int W, int H, int dw, int dh, const FrameGeom& g) {
     int xd = x, yd = y;
     if (dw > 0) {
-        xd = (int)(((int64_t)(2 * x + 1) * dw) / (2 * (int64_t)W));
-        yd = (int)(((int64_t)(2 * y + 1) * dh) / (2 * (int64_t)H));
+        if (g.small) {
+            xd = (int)div_by((uint32_t)(2 * x + 1) * (uint32_t)dw, g.w2);
+            yd = (int)div_by((uint32_t)(2 * y + 1) * (uint32_t)dh, g.h2);
+        } else {
+            xd = (int)(((int64_t)(2 * x + 1) * dw) / (2 * (int64_t)W));
+            yd = (int)(((int64_t)(2 * y + 1) * dh) / (2 * (int64_t)H));
+        }
     }
     return *reinterpret_cast<const uint16_t*>(depth + (int64_t)yd * stride + 2 * xd);
 }

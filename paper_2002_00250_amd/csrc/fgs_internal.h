@@ -22,6 +22,27 @@ constexpr int kBatchMax = 8;
 constexpr int kPbasTileW = 64;
 constexpr int kPbasTileH = 4;
 
+// Division by a number known on the host, for n < 2^31: n / d = (2n * mul) >> (32 + shift), one
+// high multiply and a shift (Granlund and Montgomery's invariant division: with l = ceil(log2 d),
+// mul = floor(2^(31 + l) / d) + 1 and shift = l the quotient is exact for every 31-bit n).  The
+// compiler's division by a run-time number is about 20 instructions, 4 of them quarter rate.
+struct FastDiv {
+    uint32_t mul, shift;
+};
+inline FastDiv fast_div(uint32_t d) {  // 1 <= d < 2^31
+    const uint32_t l = d > 1 ? 32u - (uint32_t)__builtin_clz(d - 1) : 0u;
+    return FastDiv{(uint32_t)(((uint64_t)1 << (31 + l)) / d + 1), l};
+}
+
+// Where a frame's pixels lie, precomputed for the kernels.
+struct FrameGeom {
+    int32_t flat;        // 1: rows packed and depth of the frame's size: pixel p is at 3p and 2p
+    int32_t small;       // 1: the upscaling products (2x + 1) dw and (2y + 1) dh are below 2^31
+    FastDiv w, w2, h2;   // division by W, 2W and 2H
+};
+FrameGeom frame_geom(int32_t H, int32_t W, int64_t rgb_stride, int64_t depth_stride, int32_t depth_h,
+                     int32_t depth_w);
+
 // ---------------------------------------------------------------- GMM ----
 // Device layout: per pixel, Kc "core" float4 planes (mu_r, mu_g, mu_b, v) of the
 // colour Gaussians by rank, then E "extra" float4 planes holding, in order, the
@@ -45,11 +66,21 @@ bool gmm_supported(int Kc, int Kd);
 struct GmmConsts {
     float alpha, lam, T_bg, w_init, v_init_c, v_min_c, v_init_d, v_min_d, w_depth;
     uint32_t depth_max_mm;
+    FastDiv depth_div;   // division by depth_max_mm
     int32_t rho_mode;    // matched-Gaussian rate: 0 alpha, 1 alpha / w, 2 alpha * eta
     int32_t decision;    // 1: scaled Eq. (1) density product below density_threshold
     float density_scale, density_threshold;
     int32_t var_mode;    // 1: per-channel colour variances (v_init_c, v_min_c per channel)
+    int32_t sane;        // 1: constants within the range of the approximate decisions (gmm_device.h)
 };
+
+// Whether a model's constants leave the approximate decisions room (the margins are relative,
+// so the quantities compared must stay inside the exponent range).
+__host__ __device__ inline bool gmm_sane(float lam, float w_depth, float v_min_c, float v_min_d, float v_init_c,
+                                         float v_init_d) {
+    return lam > 1.0e-6f && lam < 1.0e6f && w_depth < 1.0e6f && v_min_c > 1.0e-20f && v_min_d > 1.0e-20f &&
+           v_init_c < 1.0e20f && v_init_d < 1.0e20f;
+}
 
 struct GmmStepArgs {
     float4* state;
@@ -60,6 +91,7 @@ struct GmmStepArgs {
     int64_t rgb_stride, depth_stride;
     int32_t H, W, npix;
     int32_t depth_h, depth_w;  // 0: depth is H x W; else its size, upscaled to H x W
+    FrameGeom geom;
     GmmConsts c;
 };
 
@@ -122,6 +154,7 @@ struct PbasConsts {
     float R_incdec, R_scale, T_inc, T_dec, T_lower, T_upper;
     float R_lower[4];
     uint32_t depth_max_mm;
+    FastDiv depth_div;  // division by depth_max_mm
     uint32_t key0, key1;
     float grad_alpha;  // gradient-magnitude variant only
 };
@@ -147,6 +180,7 @@ struct PbasStepArgs {
     int64_t rgb_stride, depth_stride;
     int32_t H, W, npix;
     int32_t depth_h, depth_w;  // 0: depth is H x W; else its size, upscaled to H x W
+    FrameGeom geom;
     uint32_t t;            // frame index
     int32_t apply_pending; // neighbour writes of frame t-1 (fire bytes) still to be applied
     int32_t streaming;     // 1: non-temporal sample traffic (working set beyond the last-level cache)
@@ -203,6 +237,7 @@ struct PbasGradArgs {
     int64_t rgb_stride, depth_stride;
     int32_t H, W, npix;
     int32_t depth_h, depth_w;
+    FrameGeom geom;
     uint32_t t;
     int32_t apply_pending;
     PbasConsts c;

@@ -39,149 +39,266 @@ struct MixRec {
     uint32_t perm;
 };
 
-// Classify on the pre-update mixture (used, delta) and, if `active`, update it in
-// place.  With REC, also fill *rec.
-// With `chg`, also report which ranks may hold a different (mean, variance) than
-// before the step: bit r is set when the ranking moved another Gaussian to rank r
-// or when the Gaussian at rank r was matched or replaced (clear bits are certain).
-// With `vsel`, also the (pre-update) variance of the Gaussian attaining delta.
-template <int K, int C, bool REC, int CV = 1>
-__device__ __forceinline__ void mixture_step(Mix<K, C, CV>& m, const float (&X)[C], bool active,
-                                             float alpha, float lam2, float T_bg, float w_init,
-                                             float v_init, float v_min, bool& used,
-                                             float& delta, MixRec* rec, int rho_mode = 0,
-                                             uint32_t* chg = nullptr, float* vsel = nullptr) {
-    if (chg) *chg = 0u;
-    float q[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        if constexpr (CV == 3) {  // squared Mahalanobis distance, diagonal covariance
-            float e = X[0] - m.mu[k][0];
-            float acc = (e * e) / m.v[k];
-            e = X[1] - m.mu[k][1];
-            acc = acc + (e * e) / m.vx[k][0];
-            e = X[2] - m.mu[k][2];
-            acc = acc + (e * e) / m.vx[k][1];
-            q[k] = acc;
-        } else {
-            float e = X[0] - m.mu[k][0];
-            float d2 = e * e;
-#pragma unroll
-            for (int c = 1; c < C; ++c) {
-                e = X[c] - m.mu[k][c];
-                d2 = d2 + e * e;
-            }
-            q[k] = d2 / m.v[k];
-        }
-    }
+// Correctly rounded divisions and square roots are most of a step's arithmetic (K = 3, both
+// mixtures: 18 divisions and 6 square roots, about 280 of 800 vector instructions), and most
+// of them only feed comparisons: is q below lambda^2, which q is the least, is the score
+// negative, is one rank key above the next.  Those are decided on approximate values
+// (hardware reciprocals, a relative error below 2^-21) where these differ by more than
+// kMargin = 2^-17 of themselves; a wavefront in which some lane's values are closer than that
+// decides on the correctly rounded ones instead, so every result is bit for bit that of the
+// rounded operations (K = 5 on the 1280x720 scene: 950 -> 710 vector instructions per
+// wavefront executed).  Margins also rule out what the approximations do not carry: NaN,
+// infinities and the ends of the exponent range all come out as "not certain".
+constexpr float kMargin = 1.0f / 131072.0f;
+constexpr float kBig = 1.0e30f;
+constexpr float kTiny = 1.0e-30f;
 
-    used = m.w[0] > 0.0f;
-    int nused = 0;
+// What the classification of one mixture finds.
+struct MixClass {
+    bool used;    // the mixture has data
+    float delta;  // min q over the background Gaussians (rounded if `rounded`)
+    int amin;     // the first rank attaining it
+    int ks;       // the matched rank, -1: none
+    bool sure;    // the approximate choices are certain to be the rounded ones'
+};
+
+// Squared distance of X to Gaussian k over its variance, correctly rounded step by step.
+template <int K, int C, int CV>
+__device__ __forceinline__ float q_rounded(const Mix<K, C, CV>& m, const float (&X)[C], int k) {
+    if constexpr (CV == 3) {  // squared Mahalanobis distance, diagonal covariance
+        float e = X[0] - m.mu[k][0];
+        float acc = (e * e) / m.v[k];
+        e = X[1] - m.mu[k][1];
+        acc = acc + (e * e) / m.vx[k][0];
+        e = X[2] - m.mu[k][2];
+        acc = acc + (e * e) / m.vx[k][1];
+        return acc;
+    } else {
+        float e = X[0] - m.mu[k][0];
+        float d2 = e * e;
 #pragma unroll
-    for (int k = 0; k < K; ++k) nused += (m.w[k] > 0.0f) ? 1 : 0;
-    int B = nused;
+        for (int c = 1; c < C; ++c) {
+            e = X[c] - m.mu[k][c];
+            d2 = d2 + e * e;
+        }
+        return d2 / m.v[k];
+    }
+}
+
+// The same with approximate reciprocals.
+template <int K, int C, int CV>
+__device__ __forceinline__ float q_approx(const Mix<K, C, CV>& m, const float (&X)[C], int k) {
+    if constexpr (CV == 3) {
+        float e = X[0] - m.mu[k][0];
+        float acc = (e * e) * __builtin_amdgcn_rcpf(m.v[k]);
+        e = X[1] - m.mu[k][1];
+        acc = acc + (e * e) * __builtin_amdgcn_rcpf(m.vx[k][0]);
+        e = X[2] - m.mu[k][2];
+        return acc + (e * e) * __builtin_amdgcn_rcpf(m.vx[k][1]);
+    } else {
+        float e = X[0] - m.mu[k][0];
+        float d2 = e * e;
+#pragma unroll
+        for (int c = 1; c < C; ++c) {
+            e = X[c] - m.mu[k][c];
+            d2 = d2 + e * e;
+        }
+        return d2 * __builtin_amdgcn_rcpf(m.v[k]);
+    }
+}
+
+// The background set: the leading ranks whose weights first sum past T_bg; if they never do,
+// as many leading ranks as have data.
+template <int K, int C, int CV>
+__device__ __forceinline__ void background(const Mix<K, C, CV>& m, float T_bg, bool (&bg)[K]) {
     bool found = false;
     float cum = 0.0f;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
+        bg[k] = !found;
         cum = cum + m.w[k];
-        if (!found && cum > T_bg) {
-            B = k + 1;
-            found = true;
-        }
+        found = found || cum > T_bg;
     }
-    // delta = min over the background Gaussians; the first index attaining it
-    delta = q[0];
-    int amin = 0;
+    if (__any(!found)) {
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) n += (m.w[k] > 0.0f) ? 1 : 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) bg[k] = bg[k] && (found || k < n);
+    }
+}
+
+// delta, its rank and the matched rank for the values q.
+template <int K, int C, int CV>
+__device__ __forceinline__ void choose(MixClass& r, const Mix<K, C, CV>& m, const float (&q)[K], const bool (&bg)[K], float lam2) {
+    r.delta = q[0];
+    r.amin = 0;
 #pragma unroll
     for (int k = 1; k < K; ++k)
-        if (k < B && q[k] < delta) {
-            delta = q[k];
-            amin = k;
+        if (bg[k] && q[k] < r.delta) {
+            r.delta = q[k];
+            r.amin = k;
         }
-    if (vsel) {
-        float vs = var_sum(m, 0);
-#pragma unroll
-        for (int k = 1; k < K; ++k)
-            if (k == amin) vs = var_sum(m, k);
-        *vsel = vs;
-    }
-    if (REC) {
-        rec->argmin = amin;
-        rec->kstar = -1;
-        rec->clamp = false;
-        uint32_t id = 0;
-#pragma unroll
-        for (int k = 0; k < K; ++k) id |= (uint32_t)k << (3 * k);
-        rec->perm = id;
-    }
-
-    if (!active) return;
-
-    int ks = -1;
+    r.ks = -1;
 #pragma unroll
     for (int k = K - 1; k >= 0; --k)
-        if (m.w[k] > 0.0f && q[k] < lam2) ks = k;
+        if (m.w[k] > 0.0f && q[k] < lam2) r.ks = k;
+}
+
+// Classify on rounded values.
+template <int K, int C, int CV>
+__device__ __forceinline__ MixClass classify_rounded(const Mix<K, C, CV>& m, const float (&X)[C], float lam2, float T_bg) {
+    float q[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) q[k] = q_rounded(m, X, k);
+    MixClass r;
+    r.used = m.w[0] > 0.0f;
+    r.sure = true;
+    bool bg[K];
+    background(m, T_bg, bg);
+    choose(r, m, q, bg, lam2);
+    return r;
+}
+
+// Classify on approximate values; `sure` says where every choice is certain.  ARG: the rank
+// attaining delta counts as a choice too (its runner-up must be clearly above it).
+template <int K, int C, int CV, bool ARG>
+__device__ __forceinline__ MixClass classify_approx(const Mix<K, C, CV>& m, const float (&X)[C], float lam2, float T_bg) {
+    float q[K];
+    float near = INFINITY, top = 0.0f;
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        q[k] = q_approx(m, X, k);
+        ok = ok && fabsf(q[k] - lam2) > kMargin * lam2;  // (false for NaN)
+        top = fmaxf(top, fmaxf(q[k], m.v[k]));
+        if constexpr (CV == 3) top = fmaxf(top, fmaxf(m.vx[k][0], m.vx[k][1]));
+    }
+    bool bg[K];
+    background(m, T_bg, bg);
+    MixClass r;
+    r.used = m.w[0] > 0.0f;
+    choose(r, m, q, bg, lam2);
+    if constexpr (ARG && K > 1) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (k != r.amin && (bg[k] || k == 0)) near = fminf(near, q[k]);
+        ok = ok && near > r.delta + kMargin * fabsf(r.delta) + kTiny;
+    }
+    r.sure = ok && top < kBig;
+    return r;
+}
+
+// Update of the mixture after its classification found the match ks: weights, the matched
+// Gaussian or the replaced last one, renormalisation, ranking.  With `chg`, also report which
+// ranks may hold a different (mean, variance) than before the step: bit r is set when the
+// ranking moved another Gaussian to rank r or when the Gaussian at rank r was matched or
+// replaced (clear bits are certain).  With REC, *clamp and *perm record the choices.
+template <int K, int C, bool REC, int CV>
+__device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X)[C], int ks, float alpha, float w_init,
+                                               float v_init, float v_min, int rho_mode, uint32_t* chg, bool* clamp,
+                                               uint32_t* perm) {
+    const bool matched = ks >= 0;
+    const int tgt = matched ? ks : K - 1;
+    // the Gaussian to change, selected once (its update then runs once for the wavefront,
+    // whatever ranks its lanes matched)
+    float mu[C], v = m.v[0], vx[CV == 3 ? 2 : 1];
+#pragma unroll
+    for (int c = 0; c < C; ++c) mu[c] = m.mu[0][c];
+#pragma unroll
+    for (int c = 0; c < (CV == 3 ? 2 : 0); ++c) vx[c] = m.vx[0][c];
+#pragma unroll
+    for (int k = 1; k < K; ++k)
+        if (k == tgt) {
+#pragma unroll
+            for (int c = 0; c < C; ++c) mu[c] = m.mu[k][c];
+            v = m.v[k];
+#pragma unroll
+            for (int c = 0; c < (CV == 3 ? 2 : 0); ++c) vx[c] = m.vx[k][c];
+        }
 
     const float a = 1.0f - alpha;
+    float wm = 0.0f;  // the matched weight after its update
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         float wk = a * m.w[k];
-        if (k == ks) wk = wk + alpha;
+        if (k == ks) {
+            wk = wk + alpha;
+            wm = wk;
+        }
         m.w[k] = wk;
     }
-    if (ks >= 0) {
-        // rate of the matched mean and variance: alpha; alpha over the matched weight
-        // just updated (>= alpha > 0); or alpha times the Eq. (1) density of the
-        // matched Gaussian at the sample, before its update
-        float rho = alpha;
-        if (rho_mode != 0) {
-            float wm = m.w[0], qm = q[0], vm = var_sum(m, 0);
-#pragma unroll
-            for (int k = 1; k < K; ++k)
-                if (k == ks) {
-                    wm = m.w[k];
-                    qm = q[k];
-                    vm = var_sum(m, k);
-                }
-            rho = rho_mode == 1 ? alpha / wm : alpha * (expf(-0.5f * qm) / (6.28318530717958647692f * vm));
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            if (k != ks) continue;
-            float mn[C];
-#pragma unroll
-            for (int c = 0; c < C; ++c) mn[c] = m.mu[k][c] + rho * (X[c] - m.mu[k][c]);
-            if constexpr (CV == 3) {  // each channel's variance on its own deviation and floor
-                float e = X[0] - mn[0];
-                m.v[k] = fmaxf(m.v[k] + rho * (e * e - m.v[k]), v_min);
-                e = X[1] - mn[1];
-                m.vx[k][0] = fmaxf(m.vx[k][0] + rho * (e * e - m.vx[k][0]), v_min);
-                e = X[2] - mn[2];
-                m.vx[k][1] = fmaxf(m.vx[k][1] + rho * (e * e - m.vx[k][1]), v_min);
+    if (!matched) m.w[K - 1] = w_init;
+
+    // rate of the matched mean and variance: alpha; alpha over the matched weight just
+    // updated (>= alpha > 0); or alpha times the Eq. (1) density of the matched Gaussian at
+    // the sample, before its update
+    float rho = alpha;
+    if (rho_mode != 0 && matched) {
+        if (rho_mode == 1) {
+            rho = alpha / wm;
+        } else {
+            float qm = 0.0f, vm = v;
+            if constexpr (CV == 3) {
+                float e = X[0] - mu[0];
+                qm = (e * e) / v;
+                e = X[1] - mu[1];
+                qm = qm + (e * e) / vx[0];
+                e = X[2] - mu[2];
+                qm = qm + (e * e) / vx[1];
+                vm = (v + vx[0]) + vx[1];
             } else {
-                float e = X[0] - mn[0];
+                float e = X[0] - mu[0];
                 float d2 = e * e;
 #pragma unroll
                 for (int c = 1; c < C; ++c) {
-                    e = X[c] - mn[c];
+                    e = X[c] - mu[c];
                     d2 = d2 + e * e;
                 }
-                float vn = m.v[k] + rho * (d2 - m.v[k]);
-                if (REC) rec->clamp = vn < v_min;
-                vn = fmaxf(vn, v_min);
-                m.v[k] = vn;
+                qm = d2 / v;
             }
+            rho = alpha * (expf(-0.5f * qm) / (6.28318530717958647692f * vm));
+        }
+    }
+    float mn[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) mn[c] = mu[c] + rho * (X[c] - mu[c]);
+    bool cl = false;
+    float vn, vxn[CV == 3 ? 2 : 1];
+    if constexpr (CV == 3) {  // each channel's variance on its own deviation and floor
+        float e = X[0] - mn[0];
+        vn = fmaxf(v + rho * (e * e - v), v_min);
+        e = X[1] - mn[1];
+        vxn[0] = fmaxf(vx[0] + rho * (e * e - vx[0]), v_min);
+        e = X[2] - mn[2];
+        vxn[1] = fmaxf(vx[1] + rho * (e * e - vx[1]), v_min);
+        vxn[0] = matched ? vxn[0] : v_init;
+        vxn[1] = matched ? vxn[1] : v_init;
+    } else {
+        float e = X[0] - mn[0];
+        float d2 = e * e;
+#pragma unroll
+        for (int c = 1; c < C; ++c) {
+            e = X[c] - mn[c];
+            d2 = d2 + e * e;
+        }
+        vn = v + rho * (d2 - v);
+        cl = matched && vn < v_min;
+        vn = fmaxf(vn, v_min);
+    }
+    vn = matched ? vn : v_init;
+#pragma unroll
+    for (int c = 0; c < C; ++c) mn[c] = matched ? mn[c] : X[c];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (k == tgt) {
 #pragma unroll
             for (int c = 0; c < C; ++c) m.mu[k][c] = mn[c];
-        }
-    } else {
-        m.w[K - 1] = w_init;
+            m.v[k] = vn;
 #pragma unroll
-        for (int c = 0; c < C; ++c) m.mu[K - 1][c] = X[c];
-        m.v[K - 1] = v_init;
-        if constexpr (CV == 3) m.vx[K - 1][0] = m.vx[K - 1][1] = v_init;
-    }
+            for (int c = 0; c < (CV == 3 ? 2 : 0); ++c) m.vx[k][c] = vxn[c];
+        }
+    if (REC) *clamp = cl;
 
     float S = m.w[0];
 #pragma unroll
@@ -189,88 +306,146 @@ __device__ __forceinline__ void mixture_step(Mix<K, C, CV>& m, const float (&X)[
 #pragma unroll
     for (int k = 0; k < K; ++k) m.w[k] = m.w[k] / S;
 
-    // Rank: insertion network of adjacent compare-exchanges, strictly-greater
-    // swaps only, so equal keys keep their order (stable).
-    if (REC) rec->kstar = ks;
-    float key[K];
-    int idx[K];
+    // Rank by w / sqrt(v), descending, stable.  In a static scene the order rarely changes, so
+    // first look whether every adjacent pair is certain to be in order: clearly apart on
+    // approximate keys, or an unused Gaussian (w = 0, key 0) behind a weight >= 0.  Only a
+    // wavefront with a pair that is not computes the rounded keys, and the insertion network
+    // of adjacent compare-exchanges (strictly-greater swaps only, so equal keys keep their
+    // order) runs only if one of those is out of order.
+    uint32_t moved = 0u, pr = 0u;  // ranks that got another Gaussian; 3 bits per rank: which
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        key[k] = m.w[k] / sqrtf(var_sum(m, k));
-        idx[k] = k;
+    for (int k = 0; k < K; ++k) pr |= (uint32_t)k << (3 * k);
+    uint32_t at = 1u << tgt;       // the ranks where the changed Gaussian is now
+    bool inorder = true;
+    {
+        float above = m.w[0] * __builtin_amdgcn_rsqf(var_sum(m, 0));
+#pragma unroll
+        for (int k = 1; k < K; ++k) {
+            const float ka = m.w[k] * __builtin_amdgcn_rsqf(var_sum(m, k));
+            const bool apart = ka + kMargin * above < above && above > kTiny && above < kBig;
+            inorder = inorder && (apart || (m.w[k] == 0.0f && m.w[k - 1] >= 0.0f));
+            above = ka;
+        }
     }
-    // The network swaps nothing unless some adjacent pair is out of order, which in a
-    // static scene is rare: skip it when no lane of the wavefront needs a swap.
-    bool unsorted = false;
+    if (K > 1 && __any(!inorder)) {
+        float key[K];
+        int idx[K];
 #pragma unroll
-    for (int k = 1; k < K; ++k) unsorted = unsorted || key[k] > key[k - 1];
-    if (__any(unsorted))
+        for (int k = 0; k < K; ++k) {
+            key[k] = m.w[k] / sqrtf(var_sum(m, k));
+            idx[k] = k;
+        }
+        bool unsorted = false;
 #pragma unroll
-    for (int i = 1; i < K; ++i) {
+        for (int k = 1; k < K; ++k) unsorted = unsorted || key[k] > key[k - 1];
+        if (__any(unsorted)) {
 #pragma unroll
-        for (int j = i; j > 0; --j) {
-            const bool sw = key[j] > key[j - 1];
-            float t;
+            for (int i = 1; i < K; ++i) {
+#pragma unroll
+                for (int j = i; j > 0; --j) {
+                    const bool sw = key[j] > key[j - 1];
+                    float t;
 #define FGS_CSWAP(A, B)      \
     t = sw ? (A) : (B);      \
     (A) = sw ? (B) : (A);    \
     (B) = t;
-            FGS_CSWAP(key[j], key[j - 1]);
-            {
-                const int ti = sw ? idx[j] : idx[j - 1];
-                idx[j] = sw ? idx[j - 1] : idx[j];
-                idx[j - 1] = ti;
-            }
-            FGS_CSWAP(m.w[j], m.w[j - 1]);
-            FGS_CSWAP(m.v[j], m.v[j - 1]);
-            if constexpr (CV == 3) {
-                FGS_CSWAP(m.vx[j][0], m.vx[j - 1][0]);
-                FGS_CSWAP(m.vx[j][1], m.vx[j - 1][1]);
-            }
+                    FGS_CSWAP(key[j], key[j - 1]);
+                    {
+                        const int ti = sw ? idx[j] : idx[j - 1];
+                        idx[j] = sw ? idx[j - 1] : idx[j];
+                        idx[j - 1] = ti;
+                    }
+                    FGS_CSWAP(m.w[j], m.w[j - 1]);
+                    FGS_CSWAP(m.v[j], m.v[j - 1]);
+                    if constexpr (CV == 3) {
+                        FGS_CSWAP(m.vx[j][0], m.vx[j - 1][0]);
+                        FGS_CSWAP(m.vx[j][1], m.vx[j - 1][1]);
+                    }
 #pragma unroll
-            for (int c = 0; c < C; ++c) {
-                FGS_CSWAP(m.mu[j][c], m.mu[j - 1][c]);
-            }
+                    for (int c = 0; c < C; ++c) {
+                        FGS_CSWAP(m.mu[j][c], m.mu[j - 1][c]);
+                    }
 #undef FGS_CSWAP
+                }
+            }
+            pr = 0u;
+            at = 0u;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                pr |= (uint32_t)idx[k] << (3 * k);
+                moved |= (idx[k] != k ? 1u : 0u) << k;
+                at |= (idx[k] == tgt ? 1u : 0u) << k;
+            }
         }
     }
-    if (REC) {
-        uint32_t pr = 0;
-#pragma unroll
-        for (int k = 0; k < K; ++k) pr |= (uint32_t)idx[k] << (3 * k);
-        rec->perm = pr;
-    }
-    if (chg) {
-        const int touched = ks >= 0 ? ks : K - 1;  // matched, or replaced
-        uint32_t c = 0;
-#pragma unroll
-        for (int r = 0; r < K; ++r) c |= (uint32_t)(idx[r] != r || idx[r] == touched) << r;
-        *chg = c;
-    }
+    if (REC) *perm = pr;
+    if (chg) *chg = moved | at;
 }
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Classify on the pre-update mixture (used, delta) and, if `active`, update it in place,
+// recording the step's discrete choices.  delta is correctly rounded.
+template <int K, int C>
+__device__ __forceinline__ void mixture_step_rec(Mix<K, C>& m, const float (&X)[C], bool active, float alpha, float lam2,
+                                                 float T_bg, float w_init, float v_init, float v_min, bool sane,
+                                                 bool& used, float& delta, MixRec& rec) {
+    MixClass r = classify_approx<K, C, 1, true>(m, X, lam2, T_bg);
+    if (!sane || __any(!r.sure)) {
+        r = classify_rounded(m, X, lam2, T_bg);
+    } else {
+        Mix<1, C> s;  // the Gaussian attaining delta: one rounded division instead of K
+#pragma unroll
+        for (int c = 0; c < C; ++c) s.mu[0][c] = m.mu[0][c];
+        s.v[0] = m.v[0];
+#pragma unroll
+        for (int k = 1; k < K; ++k)
+            if (k == r.amin) {
+#pragma unroll
+                for (int c = 0; c < C; ++c) s.mu[0][c] = m.mu[k][c];
+                s.v[0] = m.v[k];
+            }
+        r.delta = q_rounded(s, X, 0);
+    }
+    used = r.used;
+    delta = r.delta;
+    rec.argmin = r.amin;
+    rec.kstar = -1;
+    rec.clamp = false;
+    uint32_t id = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) id |= (uint32_t)k << (3 * k);
+    rec.perm = id;
+    if (!active) return;
+    rec.kstar = r.ks;
+    mixture_update<K, C, true, 1>(m, X, r.ks, alpha, w_init, v_init, v_min, 0, nullptr, &rec.clamp, &rec.perm);
+}
+
 // State planes are touched once per frame.  When the device's resident model
 // state exceeds the last-level (Infinity) cache the kernels stream it with
 // non-temporal loads and stores; otherwise ordinary accesses let a cache-sized
 // working set stay resident between frames.
-template <bool NT>
-__device__ __forceinline__ float4 ld_state(const float4* p) {
-    if constexpr (NT) {
-        const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
-        return make_float4(v.x, v.y, v.z, v.w);
-    } else {
-        return *p;
-    }
+// A plane is addressed through a raw buffer resource that starts at the workgroup's first
+// pixel in that plane (scalar registers, rebuilt for the stores), so that one 32-bit lane
+// offset serves every plane: ten 64-bit vector addresses held from the loads to the stores
+// cost K = 5 twenty registers and an occupancy of 5 instead of 6.
+typedef uint32_t st_u32x4 __attribute__((__vector_size__(4 * sizeof(uint32_t))));
+constexpr int kStateWord3 = 0x00020000;  // raw 32-bit buffer, gfx9 family
+
+// Plane k from pixel p0 on (p0 < npix, the same for the whole workgroup); an access past the
+// plane's end is dropped (loads give 0).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t state_rsrc(const float4* state, int64_t npix, int64_t p0, int k) {
+    const int64_t left = (npix - p0) * 16;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float4*>(state) + (int64_t)k * npix + p0, (short)0,
+                                             (int)(left > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)left), kStateWord3);
 }
 template <bool NT>
-__device__ __forceinline__ void st_state(float4* p, float4 v) {
-    if constexpr (NT) {
-        f32x4 w = {v.x, v.y, v.z, v.w};
-        __builtin_nontemporal_store(w, reinterpret_cast<f32x4*>(p));
-    } else {
-        *p = v;
-    }
+__device__ __forceinline__ float4 ld_state(const float4* state, int64_t npix, int64_t p0, int k, uint32_t off) {
+    const st_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(state_rsrc(state, npix, p0, k), off, 0, NT ? 2 : 0);
+    return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
+}
+template <bool NT>
+__device__ __forceinline__ void st_state(float4* state, int64_t npix, int64_t p0, int k, uint32_t off, float4 v) {
+    const st_u32x4 w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
+    __builtin_amdgcn_raw_buffer_store_b128(w, state_rsrc(state, npix, p0, k), off, 0, NT ? 2 : 0);
 }
 
 // Device layout of a GMM model (planes of npix float4, plane-major):
@@ -315,31 +490,41 @@ __device__ __forceinline__ uint32_t sector_or(uint32_t bits) {
     return bits;
 }
 
+// The pixel is p0 + lane; p0 is the same for the whole workgroup.
 template <int KC, int KD, bool NT, int RW = 2, int DEC = 2, int CV = 1>
-__device__ __forceinline__ void gmm_pixel(const GmmStepArgs& a, int p) {
+__device__ __forceinline__ void gmm_pixel(const GmmStepArgs& a, int p0, int lane) {
     using L = GmmLayout<KC, KD, CV>;
     constexpr int E = L::E;
-    const int y = p / a.W;
-    const int x = p - y * a.W;
+    const int64_t npix = a.npix;
+    const uint32_t off = (uint32_t)lane * 16u;
 
     // Every read is issued before any result is used (the frame first, then the
     // state planes): loads complete in order, and the depth code's branch would
     // otherwise wait for the frame before the state reads go out.
-    const uint8_t* px = a.rgb + (int64_t)y * a.rgb_stride + 3 * x;
-    const uint32_t dmm = load_depth(a.depth, a.depth_stride, x, y, a.W, a.H, a.depth_w, a.depth_h);
+    const uint8_t* px;
+    uint32_t dmm;
+    if (a.geom.flat) {
+        px = a.rgb + 3 * (int64_t)p0 + 3 * lane;
+        dmm = *reinterpret_cast<const uint16_t*>(a.depth + 2 * (int64_t)p0 + 2 * lane);
+    } else {
+        const int p = p0 + lane;
+        const int y = (int)div_by((uint32_t)p, a.geom.w);
+        const int x = p - y * a.W;
+        px = a.rgb + (int64_t)y * a.rgb_stride + 3 * x;
+        dmm = load_depth(a.depth, a.depth_stride, x, y, a.W, a.H, a.depth_w, a.depth_h, a.geom);
+    }
     const uint32_t r0 = px[0], r1 = px[1], r2 = px[2];
-    const float4* st = a.state;
     float4 core[KC];
     float4 exv[E];
 #pragma unroll
-    for (int k = 0; k < KC; ++k) core[k] = ld_state<NT>(st + (int64_t)k * a.npix + p);
+    for (int k = 0; k < KC; ++k) core[k] = ld_state<NT>(a.state, npix, p0, k, off);
 #pragma unroll
-    for (int e = 0; e < E; ++e) exv[e] = ld_state<NT>(st + (int64_t)(KC + e) * a.npix + p);
+    for (int e = 0; e < E; ++e) exv[e] = ld_state<NT>(a.state, npix, p0, KC + e, off);
     __builtin_amdgcn_sched_barrier(0);
 
     const float Xc[3] = {(float)r0, (float)r1, (float)r2};
     const bool valid = dmm > 0u;
-    const float Xd[1] = {(float)depth_code(dmm, a.c.depth_max_mm)};
+    const float Xd[1] = {(float)depth_code(dmm, a.c.depth_max_mm, a.c.depth_div)};
     float ex[4 * E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -370,39 +555,60 @@ __device__ __forceinline__ void gmm_pixel(const GmmStepArgs& a, int p) {
     }
 
     const float lam2 = a.c.lam * a.c.lam;
-    bool used_c, used_d;
-    float dc, dd;
-    uint32_t chg_c, chg_d;
-    float vsel_c = 1.0f, vsel_d = 1.0f;
     const int rw = RW == 0 ? 0 : a.c.rho_mode;
     const bool dec = DEC == 2 ? a.c.decision != 0 : DEC == 1;
     float4* so = a.state;
-    mixture_step<KC, 3, false, CV>(mc, Xc, true, a.c.alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_c,
-                               a.c.v_min_c, used_c, dc, nullptr, rw, &chg_c, DEC ? &vsel_c : nullptr);
+    asm volatile("" : "+s"(so));  // the stores' descriptors are built again, not kept since the loads
+    // Both mixtures are classified first, on the pre-update state, and the mask is decided;
+    // the density decision wants rounded values.
+    MixClass cc = classify_approx<KC, 3, CV, false>(mc, Xc, lam2, a.c.T_bg);
+    MixClass cd = classify_approx<KD, 1, 1, false>(md, Xd, lam2, a.c.T_bg);
+    const bool term_c = cc.used;
+    const bool term_d = valid && cd.used;
+    bool fg, sure = cc.sure && (cd.sure || !valid) && a.c.sane != 0 && !(DEC != 0 && dec);
+    {
+        const float wd = a.c.w_depth;
+        const float Z = (term_c ? cc.delta - lam2 : 0.0f) + (term_d ? wd * (cd.delta - lam2) : 0.0f);
+        const float size = (term_c ? fabsf(cc.delta) + lam2 : 0.0f) + (term_d ? wd * (fabsf(cd.delta) + lam2) : 0.0f);
+        fg = Z >= 0.0f;
+        sure = sure && (fabsf(Z) > kMargin * size || !(term_c || term_d));
+    }
+    if (__any(!sure)) {
+        cc = classify_rounded(mc, Xc, lam2, a.c.T_bg);
+        cd = classify_rounded(md, Xd, lam2, a.c.T_bg);
+        if (DEC != 0 && dec) {
+            float vs_c = var_sum(mc, 0), vs_d = md.v[0];
+#pragma unroll
+            for (int k = 1; k < KC; ++k)
+                if (k == cc.amin) vs_c = var_sum(mc, k);
+#pragma unroll
+            for (int k = 1; k < KD; ++k)
+                if (k == cd.amin) vs_d = md.v[k];
+            const float Pc = density_factor(cc.delta, vs_c, a.c.density_scale);
+            const float Pd = density_factor(cd.delta, vs_d, a.c.density_scale);
+            const float P = term_c ? (term_d ? Pc * Pd : Pc) : Pd;
+            fg = P < a.c.density_threshold;
+        } else {
+            const float tc = cc.delta - lam2;
+            const float td = a.c.w_depth * (cd.delta - lam2);
+            const float Z = term_c ? (term_d ? tc + td : tc) : td;
+            fg = Z >= 0.0f;
+        }
+    }
+    a.mask[(int64_t)p0 + lane] = ((term_c || term_d) && fg) ? (uint8_t)255 : (uint8_t)0;
+
+    uint32_t chg_c = 0u, chg_d = 0u;
+    mixture_update<KC, 3, false, CV>(mc, Xc, cc.ks, a.c.alpha, a.c.w_init, a.c.v_init_c, a.c.v_min_c, rw, &chg_c,
+                                     nullptr, nullptr);
     // the colour means and variances are final: store them before the depth step
     const uint32_t wc = sector_or(chg_c);
 #pragma unroll
     for (int k = 0; k < KC; ++k)
         if ((wc >> k) & 1u)
-            st_state<NT>(so + (int64_t)k * a.npix + p, make_float4(mc.mu[k][0], mc.mu[k][1], mc.mu[k][2], mc.v[k]));
-    mixture_step<KD, 1, false>(md, Xd, valid, a.c.alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_d,
-                               a.c.v_min_d, used_d, dd, nullptr, rw, &chg_d, DEC ? &vsel_d : nullptr);
-
-    const bool term_c = used_c;
-    const bool term_d = valid && used_d;
-    bool fg;
-    if (DEC != 0 && dec) {
-        const float Pc = density_factor(dc, vsel_c, a.c.density_scale);
-        const float Pd = density_factor(dd, vsel_d, a.c.density_scale);
-        const float P = term_c ? (term_d ? Pc * Pd : Pc) : Pd;
-        fg = P < a.c.density_threshold;
-    } else {
-        const float tc = dc - lam2;
-        const float td = a.c.w_depth * (dd - lam2);
-        const float Z = term_c ? (term_d ? tc + td : tc) : td;
-        fg = Z >= 0.0f;
-    }
-    a.mask[p] = ((term_c || term_d) && fg) ? (uint8_t)255 : (uint8_t)0;
+            st_state<NT>(so, npix, p0, k, off, make_float4(mc.mu[k][0], mc.mu[k][1], mc.mu[k][2], mc.v[k]));
+    if (valid)
+        mixture_update<KD, 1, false, 1>(md, Xd, cd.ks, a.c.alpha, a.c.w_init, a.c.v_init_d, a.c.v_min_d, rw, &chg_d,
+                                        nullptr, nullptr);
 
     // Which extra floats may change: the colour weights always (the colour mixture
     // is updated every frame), the depth weights where depth > 0 (the depth mixture
@@ -438,7 +644,7 @@ __device__ __forceinline__ void gmm_pixel(const GmmStepArgs& a, int p) {
 #pragma unroll
     for (int e = 0; e < E; ++e)
         if ((we >> e) & 1u)
-            st_state<NT>(so + (int64_t)(KC + e) * a.npix + p,
+            st_state<NT>(so, npix, p0, KC + e, off,
                          make_float4(ex[4 * e + 0], ex[4 * e + 1], ex[4 * e + 2], ex[4 * e + 3]));
 }
 

@@ -6,7 +6,7 @@
 //
 // Arithmetic is IEEE binary32, each operation rounded on its own (the library is
 // built with -ffp-contract=off; division and square root are correctly rounded),
-// in the order of the method:
+// in the order of the method (the approximate decisions of gmm_device.h give the same results):
 //   q_k = d2_k / v_k,  d2 = ((e0*e0) + e1*e1) + e2*e2
 //   decision on the ranked pre-update mixture: B = leading Gaussians whose
 //     weights first sum past T_bg (else those with w > 0), delta = min_{k<B} q_k,
@@ -26,25 +26,32 @@ namespace fgs {
 
 namespace {
 
-// 512 lanes per workgroup: measured on the 8-model 720p step, GMM K=5 per launch 308.2 us
-// with 256 lanes, 302.2 with 512, 313.8 with 1024, 320.9 with 128 (same registers and
-// occupancy; larger workgroups retire in fewer, larger pieces, up to the point where one
-// no longer fits beside another on a CU).
-constexpr int kBlock = 512;
+// 256 lanes per workgroup, and where the state is streamed three workgroups per CU: HBM serves
+// a few pages of every plane better than many.  Measured on 8 models of 1280x720, K = 5, non-
+// temporal, us per launch by waves per CU: 8 288, 12 269.4, 16 283, 20 and more 294 (512-lane
+// workgroups 277 with 16 waves, 286 with 24; 192 lanes 282-294; 128 lanes 272 at best).  Against
+// the 512-lane kernel without the approximate decisions and scalar plane addresses (gmm_device.h):
+// K = 5 280.4 -> 269.4 (6.5 TB/s of HBM traffic), 8 x K = 3 186 -> 177, 6 x 7/3 228 -> 220, one
+// 7/3 1920x1080 91.5 -> 88.4.  Two planes a pixel (K = 1) are too few bytes per wave for that
+// (76 -> 91 us with the limit), so it holds from six planes (K = 3) on.  A cache-resident state
+// wants every wave it can get: K = 3 per-channel variances at 853x487, 17.6 -> 16.1 us.
+constexpr int kBlock = 256;
+constexpr int kStreamPlanes = 6;
+constexpr unsigned kStreamLds = 48u << 10;  // 3 of these fit a CU's 160 KiB; nothing is kept there
 
 // GEN = false: the default rate and decision compiled in; GEN = true: both read
 // from the constants (any other choice).  CV = 3: per-channel colour variances.
 // One launch steps b.n models (one for a single push): workgroup w takes pixels
-// 256 (w - first[i]) .. +255 of model i, first[i] <= w < first[i + 1].
+// kBlock (w - first[i]) .. + kBlock - 1 of model i, first[i] <= w < first[i + 1].
 template <int NB, int KC, int KD, bool NT, bool GEN, int CV>
 __global__ __launch_bounds__(kBlock) void gmm_step_kernel(GmmBatch<NB> b) {
     const int w = (int)blockIdx.x;
     int i = 0;
 #pragma unroll
-    for (int j = 1; j < NB; ++j) i += (j < b.n && w >= b.first[j]) ? 1 : 0;
+    for (int j = 1; j < NB; ++j) i = w >= b.first[j] ? j : i;  // (first[j] is the grid size for j >= n)
     const GmmStepArgs& a = b.a[i];
-    const int p = (w - b.first[i]) * kBlock + (int)threadIdx.x;
-    if (p < a.npix) gmm_pixel<KC, KD, NT, GEN ? 2 : 0, GEN ? 2 : 0, CV>(a, p);
+    const int p0 = (w - b.first[i]) * kBlock, lane = (int)threadIdx.x;
+    if (p0 + lane < a.npix) gmm_pixel<KC, KD, NT, GEN ? 2 : 0, GEN ? 2 : 0, CV>(a, p0, lane);
 }
 
 // Run-time Kc, Kd indices of the extra-plane fields (fgs_internal.h).
@@ -136,8 +143,10 @@ __global__ void gmm_import_kernel(float4* state, const float* in, int Kc, int Kd
 
 template <int NB, int KC, int KD, bool GEN, int CV>
 void launch_step_g(const GmmBatch<NB>& b, unsigned grid, hipStream_t s) {
+    constexpr int kPlanes = KC + GmmLayout<KC, KD, CV>::E;
     if (b.a[0].streaming)
-        hipLaunchKernelGGL((gmm_step_kernel<NB, KC, KD, true, GEN, CV>), dim3(grid), dim3(kBlock), 0, s, b);
+        hipLaunchKernelGGL((gmm_step_kernel<NB, KC, KD, true, GEN, CV>), dim3(grid), dim3(kBlock),
+                           kPlanes >= kStreamPlanes ? kStreamLds : 0, s, b);
     else
         hipLaunchKernelGGL((gmm_step_kernel<NB, KC, KD, false, GEN, CV>), dim3(grid), dim3(kBlock), 0, s, b);
 }

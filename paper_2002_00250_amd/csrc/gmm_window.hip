@@ -82,7 +82,7 @@ __device__ __forceinline__ Input load_input(const GmmWindowArgs& a, int t, int p
     in.Xc[1] = (float)px[1];
     in.Xc[2] = (float)px[2];
     in.valid = dmm > 0u;
-    in.Xd[0] = (float)depth_code(dmm, a.c.depth_max_mm);
+    in.Xd[0] = (float)depth_code(dmm, a.c.depth_max_mm, a.c.depth_div);
     return in;
 }
 
@@ -92,6 +92,7 @@ __global__ __launch_bounds__(kBlock) void gmm_window_forward_kernel(GmmWindowArg
     if (p >= a.npix) return;
     const float alpha = a.theta[0], lam = a.theta[1], wd = a.theta[2];
     const float lam2 = lam * lam;
+    const bool sane = gmm_sane(lam, wd, a.c.v_min_c, a.c.v_min_d, a.c.v_init_c, a.c.v_init_d);
     Mix<K, 3> mc;
     Mix<K, 1> md;
 #pragma unroll
@@ -121,10 +122,10 @@ __global__ __launch_bounds__(kBlock) void gmm_window_forward_kernel(GmmWindowArg
         bool used_c, used_d;
         float dc, dd;
         MixRec rc, rd;
-        mixture_step<K, 3, true>(mc, in.Xc, true, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_c,
-                                 a.c.v_min_c, used_c, dc, &rc);
-        mixture_step<K, 1, true>(md, in.Xd, in.valid, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_d,
-                                 a.c.v_min_d, used_d, dd, &rd);
+        mixture_step_rec(mc, in.Xc, true, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_c, a.c.v_min_c, sane,
+                         used_c, dc, rc);
+        mixture_step_rec(md, in.Xd, in.valid, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_d, a.c.v_min_d, sane,
+                         used_d, dd, rd);
         const bool term_c = used_c, term_d = in.valid && used_d;
         const float tc = dc - lam2;
         const float td = wd * (dd - lam2);

@@ -246,7 +246,7 @@ __device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by,
     const uint2 Sv = a.m.S[p];
     uint32_t lastw = in_pad ? 0u : a.m.last[p];
     const uint8_t* px = a.rgb + (int64_t)y * a.rgb_stride + 3 * x;
-    const uint32_t dmm = load_depth(a.depth, a.depth_stride, x, y, a.W, a.H, a.depth_w, a.depth_h);
+    const uint32_t dmm = load_depth(a.depth, a.depth_stride, x, y, a.W, a.H, a.depth_w, a.depth_h, a.geom);
     const uint32_t I0 = px[0], I1 = px[1], I2 = px[2];
     __builtin_amdgcn_sched_barrier(0);
 
@@ -276,7 +276,7 @@ __device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by,
 
     // Ingest (the depth code needs the depth read; computed once every read is issued).
     const bool valid = dmm > 0u;
-    const uint32_t I3 = depth_code(dmm, a.c.depth_max_mm);
+    const uint32_t I3 = depth_code(dmm, a.c.depth_max_mm, a.c.depth_div);
     const uint32_t Iw = I0 | (I1 << 8) | (I2 << 16) | (I3 << 24);
     float R[4] = {Rv.x, Rv.y, Rv.z, Rv.w};
     float T[4] = {Tv.x, Tv.y, Tv.z, Tv.w};
@@ -497,11 +497,11 @@ __device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by,
 
 // Frames 0..N-1: sample slot t takes the frame; the mask is empty.
 __device__ __forceinline__ void fill_pixel(const PbasStepArgs& a, int p) {
-    const int y = p / a.W, x = p - (p / a.W) * a.W;
+    const int y = (int)div_by((uint32_t)p, a.geom.w), x = p - y * a.W;
     const uint8_t* px = a.rgb + (int64_t)y * a.rgb_stride + 3 * x;
-    const uint32_t dmm = load_depth(a.depth, a.depth_stride, x, y, a.W, a.H, a.depth_w, a.depth_h);
+    const uint32_t dmm = load_depth(a.depth, a.depth_stride, x, y, a.W, a.H, a.depth_w, a.depth_h, a.geom);
     const uint32_t Iw = (uint32_t)px[0] | ((uint32_t)px[1] << 8) | ((uint32_t)px[2] << 16) |
-                        (depth_code(dmm, a.c.depth_max_mm) << 24);
+                        (depth_code(dmm, a.c.depth_max_mm, a.c.depth_div) << 24);
     *reinterpret_cast<uint32_t*>(sample_byte(a.m.samples, a.npix, (int)a.t, p, 0)) = Iw;
     if (a.m.last_in_pad)
         *reinterpret_cast<uint32_t*>(sample_byte(a.m.samples, a.npix, a.c.N, p, 0)) = Iw;

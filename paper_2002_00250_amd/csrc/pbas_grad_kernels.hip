@@ -80,10 +80,10 @@ __device__ __forceinline__ void add_magnitudes(unsigned long long* gsum, uint32_
 
 __device__ __forceinline__ uint32_t frame_word(const PbasGradArgs& a, int x, int y, bool& valid) {
     const uint8_t* px = a.rgb + (int64_t)y * a.rgb_stride + 3 * x;
-    const uint32_t dmm = load_depth(a.depth, a.depth_stride, x, y, a.W, a.H, a.depth_w, a.depth_h);
+    const uint32_t dmm = load_depth(a.depth, a.depth_stride, x, y, a.W, a.H, a.depth_w, a.depth_h, a.geom);
     valid = dmm > 0u;
     return (uint32_t)px[0] | ((uint32_t)px[1] << 8) | ((uint32_t)px[2] << 16) |
-           (depth_code(dmm, a.c.depth_max_mm) << 24);
+           (depth_code(dmm, a.c.depth_max_mm, a.c.depth_div) << 24);
 }
 
 // Frames 0..N-1: slot t takes the frame's value and magnitudes; the mask is empty.
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kBlock) void pbas_grad_fill_kernel(PbasGradArgs a) 
     const int p = blockIdx.x * kBlock + threadIdx.x;
     const bool inside = p < a.npix;
     const int q = inside ? p : 0;
-    const int y = q / a.W, x = q - y * a.W;
+    const int y = (int)div_by((uint32_t)q, a.geom.w), x = q - y * a.W;
     bool valid;
     const uint32_t v = frame_word(a, x, y, valid);
     const uint32_t mw = colour_magnitudes(a.rgb, a.rgb_stride, x, y, a.W, a.H);

@@ -33,7 +33,7 @@ __global__ __launch_bounds__(kBlock) void pbas_step_kernel(PbasBatch<NB> b) {
     const int w = (int)blockIdx.x;
     int i = 0;
 #pragma unroll
-    for (int j = 1; j < NB; ++j) i += (j < b.n && w >= b.first[j]) ? 1 : 0;
+    for (int j = 1; j < NB; ++j) i = w >= b.first[j] ? j : i;  // (first[j] is the grid size for j >= n)
     const int local = w - b.first[i], tiles_x = b.tiles_x[i];
     pbas_tile<NMAX, class_min(NMAX), NT>(b.a[i], local % tiles_x, local / tiles_x, sh);
 }

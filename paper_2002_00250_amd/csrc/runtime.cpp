@@ -208,8 +208,21 @@ GmmConsts fgs::gmm_consts(const fgs_gmm_params& p) {
     const float vm = p.var_mode ? p.v_min_c / 3.0f : p.v_min_c;
     return GmmConsts{p.alpha, p.lambda,   p.T_bg,    p.w_init,
                      vi,      vm,         p.v_init_d, p.v_min_d,
-                     p.w_depth, (uint32_t)p.depth_max_mm, p.rho_mode,
-                     p.decision == 1 ? 1 : 0, p.density_scale, p.density_threshold, p.var_mode};
+                     p.w_depth, (uint32_t)p.depth_max_mm, fast_div((uint32_t)p.depth_max_mm), p.rho_mode,
+                     p.decision == 1 ? 1 : 0, p.density_scale, p.density_threshold, p.var_mode,
+                     gmm_sane(p.lambda, p.w_depth, vm, p.v_min_d, vi, p.v_init_d) ? 1 : 0};
+}
+
+FrameGeom fgs::frame_geom(int32_t H, int32_t W, int64_t rgb_stride, int64_t depth_stride, int32_t depth_h,
+                          int32_t depth_w) {
+    FrameGeom g;
+    g.flat = depth_w == 0 && rgb_stride == 3 * (int64_t)W && depth_stride == 2 * (int64_t)W ? 1 : 0;
+    constexpr int64_t kLimit = (int64_t)1 << 31;
+    g.small = 2 * (int64_t)W * depth_w < kLimit && 2 * (int64_t)H * depth_h < kLimit ? 1 : 0;
+    g.w = fast_div((uint32_t)W);
+    g.w2 = fast_div(2 * (uint32_t)W);
+    g.h2 = fast_div(2 * (uint32_t)H);
+    return g;
 }
 
 bool fgs::model_use_streaming(const fgs_model* m) {
@@ -232,6 +245,7 @@ void fgs::model_next_gmm(fgs_model* m, const uint8_t* rgb, int64_t rs, const uin
     a->H = m->H;
     a->W = m->W;
     a->npix = m->npix;
+    a->geom = frame_geom(m->H, m->W, rs, ds, dh, dw);
     a->streaming = model_use_streaming(m) ? 1 : 0;
     a->c = m->gc;
     m->t += 1;
@@ -249,6 +263,7 @@ void fgs::model_next_pbas(fgs_model* m, const uint8_t* rgb, int64_t rs, const ui
     a->H = m->H;
     a->W = m->W;
     a->npix = m->npix;
+    a->geom = frame_geom(m->H, m->W, rs, ds, dh, dw);
     a->t = (uint32_t)m->t;
     a->apply_pending = m->pending ? 1 : 0;
     a->streaming = model_use_streaming(m) ? 1 : 0;
@@ -269,6 +284,7 @@ void fgs::model_next_pbas_grad(fgs_model* m, const uint8_t* rgb, int64_t rs, con
     a->H = m->H;
     a->W = m->W;
     a->npix = m->npix;
+    a->geom = frame_geom(m->H, m->W, rs, ds, dh, dw);
     a->t = (uint32_t)m->t;
     a->apply_pending = m->pending ? 1 : 0;
     a->c = m->pc;
@@ -402,6 +418,7 @@ fgs_status fgs_create(fgs_algo algo, int32_t H, int32_t W, const void* params, v
     m->pc.T_upper = m->pp.T_upper;
     for (int j = 0; j < 4; ++j) m->pc.R_lower[j] = m->pp.R_lower[j];
     m->pc.depth_max_mm = (uint32_t)m->pp.depth_max_mm;
+    m->pc.depth_div = fast_div((uint32_t)m->pp.depth_max_mm);
     m->pc.key0 = (uint32_t)(m->pp.seed & 0xFFFFFFFFu);
     m->pc.key1 = (uint32_t)(m->pp.seed >> 32);
     m->pc.grad_alpha = m->pp.grad_alpha;

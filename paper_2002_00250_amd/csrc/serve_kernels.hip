@@ -28,8 +28,8 @@ __global__ __launch_bounds__(256) void serve_kernel(const ServeEntry* __restrict
         const ServeEntry& e = entries[lo];
         const int local = w - prefix[lo];
         if (e.algo == FGS_GMM) {
-            const int p = local * 256 + (int)threadIdx.x;
-            if (p < e.g.npix) gmm_pixel<KG, KG, NT>(e.g, p);
+            const int p0 = local * 256, lane = (int)threadIdx.x;
+            if (p0 + lane < e.g.npix) gmm_pixel<KG, KG, NT>(e.g, p0, lane);
         } else if (e.fill) {
             const int p = local * 256 + (int)threadIdx.x;
             if (p < e.p.npix) pbas::fill_pixel(e.p, p);
