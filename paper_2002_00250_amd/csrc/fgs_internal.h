@@ -130,11 +130,16 @@ struct GmmWindowArgs {
     float* Z;               // [T][npix] pre-update scores (0 where no term)
     uint8_t* has;           // [T][npix] 1 where Z has a term
     uint64_t* rec;          // [T][npix] recorded discrete choices
-    float* ckpt;            // [nseg][6K][npix]
-    float* scratch;         // [E][6K][npix]
+    int32_t saved;          // 1: scratch holds every frame, written by the forward
+    float* ckpt;            // [nseg][6K][npix]; saved: [6K][npix], before the last frame
+    float* scratch;         // [rows][npix] float4, then [rows][npix] float2, rows = E (saved: T)
     const float* dZ;        // [T][npix]
     double* partial;        // [blocks][3]
     double* dtheta;         // [3]
+    __host__ __device__ float4* scratch4() const { return reinterpret_cast<float4*>(scratch); }
+    __host__ __device__ float2* scratch2() const {
+        return reinterpret_cast<float2*>(scratch + 4 * (int64_t)(saved ? T : E) * npix);
+    }
 };
 bool gmm_window_supported(int K);
 int gmm_window_blocks(int npix);

@@ -32,11 +32,13 @@ __device__ __forceinline__ float var_sum(const Mix<K, C, CV>& m, int k) {
 // The discrete choices of one step, recorded for the adjoint: the Gaussian that
 // attains delta, the matched Gaussian (-1: replacement), whether the variance floor
 // applied, and the ranking (3 bits per rank: the pre-ranking index now at that rank).
+template <int C>
 struct MixRec {
     int argmin;
     int kstar;
     bool clamp;
     uint32_t perm;
+    float mu[C], v;  // the changed Gaussian's mean and variance before the step
 };
 
 // Correctly rounded divisions and square roots are most of a step's arithmetic (K = 3, both
@@ -51,7 +53,10 @@ struct MixRec {
 // infinities and the ends of the exponent range all come out as "not certain".
 constexpr float kMargin = 1.0f / 131072.0f;
 constexpr float kBig = 1.0e30f;
-constexpr float kTiny = 1.0e-30f;
+constexpr float kTiny = 1.0e-35f;
+
+__device__ __forceinline__ bool any_lane(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0; }
+__device__ __forceinline__ uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
 
 // What the classification of one mixture finds.
 struct MixClass {
@@ -59,7 +64,8 @@ struct MixClass {
     float delta;  // min q over the background Gaussians (rounded if `rounded`)
     int amin;     // the first rank attaining it
     int ks;       // the matched rank, -1: none
-    bool sure;    // the approximate choices are certain to be the rounded ones'
+    bool sure;    // the approximate choices are certain to be the rounded ones', and every
+                  // weight, variance and distance is in [0, kBig)
 };
 
 // Squared distance of X to Gaussian k over its variance, correctly rounded step by step.
@@ -111,6 +117,7 @@ __device__ __forceinline__ float q_approx(const Mix<K, C, CV>& m, const float (&
 // as many leading ranks as have data.
 template <int K, int C, int CV>
 __device__ __forceinline__ void background(const Mix<K, C, CV>& m, float T_bg, bool (&bg)[K]) {
+    int n = 0;
     bool found = false;
     float cum = 0.0f;
 #pragma unroll
@@ -118,31 +125,32 @@ __device__ __forceinline__ void background(const Mix<K, C, CV>& m, float T_bg, b
         bg[k] = !found;
         cum = cum + m.w[k];
         found = found || cum > T_bg;
+        n += (m.w[k] > 0.0f) ? 1 : 0;
     }
-    if (__any(!found)) {
-        int n = 0;
 #pragma unroll
-        for (int k = 0; k < K; ++k) n += (m.w[k] > 0.0f) ? 1 : 0;
-#pragma unroll
-        for (int k = 0; k < K; ++k) bg[k] = bg[k] && (found || k < n);
-    }
+    for (int k = 0; k < K; ++k) bg[k] = bg[k] && (found || k < n);
 }
 
-// delta, its rank and the matched rank for the values q.
+// delta, its rank and the matched rank for the values q; the least background value that is
+// not delta's own (infinity if there is none).
 template <int K, int C, int CV>
-__device__ __forceinline__ void choose(MixClass& r, const Mix<K, C, CV>& m, const float (&q)[K], const bool (&bg)[K], float lam2) {
+__device__ __forceinline__ float choose(MixClass& r, const Mix<K, C, CV>& m, const float (&q)[K], const bool (&bg)[K],
+                                        float lam2) {
+    float next = INFINITY;
     r.delta = q[0];
     r.amin = 0;
 #pragma unroll
-    for (int k = 1; k < K; ++k)
-        if (bg[k] && q[k] < r.delta) {
-            r.delta = q[k];
-            r.amin = k;
-        }
+    for (int k = 1; k < K; ++k) {
+        const bool less = bg[k] && q[k] < r.delta;
+        const float other = less ? r.delta : (bg[k] ? q[k] : INFINITY);
+        next = other < next ? other : next;
+        r.delta = less ? q[k] : r.delta;
+        r.amin = less ? k : r.amin;
+    }
     r.ks = -1;
 #pragma unroll
-    for (int k = K - 1; k >= 0; --k)
-        if (m.w[k] > 0.0f && q[k] < lam2) r.ks = k;
+    for (int k = K - 1; k >= 0; --k) r.ks = m.w[k] > 0.0f && q[k] < lam2 ? k : r.ks;
+    return next;
 }
 
 // Classify on rounded values.
@@ -165,27 +173,23 @@ __device__ __forceinline__ MixClass classify_rounded(const Mix<K, C, CV>& m, con
 template <int K, int C, int CV, bool ARG>
 __device__ __forceinline__ MixClass classify_approx(const Mix<K, C, CV>& m, const float (&X)[C], float lam2, float T_bg) {
     float q[K];
-    float near = INFINITY, top = 0.0f;
+    uint32_t top = 0u;  // the largest bit pattern: at or above kBig's for a sign, an infinity or a NaN
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         q[k] = q_approx(m, X, k);
-        ok = ok && fabsf(q[k] - lam2) > kMargin * lam2;  // (false for NaN)
-        top = fmaxf(top, fmaxf(q[k], m.v[k]));
-        if constexpr (CV == 3) top = fmaxf(top, fmaxf(m.vx[k][0], m.vx[k][1]));
+        ok = ok && fabsf(q[k] - lam2) > kMargin * lam2;
+        top = umax(top, umax(__float_as_uint(q[k]), __float_as_uint(m.v[k])));
+        top = umax(top, __float_as_uint(m.w[k]));
+        if constexpr (CV == 3) top = umax(top, umax(__float_as_uint(m.vx[k][0]), __float_as_uint(m.vx[k][1])));
     }
     bool bg[K];
     background(m, T_bg, bg);
     MixClass r;
     r.used = m.w[0] > 0.0f;
-    choose(r, m, q, bg, lam2);
-    if constexpr (ARG && K > 1) {
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (k != r.amin && (bg[k] || k == 0)) near = fminf(near, q[k]);
-        ok = ok && near > r.delta + kMargin * fabsf(r.delta) + kTiny;
-    }
-    r.sure = ok && top < kBig;
+    const float next = choose(r, m, q, bg, lam2);
+    if constexpr (ARG && K > 1) ok = ok && next > __builtin_fmaf(kMargin, r.delta, r.delta) + kTiny;
+    r.sure = ok && top < __float_as_uint(kBig);
     return r;
 }
 
@@ -193,11 +197,12 @@ __device__ __forceinline__ MixClass classify_approx(const Mix<K, C, CV>& m, cons
 // Gaussian or the replaced last one, renormalisation, ranking.  With `chg`, also report which
 // ranks may hold a different (mean, variance) than before the step: bit r is set when the
 // ranking moved another Gaussian to rank r or when the Gaussian at rank r was matched or
-// replaced (clear bits are certain).  With REC, *clamp and *perm record the choices.
+// replaced (clear bits are certain).  With REC, *rec records the choices.  `plain`: in no lane
+// of the wavefront is a weight or a variance negative, infinite or NaN.
 template <int K, int C, bool REC, int CV>
 __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X)[C], int ks, float alpha, float w_init,
-                                               float v_init, float v_min, int rho_mode, uint32_t* chg, bool* clamp,
-                                               uint32_t* perm) {
+                                               float v_init, float v_min, int rho_mode, bool plain, uint32_t* chg,
+                                               MixRec<C>* rec) {
     const bool matched = ks >= 0;
     const int tgt = matched ? ks : K - 1;
     // the Gaussian to change, selected once (its update then runs once for the wavefront,
@@ -208,14 +213,14 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
 #pragma unroll
     for (int c = 0; c < (CV == 3 ? 2 : 0); ++c) vx[c] = m.vx[0][c];
 #pragma unroll
-    for (int k = 1; k < K; ++k)
-        if (k == tgt) {
+    for (int k = 1; k < K; ++k) {
+        const bool here = k == tgt;
 #pragma unroll
-            for (int c = 0; c < C; ++c) mu[c] = m.mu[k][c];
-            v = m.v[k];
+        for (int c = 0; c < C; ++c) mu[c] = here ? m.mu[k][c] : mu[c];
+        v = here ? m.v[k] : v;
 #pragma unroll
-            for (int c = 0; c < (CV == 3 ? 2 : 0); ++c) vx[c] = m.vx[k][c];
-        }
+        for (int c = 0; c < (CV == 3 ? 2 : 0); ++c) vx[c] = here ? m.vx[k][c] : vx[c];
+    }
 
     const float a = 1.0f - alpha;
     float wm = 0.0f;  // the matched weight after its update
@@ -290,15 +295,20 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
 #pragma unroll
     for (int c = 0; c < C; ++c) mn[c] = matched ? mn[c] : X[c];
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (k == tgt) {
+    for (int k = 0; k < K; ++k) {
+        const bool here = k == tgt;
 #pragma unroll
-            for (int c = 0; c < C; ++c) m.mu[k][c] = mn[c];
-            m.v[k] = vn;
+        for (int c = 0; c < C; ++c) m.mu[k][c] = here ? mn[c] : m.mu[k][c];
+        m.v[k] = here ? vn : m.v[k];
 #pragma unroll
-            for (int c = 0; c < (CV == 3 ? 2 : 0); ++c) m.vx[k][c] = vxn[c];
-        }
-    if (REC) *clamp = cl;
+        for (int c = 0; c < (CV == 3 ? 2 : 0); ++c) m.vx[k][c] = here ? vxn[c] : m.vx[k][c];
+    }
+    if (REC) {
+        rec->clamp = cl;
+#pragma unroll
+        for (int c = 0; c < C; ++c) rec->mu[c] = mu[c];
+        rec->v = v;
+    }
 
     float S = m.w[0];
 #pragma unroll
@@ -308,7 +318,7 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
 
     // Rank by w / sqrt(v), descending, stable.  In a static scene the order rarely changes, so
     // first look whether every adjacent pair is certain to be in order: clearly apart on
-    // approximate keys, or an unused Gaussian (w = 0, key 0) behind a weight >= 0.  Only a
+    // approximate keys, or the lower one unused (w = 0, key 0).  Only a
     // wavefront with a pair that is not computes the rounded keys, and the insertion network
     // of adjacent compare-exchanges (strictly-greater swaps only, so equal keys keep their
     // order) runs only if one of those is out of order.
@@ -316,18 +326,19 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
 #pragma unroll
     for (int k = 0; k < K; ++k) pr |= (uint32_t)k << (3 * k);
     uint32_t at = 1u << tgt;       // the ranks where the changed Gaussian is now
-    bool inorder = true;
+    bool inorder = plain;
     {
         float above = m.w[0] * __builtin_amdgcn_rsqf(var_sum(m, 0));
 #pragma unroll
         for (int k = 1; k < K; ++k) {
             const float ka = m.w[k] * __builtin_amdgcn_rsqf(var_sum(m, k));
-            const bool apart = ka + kMargin * above < above && above > kTiny && above < kBig;
-            inorder = inorder && (apart || (m.w[k] == 0.0f && m.w[k - 1] >= 0.0f));
+            // (keys below kTiny, where rounding is no longer relative, are not apart)
+            const bool apart = __builtin_fmaf(above, 1.0f - kMargin, -kTiny) > ka;
+            inorder = inorder && (apart || m.w[k] == 0.0f);
             above = ka;
         }
     }
-    if (K > 1 && __any(!inorder)) {
+    if (K > 1 && any_lane(!inorder)) {
         float key[K];
         int idx[K];
 #pragma unroll
@@ -338,7 +349,7 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
         bool unsorted = false;
 #pragma unroll
         for (int k = 1; k < K; ++k) unsorted = unsorted || key[k] > key[k - 1];
-        if (__any(unsorted)) {
+        if (any_lane(unsorted)) {
 #pragma unroll
             for (int i = 1; i < K; ++i) {
 #pragma unroll
@@ -378,7 +389,7 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
             }
         }
     }
-    if (REC) *perm = pr;
+    if (REC) rec->perm = pr;
     if (chg) *chg = moved | at;
 }
 
@@ -387,9 +398,10 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
 template <int K, int C>
 __device__ __forceinline__ void mixture_step_rec(Mix<K, C>& m, const float (&X)[C], bool active, float alpha, float lam2,
                                                  float T_bg, float w_init, float v_init, float v_min, bool sane,
-                                                 bool& used, float& delta, MixRec& rec) {
+                                                 bool& used, float& delta, MixRec<C>& rec) {
     MixClass r = classify_approx<K, C, 1, true>(m, X, lam2, T_bg);
-    if (!sane || __any(!r.sure)) {
+    const bool plain = sane && !any_lane(!r.sure);
+    if (!plain) {
         r = classify_rounded(m, X, lam2, T_bg);
     } else {
         Mix<1, C> s;  // the Gaussian attaining delta: one rounded division instead of K
@@ -397,12 +409,12 @@ __device__ __forceinline__ void mixture_step_rec(Mix<K, C>& m, const float (&X)[
         for (int c = 0; c < C; ++c) s.mu[0][c] = m.mu[0][c];
         s.v[0] = m.v[0];
 #pragma unroll
-        for (int k = 1; k < K; ++k)
-            if (k == r.amin) {
+        for (int k = 1; k < K; ++k) {
+            const bool here = k == r.amin;
 #pragma unroll
-                for (int c = 0; c < C; ++c) s.mu[0][c] = m.mu[k][c];
-                s.v[0] = m.v[k];
-            }
+            for (int c = 0; c < C; ++c) s.mu[0][c] = here ? m.mu[k][c] : s.mu[0][c];
+            s.v[0] = here ? m.v[k] : s.v[0];
+        }
         r.delta = q_rounded(s, X, 0);
     }
     used = r.used;
@@ -410,13 +422,15 @@ __device__ __forceinline__ void mixture_step_rec(Mix<K, C>& m, const float (&X)[
     rec.argmin = r.amin;
     rec.kstar = -1;
     rec.clamp = false;
-    uint32_t id = 0;
+    rec.perm = 0u;
 #pragma unroll
-    for (int k = 0; k < K; ++k) id |= (uint32_t)k << (3 * k);
-    rec.perm = id;
+    for (int k = 0; k < K; ++k) rec.perm |= (uint32_t)k << (3 * k);
+#pragma unroll
+    for (int c = 0; c < C; ++c) rec.mu[c] = 0.0f;
+    rec.v = 0.0f;
     if (!active) return;
     rec.kstar = r.ks;
-    mixture_update<K, C, true, 1>(m, X, r.ks, alpha, w_init, v_init, v_min, 0, nullptr, &rec.clamp, &rec.perm);
+    mixture_update<K, C, true, 1>(m, X, r.ks, alpha, w_init, v_init, v_min, 0, plain, nullptr, &rec);
 }
 
 // State planes are touched once per frame.  When the device's resident model
@@ -569,11 +583,12 @@ __device__ __forceinline__ void gmm_pixel(const GmmStepArgs& a, int p0, int lane
     {
         const float wd = a.c.w_depth;
         const float Z = (term_c ? cc.delta - lam2 : 0.0f) + (term_d ? wd * (cd.delta - lam2) : 0.0f);
-        const float size = (term_c ? fabsf(cc.delta) + lam2 : 0.0f) + (term_d ? wd * (fabsf(cd.delta) + lam2) : 0.0f);
+        const float size = (term_c ? cc.delta + lam2 : 0.0f) + (term_d ? wd * (cd.delta + lam2) : 0.0f);
         fg = Z >= 0.0f;
         sure = sure && (fabsf(Z) > kMargin * size || !(term_c || term_d));
     }
-    if (__any(!sure)) {
+    const bool plain = !any_lane(!sure);
+    if (!plain) {
         cc = classify_rounded(mc, Xc, lam2, a.c.T_bg);
         cd = classify_rounded(md, Xd, lam2, a.c.T_bg);
         if (DEC != 0 && dec) {
@@ -598,8 +613,8 @@ __device__ __forceinline__ void gmm_pixel(const GmmStepArgs& a, int p0, int lane
     a.mask[(int64_t)p0 + lane] = ((term_c || term_d) && fg) ? (uint8_t)255 : (uint8_t)0;
 
     uint32_t chg_c = 0u, chg_d = 0u;
-    mixture_update<KC, 3, false, CV>(mc, Xc, cc.ks, a.c.alpha, a.c.w_init, a.c.v_init_c, a.c.v_min_c, rw, &chg_c,
-                                     nullptr, nullptr);
+    mixture_update<KC, 3, false, CV>(mc, Xc, cc.ks, a.c.alpha, a.c.w_init, a.c.v_init_c, a.c.v_min_c, rw, plain,
+                                     &chg_c, nullptr);
     // the colour means and variances are final: store them before the depth step
     const uint32_t wc = sector_or(chg_c);
 #pragma unroll
@@ -607,8 +622,8 @@ __device__ __forceinline__ void gmm_pixel(const GmmStepArgs& a, int p0, int lane
         if ((wc >> k) & 1u)
             st_state<NT>(so, npix, p0, k, off, make_float4(mc.mu[k][0], mc.mu[k][1], mc.mu[k][2], mc.v[k]));
     if (valid)
-        mixture_update<KD, 1, false, 1>(md, Xd, cd.ks, a.c.alpha, a.c.w_init, a.c.v_init_d, a.c.v_min_d, rw, &chg_d,
-                                        nullptr, nullptr);
+        mixture_update<KD, 1, false, 1>(md, Xd, cd.ks, a.c.alpha, a.c.w_init, a.c.v_init_d, a.c.v_min_d, rw, plain,
+                                        &chg_d, nullptr);
 
     // Which extra floats may change: the colour weights always (the colour mixture
     // is updated every frame), the depth weights where depth > 0 (the depth mixture

@@ -13,12 +13,24 @@
 //
 // Backward: with the recorded choices held fixed the weights reach Z only through
 // discrete choices, so their adjoints vanish; alpha's gradient flows through the
-// matched Gaussian's mean and variance updates.  Each lane walks the segments in
-// reverse: it replays the segment's means/variances from the checkpoint into a
-// scratch buffer (same fp32 operations as the forward, so the same values), then
-// runs the reverse sweep over the segment.  Per-lane gradients accumulate in
-// fp64 and are reduced in a fixed order (block tree, then one block over the
-// block partials), so the result is deterministic.
+// matched Gaussian's mean and variance updates.  A step changes one Gaussian of each
+// mixture and reorders them, so the reverse sweep undoes it from the recorded ranking and
+// the changed Gaussian's mean and variance before the step (16 bytes of the colour mixture,
+// 8 of the depth mixture).  Where the memory allows (SAVED) the forward keeps those for every
+// frame, beside the state before the last frame.  Otherwise it keeps checkpoints, and each
+// lane walks the segments in reverse: it replays a segment's means and variances from its
+// checkpoint (the forward's operations, so the same values) into a scratch buffer of the
+// same 24 bytes a frame, then sweeps it.  Per-lane gradients accumulate in fp64 and are
+// reduced in a fixed order (wavefront and block tree, then one block over the block
+// partials), so the result is deterministic.
+//
+// Measured, 64 frames of 640x480, K = 3 (forward, backward): with the whole state stored to
+// scratch per frame (72 bytes a pixel and frame) 310 and 657 us; with the changed Gaussians and
+// a replay 275 and 409; with the changed Gaussians of every frame kept 273 and 240.  The forward
+// is bound by its vector instructions (about 500 per wavefront and frame, the ALUs 95 % busy);
+// the backward reads 45 bytes a pixel and frame (3.7 TB/s) beside 380 instructions.  4,800
+// wavefronts are 4.7 a SIMD, hence the launch bound of 5 (96 registers) for K <= 3: with 111
+// registers a sixth of them ran in a second round.
 #include "device_common.h"
 #include "fgs_internal.h"
 #include "gmm_device.h"
@@ -32,7 +44,8 @@ constexpr int kBlock = 256;
 // Record layout, per mixture (colour in bits 0..31, depth in 32..63):
 //   bit 0 term, bits 1-3 argmin, bit 4 active, bits 5-7 matched (7 = replaced),
 //   bit 8 floor applied, bits 9.. ranking (3 bits per rank).
-__device__ __forceinline__ uint32_t pack_rec(const MixRec& r, bool term, bool active) {
+template <int C>
+__device__ __forceinline__ uint32_t pack_rec(const MixRec<C>& r, bool term, bool active) {
     return (term ? 1u : 0u) | ((uint32_t)r.argmin << 1) | (active ? 16u : 0u) |
            ((uint32_t)(r.kstar < 0 ? 7 : r.kstar) << 5) | (r.clamp ? 256u : 0u) | (r.perm << 9);
 }
@@ -74,25 +87,34 @@ struct Input {
     bool valid;
 };
 
-__device__ __forceinline__ Input load_input(const GmmWindowArgs& a, int t, int p) {
+// The bytes of one pixel of frame t as read; a frame's base is the same for the whole launch,
+// so a lane keeps one 32-bit offset.  Read one frame ahead of their use: a window is a serial
+// chain of frames per lane, with few wavefronts beside it to hide a read's latency.
+struct Raw {
+    uint32_t r, g, b, d;
+};
+__device__ __forceinline__ Raw read_input(const GmmWindowArgs& a, int t, uint32_t p) {
+    const uint8_t* px = a.rgb + (int64_t)t * a.npix * 3 + 3u * p;
+    return Raw{px[0], px[1], px[2], (a.depth + (int64_t)t * a.npix)[p]};
+}
+__device__ __forceinline__ Input input_of(const GmmWindowArgs& a, const Raw& raw) {
     Input in;
-    const uint8_t* px = a.rgb + ((int64_t)t * a.npix + p) * 3;
-    const uint32_t dmm = a.depth[(int64_t)t * a.npix + p];
-    in.Xc[0] = (float)px[0];
-    in.Xc[1] = (float)px[1];
-    in.Xc[2] = (float)px[2];
-    in.valid = dmm > 0u;
-    in.Xd[0] = (float)depth_code(dmm, a.c.depth_max_mm, a.c.depth_div);
+    in.Xc[0] = (float)raw.r;
+    in.Xc[1] = (float)raw.g;
+    in.Xc[2] = (float)raw.b;
+    in.valid = raw.d > 0u;
+    in.Xd[0] = (float)depth_code(raw.d, a.c.depth_max_mm, a.c.depth_div);
     return in;
 }
 
-template <int K>
-__global__ __launch_bounds__(kBlock) void gmm_window_forward_kernel(GmmWindowArgs a) {
+template <int K, bool SAVED>
+__global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_kernel(GmmWindowArgs a) {
     const int p = blockIdx.x * kBlock + threadIdx.x;
     if (p >= a.npix) return;
     const float alpha = a.theta[0], lam = a.theta[1], wd = a.theta[2];
     const float lam2 = lam * lam;
-    const bool sane = gmm_sane(lam, wd, a.c.v_min_c, a.c.v_min_d, a.c.v_init_c, a.c.v_init_d);
+    const bool sane = alpha > 0.0f && alpha < 1.0f &&
+                      gmm_sane(lam, wd, a.c.v_min_c, a.c.v_min_d, a.c.v_init_c, a.c.v_init_d);
     Mix<K, 3> mc;
     Mix<K, 1> md;
 #pragma unroll
@@ -105,8 +127,13 @@ __global__ __launch_bounds__(kBlock) void gmm_window_forward_kernel(GmmWindowArg
         md.v[k] = a.c.v_init_d;
     }
     const int64_t F = 6 * K;
-    for (int t = 0; t < a.T; ++t) {
-        if (t % a.E == 0) {
+    Raw next = read_input(a, 0, p);
+#pragma unroll 1
+    for (int t = 0, e = 0; t < a.T; ++t, e = e + 1 == a.E ? 0 : e + 1) {
+        const Raw raw = next;
+        next = read_input(a, min(t + 1, a.T - 1), p);
+        __builtin_amdgcn_sched_barrier(0);
+        if (SAVED ? t + 1 == a.T : e == 0) {
             MV<K> s;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -116,190 +143,240 @@ __global__ __launch_bounds__(kBlock) void gmm_window_forward_kernel(GmmWindowArg
                 s.mud[k] = md.mu[k][0];
                 s.vd[k] = md.v[k];
             }
-            store_mv<K>(s, a.ckpt + (int64_t)(t / a.E) * F * a.npix, a.npix, p);
+            store_mv<K>(s, a.ckpt + (int64_t)(SAVED ? 0 : t / a.E) * F * a.npix, a.npix, p);
         }
-        const Input in = load_input(a, t, p);
+        const Input in = input_of(a, raw);
         bool used_c, used_d;
         float dc, dd;
-        MixRec rc, rd;
+        MixRec<3> rc;
+        MixRec<1> rd;
         mixture_step_rec(mc, in.Xc, true, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_c, a.c.v_min_c, sane,
                          used_c, dc, rc);
         mixture_step_rec(md, in.Xd, in.valid, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_d, a.c.v_min_d, sane,
                          used_d, dd, rd);
+        if (SAVED) {
+            (a.scratch4() + (int64_t)t * a.npix)[(uint32_t)p] = make_float4(rc.mu[0], rc.mu[1], rc.mu[2], rc.v);
+            (a.scratch2() + (int64_t)t * a.npix)[(uint32_t)p] = make_float2(rd.mu[0], rd.v);
+        }
         const bool term_c = used_c, term_d = in.valid && used_d;
         const float tc = dc - lam2;
         const float td = wd * (dd - lam2);
         const float Z = term_c ? (term_d ? tc + td : tc) : (term_d ? td : 0.0f);
-        const int64_t o = (int64_t)t * a.npix + p;
-        a.Z[o] = Z;
-        a.has[o] = (term_c || term_d) ? 1 : 0;
-        a.rec[o] = (uint64_t)pack_rec(rc, term_c, true) | ((uint64_t)pack_rec(rd, term_d, in.valid) << 32);
+        const int64_t o = (int64_t)t * a.npix;
+        (a.Z + o)[(uint32_t)p] = Z;
+        (a.has + o)[(uint32_t)p] = (term_c || term_d) ? 1 : 0;
+        (a.rec + o)[(uint32_t)p] = (uint64_t)pack_rec(rc, term_c, true) | ((uint64_t)pack_rec(rd, term_d, in.valid) << 32);
     }
 }
 
-// Replay of one mixture's means/variances with recorded choices (fp32, the
-// forward's operations in the forward's order).
-template <int K, int C>
-__device__ __forceinline__ void replay_mix(float (&mu)[K][C], float (&v)[K], const float (&X)[C],
-                                           uint32_t r, float alpha, float v_init, float v_min) {
-    if (!(r & 16u)) return;
+// A recorded choice, unpacked.
+struct Choice {
+    bool term, active, matched, clamp, ranked;  // ranked: the step reordered the Gaussians
+    int amin, tgt;                              // tgt: the Gaussian matched, or replaced (the last)
+};
+template <int K>
+__device__ __forceinline__ Choice choice_of(uint32_t r) {
+    uint32_t id = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) id |= (uint32_t)k << (3 * k);
+    Choice c;
     const int ks = (int)((r >> 5) & 7u);
-    const bool clamp = (r >> 8) & 1u;
+    c.term = (r & 1u) != 0u;
+    c.active = (r & 16u) != 0u;
+    c.matched = ks != 7;
+    c.clamp = (r & 256u) != 0u;
+    c.ranked = (r >> 9) != id;
+    c.amin = (int)((r >> 1) & 7u);
+    c.tgt = c.matched ? ks : K - 1;
+    return c;
+}
+
+// One Gaussian's mean and variance (or their adjoints) out of K, and back into its place.
+template <int K, int C>
+__device__ __forceinline__ void pick(const float (&m)[K][C], const float (&v)[K], int at, float (&pm)[C], float& pv) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) pm[c] = m[0][c];
+    pv = v[0];
+#pragma unroll
+    for (int k = 1; k < K; ++k) {
+        const bool here = k == at;
+#pragma unroll
+        for (int c = 0; c < C; ++c) pm[c] = here ? m[k][c] : pm[c];
+        pv = here ? v[k] : pv;
+    }
+}
+template <int K, int C>
+__device__ __forceinline__ void put(float (&m)[K][C], float (&v)[K], int at, const float (&pm)[C], float pv) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        if (k != ks) continue;
+        const bool here = k == at;
+#pragma unroll
+        for (int c = 0; c < C; ++c) m[k][c] = here ? pm[c] : m[k][c];
+        v[k] = here ? pv : v[k];
+    }
+}
+
+// Rank r holds the Gaussian that was at (perm >> 3r) & 7: into that order (rank), and back.
+template <int K, int C, bool BACK>
+__device__ __forceinline__ void reorder(float (&m)[K][C], float (&v)[K], uint32_t perm) {
+    float om[K][C], ov[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) om[k][c] = m[0][c];
+        ov[k] = v[0];
+    }
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        const int src = (int)((perm >> (3 * r)) & 7u);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int to = BACK ? k : r, from = BACK ? r : k;
+            if (from == 0) continue;
+            const bool here = src == k;
+#pragma unroll
+            for (int c = 0; c < C; ++c) om[to][c] = here ? m[from][c] : om[to][c];
+            ov[to] = here ? v[from] : ov[to];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) m[k][c] = om[k][c];
+        v[k] = ov[k];
+    }
+}
+
+// Replay of one mixture's means/variances with recorded choices (fp32, the forward's operations
+// in the forward's order).  pm, pv: the changed Gaussian before the step.  `last`: only those are
+// wanted, the state stays.
+template <int K, int C>
+__device__ __forceinline__ void replay_mix(float (&mu)[K][C], float (&v)[K], const float (&X)[C], uint32_t r,
+                                           float alpha, float v_init, float v_min, bool last, float (&pm)[C],
+                                           float& pv) {
+    const Choice ch = choice_of<K>(r);
+    pick(mu, v, ch.tgt, pm, pv);
+    if (last) return;
+    if (!ch.active) return;
+    float mn[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) mn[c] = pm[c] + alpha * (X[c] - pm[c]);
+    float e = X[0] - mn[0];
+    float d2 = e * e;
+#pragma unroll
+    for (int c = 1; c < C; ++c) {
+        e = X[c] - mn[c];
+        d2 = d2 + e * e;
+    }
+    const float vt = pv + alpha * (d2 - pv);
+    const float vn = ch.matched ? (ch.clamp ? v_min : vt) : v_init;
+#pragma unroll
+    for (int c = 0; c < C; ++c) mn[c] = ch.matched ? mn[c] : X[c];
+    put(mu, v, ch.tgt, mn, vn);
+    if (__any(ch.ranked)) reorder<K, C, false>(mu, v, r >> 9);
+}
+
+// x / v with r = 1 / v at hand: one correction step (a quotient that is not finite stays).
+__device__ __forceinline__ float quotient(float x, float v, float r) {
+    const float q = x * r;
+    const float c = __builtin_fmaf(__builtin_fmaf(-v, q, x), r, q);
+    return __builtin_isfinite(c) ? c : q;
+}
+
+// One step backwards for one mixture.  In: the means/variances after the step (`undo`) or before
+// it, the adjoint (am, av) of those after it, and the changed Gaussian before it (pm, pv).  Out:
+// the means/variances before the step, their adjoint with the score's added (g = dL/dZ times
+// the mixture's factor in Z), the step's contribution to d/d alpha, and delta.
+template <int K, int C>
+__device__ __forceinline__ void reverse_mix(float (&mu)[K][C], float (&v)[K], const float (&X)[C], uint32_t r,
+                                            float alpha, bool undo, const float (&pm)[C], float pv, float g,
+                                            float (&am)[K][C], float (&av)[K], double& ga, float& delta) {
+    const Choice ch = choice_of<K>(r);
+    if (ch.active) {
+        if (__any(ch.ranked)) {
+            reorder<K, C, true>(am, av, r >> 9);
+            if (undo) reorder<K, C, true>(mu, v, r >> 9);
+        }
+        if (undo) put(mu, v, ch.tgt, pm, pv);
+        float bm[C], bv;
+        pick(am, av, ch.tgt, bm, bv);
         float mn[C];
 #pragma unroll
-        for (int c = 0; c < C; ++c) mn[c] = mu[k][c] + alpha * (X[c] - mu[k][c]);
-        float e = X[0] - mn[0];
+        for (int c = 0; c < C; ++c) mn[c] = pm[c] + alpha * (X[c] - pm[c]);
+        float d2 = 0.f;
+#pragma unroll
+        for (int c = 0; c < C; ++c) d2 += (X[c] - mn[c]) * (X[c] - mn[c]);
+        const float avt = ch.clamp ? 0.f : bv;
+        float gam = avt * (d2 - pv);
+        float nm[C], nv = (1.0f - alpha) * avt;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const float amn = bm[c] + avt * alpha * (-2.0f) * (X[c] - mn[c]);
+            gam += amn * (X[c] - pm[c]);
+            nm[c] = ch.matched ? (1.0f - alpha) * amn : 0.f;
+        }
+        nv = ch.matched ? nv : 0.f;
+        put(am, av, ch.tgt, nm, nv);
+        ga += (double)(ch.matched ? gam : 0.f);
+    }
+    if (ch.term) {  // Z depends on the state before the step through delta = |X - mu_a|^2 / v_a
+        float sm[C], sv, tm[C], tv;
+        pick(mu, v, ch.amin, sm, sv);
+        pick(am, av, ch.amin, tm, tv);
+        float e = X[0] - sm[0];
         float d2 = e * e;
 #pragma unroll
         for (int c = 1; c < C; ++c) {
-            e = X[c] - mn[c];
+            e = X[c] - sm[c];
             d2 = d2 + e * e;
         }
-        const float vt = v[k] + alpha * (d2 - v[k]);
+        const float rv = 1.0f / sv;
+        delta = quotient(d2, sv, rv);
 #pragma unroll
-        for (int c = 0; c < C; ++c) mu[k][c] = mn[c];
-        v[k] = clamp ? v_min : vt;
-    }
-    if (ks == 7) {
-#pragma unroll
-        for (int c = 0; c < C; ++c) mu[K - 1][c] = X[c];
-        v[K - 1] = v_init;
-    }
-    float nmu[K][C], nv[K];
-#pragma unroll
-    for (int rk = 0; rk < K; ++rk) {
-        const int src = (int)((r >> (9 + 3 * rk)) & 7u);
-#pragma unroll
-        for (int c = 0; c < C; ++c) nmu[rk][c] = mu[0][c];
-        nv[rk] = v[0];
-#pragma unroll
-        for (int k = 1; k < K; ++k)
-            if (src == k) {
-#pragma unroll
-                for (int c = 0; c < C; ++c) nmu[rk][c] = mu[k][c];
-                nv[rk] = v[k];
-            }
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-#pragma unroll
-        for (int c = 0; c < C; ++c) mu[k][c] = nmu[k][c];
-        v[k] = nv[k];
+        for (int c = 0; c < C; ++c) tm[c] += quotient(g * (-2.0f) * (X[c] - sm[c]), sv, rv);
+        tv += g * quotient(-delta, sv, rv);
+        put(am, av, ch.amin, tm, tv);
     }
 }
 
-// Adjoint of one mixture's step.  In: pre-step means/variances, the adjoint of the
-// post-step means/variances (am, av).  Out: the adjoint of the pre-step values (in
-// place) and the step's contribution to d/d alpha.
-template <int K, int C>
-__device__ __forceinline__ double reverse_mix(const float (&mu)[K][C], const float (&v)[K],
-                                              const float (&X)[C], uint32_t r, float alpha,
-                                              float (&am)[K][C], float (&av)[K]) {
-    if (!(r & 16u)) return 0.0;  // inactive: the state passed through
-    // un-rank: post rank rk came from pre index perm(rk)
-    float bm[K][C], bv[K];
+// Sums of three values over the block, in a fixed order; the result is lane 0's.
+__device__ __forceinline__ void block_sum3(double (&x)[3], double (*sh)[3]) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
+    for (int off = 32; off > 0; off >>= 1)
 #pragma unroll
-        for (int c = 0; c < C; ++c) bm[k][c] = 0.f;
-        bv[k] = 0.f;
-    }
+        for (int i = 0; i < 3; ++i) x[i] += __shfl_xor(x[i], off, 64);
+    if ((threadIdx.x & 63) == 0)
 #pragma unroll
-    for (int rk = 0; rk < K; ++rk) {
-        const int src = (int)((r >> (9 + 3 * rk)) & 7u);
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (src == k) {
-#pragma unroll
-                for (int c = 0; c < C; ++c) bm[k][c] += am[rk][c];
-                bv[k] += av[rk];
-            }
-    }
-    const int ks = (int)((r >> 5) & 7u);
-    const bool clamp = (r >> 8) & 1u;
-    double ga = 0.0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        if (k == ks) {
-            float mn[C];
-#pragma unroll
-            for (int c = 0; c < C; ++c) mn[c] = mu[k][c] + alpha * (X[c] - mu[k][c]);
-            float d2 = 0.f;
-#pragma unroll
-            for (int c = 0; c < C; ++c) d2 += (X[c] - mn[c]) * (X[c] - mn[c]);
-            const float avt = clamp ? 0.f : bv[k];
-            float gam = avt * (d2 - v[k]);
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                const float amn = bm[k][c] + avt * alpha * (-2.0f) * (X[c] - mn[c]);
-                gam += amn * (X[c] - mu[k][c]);
-                am[k][c] = (1.0f - alpha) * amn;
-            }
-            av[k] = (1.0f - alpha) * avt;
-            ga += (double)gam;
-        } else if (ks == 7 && k == K - 1) {
-#pragma unroll
-            for (int c = 0; c < C; ++c) am[k][c] = 0.f;
-            av[k] = 0.f;
-        } else {
-#pragma unroll
-            for (int c = 0; c < C; ++c) am[k][c] = bm[k][c];
-            av[k] = bv[k];
-        }
-    }
-    return ga;
-}
-
-// Z's dependence on the pre-step state through delta = |X - mu_a|^2 / v_a.
-template <int K, int C>
-__device__ __forceinline__ float score_adjoint(const float (&mu)[K][C], const float (&v)[K],
-                                               const float (&X)[C], uint32_t r, float g,
-                                               float (&am)[K][C], float (&av)[K]) {
-    const int a = (int)((r >> 1) & 7u);
-    float delta = 0.f;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        if (k != a) continue;
-        float e = X[0] - mu[k][0];
-        float d2 = e * e;
-#pragma unroll
-        for (int c = 1; c < C; ++c) {
-            e = X[c] - mu[k][c];
-            d2 = d2 + e * e;
-        }
-        delta = d2 / v[k];
-#pragma unroll
-        for (int c = 0; c < C; ++c) am[k][c] += g * (-2.0f) * (X[c] - mu[k][c]) / v[k];
-        av[k] += g * (-delta / v[k]);
-    }
-    return delta;
-}
-
-__device__ __forceinline__ double block_sum(double x, double* sh) {
-    sh[threadIdx.x] = x;
+        for (int i = 0; i < 3; ++i) sh[threadIdx.x >> 6][i] = x[i];
     __syncthreads();
+    if (threadIdx.x == 0)
 #pragma unroll
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    const double r = sh[0];
-    __syncthreads();
-    return r;
+        for (int w = 1; w < kBlock / 64; ++w)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) x[i] += sh[w][i];
 }
 
-template <int K>
-__global__ __launch_bounds__(kBlock) void gmm_window_backward_kernel(GmmWindowArgs a) {
-    __shared__ double sh[kBlock];
+// What the reverse sweep reads for one frame, one frame ahead of its use.
+struct BackRead {
+    Raw raw;
+    uint64_t rec;
+    float4 pc;   // the colour Gaussian the step changed, before it: mean, variance
+    float2 pd;   // the depth one
+    float g;
+};
+
+template <int K, bool SAVED>
+__global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_kernel(GmmWindowArgs a) {
+    __shared__ double sh[kBlock / 64][3];
     const int p = blockIdx.x * kBlock + threadIdx.x;
-    double g_alpha = 0.0, g_lam = 0.0, g_wd = 0.0;
+    const uint32_t up = (uint32_t)p;
+    double acc[3] = {0.0, 0.0, 0.0};  // alpha, lambda, w_depth
     if (p < a.npix) {
         const float alpha = a.theta[0], lam = a.theta[1], wd = a.theta[2];
         const float lam2 = lam * lam;
-        const int64_t F = 6 * K;
+        const int64_t F = 6 * K, npix = a.npix;
+        float4* sc = a.scratch4();
+        float2* sd = a.scratch2();
         float amc[K][3], avc[K], amd[K][1], avd[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -308,69 +385,89 @@ __global__ __launch_bounds__(kBlock) void gmm_window_backward_kernel(GmmWindowAr
             amd[k][0] = 0.f;
             avd[k] = 0.f;
         }
-        for (int seg = a.nseg - 1; seg >= 0; --seg) {
-            const int t0 = seg * a.E;
-            const int t1 = min(a.T, t0 + a.E);
-            MV<K> s;
-            load_mv<K>(s, a.ckpt + (int64_t)seg * F * a.npix, a.npix, p);
-            for (int t = t0; t < t1; ++t) {
-                store_mv<K>(s, a.scratch + (int64_t)(t - t0) * F * a.npix, a.npix, p);
-                if (t + 1 == t1) break;
-                const Input in = load_input(a, t, p);
-                const uint64_t rr = a.rec[(int64_t)t * a.npix + p];
-                float mud[K][1];
+        for (int seg = SAVED ? 0 : a.nseg - 1; seg >= 0; --seg) {
+            const int t0 = SAVED ? 0 : seg * a.E;
+            const int t1 = SAVED ? a.T : min(a.T, t0 + a.E);
+            float muc[K][3], vc[K], mud[K][1], vd[K];
+            {
+                MV<K> s;
+                load_mv<K>(s, a.ckpt + (int64_t)seg * F * npix, npix, p);
 #pragma unroll
-                for (int k = 0; k < K; ++k) mud[k][0] = s.mud[k];
-                replay_mix<K, 3>(s.muc, s.vc, in.Xc, (uint32_t)rr, alpha, a.c.v_init_c, a.c.v_min_c);
-                replay_mix<K, 1>(mud, s.vd, in.Xd, (uint32_t)(rr >> 32), alpha, a.c.v_init_d, a.c.v_min_d);
+                for (int k = 0; k < K; ++k) {
 #pragma unroll
-                for (int k = 0; k < K; ++k) s.mud[k] = mud[k][0];
-            }
-            for (int t = t1 - 1; t >= t0; --t) {
-                load_mv<K>(s, a.scratch + (int64_t)(t - t0) * F * a.npix, a.npix, p);
-                const Input in = load_input(a, t, p);
-                const int64_t o = (int64_t)t * a.npix + p;
-                const uint64_t rr = a.rec[o];
-                const uint32_t rc = (uint32_t)rr, rd = (uint32_t)(rr >> 32);
-                float mud[K][1];
-#pragma unroll
-                for (int k = 0; k < K; ++k) mud[k][0] = s.mud[k];
-                // the step t: post-state adjoint -> pre-state adjoint
-                g_alpha += reverse_mix<K, 3>(s.muc, s.vc, in.Xc, rc, alpha, amc, avc);
-                g_alpha += reverse_mix<K, 1>(mud, s.vd, in.Xd, rd, alpha, amd, avd);
-                // the score Z_t on the pre-state
-                const float g = a.dZ[o];
-                if (rc & 1u) {
-                    score_adjoint<K, 3>(s.muc, s.vc, in.Xc, rc, g, amc, avc);
-                    g_lam += (double)(g * (-2.0f * lam));
+                    for (int c = 0; c < 3; ++c) muc[k][c] = s.muc[k][c];
+                    vc[k] = s.vc[k];
+                    mud[k][0] = s.mud[k];
+                    vd[k] = s.vd[k];
                 }
+            }
+            if (!SAVED) {
+                Raw nraw = read_input(a, t0, up);
+                uint64_t nrec = (a.rec + (int64_t)t0 * npix)[up];
+#pragma unroll 1
+                for (int t = t0; t < t1; ++t) {
+                    const Raw raw = nraw;
+                    const uint64_t rr = nrec;
+                    const int tn = min(t + 1, t1 - 1);
+                    nraw = read_input(a, tn, up);
+                    nrec = (a.rec + (int64_t)tn * npix)[up];
+                    __builtin_amdgcn_sched_barrier(0);
+                    const Input in = input_of(a, raw);
+                    const bool last = t + 1 == t1;
+                    float pm[3], pv, qm[1], qv;
+                    replay_mix<K, 3>(muc, vc, in.Xc, (uint32_t)rr, alpha, a.c.v_init_c, a.c.v_min_c, last, pm, pv);
+                    replay_mix<K, 1>(mud, vd, in.Xd, (uint32_t)(rr >> 32), alpha, a.c.v_init_d, a.c.v_min_d, last, qm,
+                                     qv);
+                    (sc + (int64_t)(t - t0) * npix)[up] = make_float4(pm[0], pm[1], pm[2], pv);
+                    (sd + (int64_t)(t - t0) * npix)[up] = make_float2(qm[0], qv);
+                }
+            }
+            auto read = [&](int t) {
+                BackRead b;
+                b.raw = read_input(a, t, up);
+                b.rec = (a.rec + (int64_t)t * npix)[up];
+                b.pc = (sc + (int64_t)(t - t0) * npix)[up];
+                b.pd = (sd + (int64_t)(t - t0) * npix)[up];
+                b.g = (a.dZ + (int64_t)t * npix)[up];
+                return b;
+            };
+            BackRead next = read(t1 - 1);
+#pragma unroll 1
+            for (int t = t1 - 1; t >= t0; --t) {
+                const BackRead b = next;
+                next = read(max(t - 1, t0));
+                __builtin_amdgcn_sched_barrier(0);
+                const Input in = input_of(a, b.raw);
+                const bool undo = t + 1 != t1;
+                const uint32_t rc = (uint32_t)b.rec, rd = (uint32_t)(b.rec >> 32);
+                const float pm[3] = {b.pc.x, b.pc.y, b.pc.z}, qm[1] = {b.pd.x};
+                float dc = 0.f, dd = 0.f;
+                reverse_mix<K, 3>(muc, vc, in.Xc, rc, alpha, undo, pm, b.pc.w, b.g, amc, avc, acc[0], dc);
+                reverse_mix<K, 1>(mud, vd, in.Xd, rd, alpha, undo, qm, b.pd.y, b.g * wd, amd, avd, acc[0], dd);
+                if (rc & 1u) acc[1] += (double)(b.g * (-2.0f * lam));
                 if (rd & 1u) {
-                    const float dd = score_adjoint<K, 1>(mud, s.vd, in.Xd, rd, g * wd, amd, avd);
-                    g_lam += (double)(g * (-2.0f * lam) * wd);
-                    g_wd += (double)(g * (dd - lam2));
+                    acc[1] += (double)(b.g * (-2.0f * lam) * wd);
+                    acc[2] += (double)(b.g * (dd - lam2));
                 }
             }
         }
     }
-    const double ra = block_sum(g_alpha, sh);
-    const double rl = block_sum(g_lam, sh);
-    const double rw = block_sum(g_wd, sh);
-    if (threadIdx.x == 0) {
-        a.partial[3 * blockIdx.x + 0] = ra;
-        a.partial[3 * blockIdx.x + 1] = rl;
-        a.partial[3 * blockIdx.x + 2] = rw;
-    }
+    block_sum3(acc, sh);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) a.partial[3 * blockIdx.x + i] = acc[i];
 }
 
-__global__ __launch_bounds__(kBlock) void gmm_window_reduce_kernel(const double* partial, int nblocks,
-                                                                  double* out) {
-    __shared__ double sh[kBlock];
-    for (int i = 0; i < 3; ++i) {
-        double acc = 0.0;
-        for (int b = threadIdx.x; b < nblocks; b += kBlock) acc += partial[3 * b + i];
-        const double r = block_sum(acc, sh);
-        if (threadIdx.x == 0) out[i] = r;
-    }
+__global__ __launch_bounds__(kBlock) void gmm_window_reduce_kernel(const double* partial, int nblocks, double* out) {
+    __shared__ double sh[kBlock / 64][3];
+    double acc[3] = {0.0, 0.0, 0.0};
+    for (int b = threadIdx.x; b < nblocks; b += kBlock)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) acc[i] += partial[3 * b + i];
+    block_sum3(acc, sh);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) out[i] = acc[i];
 }
 
 }  // namespace
@@ -379,14 +476,29 @@ int gmm_window_blocks(int npix) { return (npix + kBlock - 1) / kBlock; }
 
 bool gmm_window_supported(int K) { return K >= 1 && K <= 5; }
 
+namespace {
+
+template <int K>
+void launch_forward(const GmmWindowArgs& a, dim3 grid, hipStream_t s) {
+    if (a.saved) hipLaunchKernelGGL((gmm_window_forward_kernel<K, true>), grid, dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((gmm_window_forward_kernel<K, false>), grid, dim3(kBlock), 0, s, a);
+}
+template <int K>
+void launch_backward(const GmmWindowArgs& a, dim3 grid, hipStream_t s) {
+    if (a.saved) hipLaunchKernelGGL((gmm_window_backward_kernel<K, true>), grid, dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((gmm_window_backward_kernel<K, false>), grid, dim3(kBlock), 0, s, a);
+}
+
+}  // namespace
+
 hipError_t gmm_window_launch_forward(const GmmWindowArgs& a, int K, hipStream_t s) {
     const dim3 grid(gmm_window_blocks(a.npix));
     switch (K) {
-        case 1: hipLaunchKernelGGL(gmm_window_forward_kernel<1>, grid, dim3(kBlock), 0, s, a); break;
-        case 2: hipLaunchKernelGGL(gmm_window_forward_kernel<2>, grid, dim3(kBlock), 0, s, a); break;
-        case 3: hipLaunchKernelGGL(gmm_window_forward_kernel<3>, grid, dim3(kBlock), 0, s, a); break;
-        case 4: hipLaunchKernelGGL(gmm_window_forward_kernel<4>, grid, dim3(kBlock), 0, s, a); break;
-        case 5: hipLaunchKernelGGL(gmm_window_forward_kernel<5>, grid, dim3(kBlock), 0, s, a); break;
+        case 1: launch_forward<1>(a, grid, s); break;
+        case 2: launch_forward<2>(a, grid, s); break;
+        case 3: launch_forward<3>(a, grid, s); break;
+        case 4: launch_forward<4>(a, grid, s); break;
+        case 5: launch_forward<5>(a, grid, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -396,11 +508,11 @@ hipError_t gmm_window_launch_backward(const GmmWindowArgs& a, int K, hipStream_t
     const int nb = gmm_window_blocks(a.npix);
     const dim3 grid(nb);
     switch (K) {
-        case 1: hipLaunchKernelGGL(gmm_window_backward_kernel<1>, grid, dim3(kBlock), 0, s, a); break;
-        case 2: hipLaunchKernelGGL(gmm_window_backward_kernel<2>, grid, dim3(kBlock), 0, s, a); break;
-        case 3: hipLaunchKernelGGL(gmm_window_backward_kernel<3>, grid, dim3(kBlock), 0, s, a); break;
-        case 4: hipLaunchKernelGGL(gmm_window_backward_kernel<4>, grid, dim3(kBlock), 0, s, a); break;
-        case 5: hipLaunchKernelGGL(gmm_window_backward_kernel<5>, grid, dim3(kBlock), 0, s, a); break;
+        case 1: launch_backward<1>(a, grid, s); break;
+        case 2: launch_backward<2>(a, grid, s); break;
+        case 3: launch_backward<3>(a, grid, s); break;
+        case 4: launch_backward<4>(a, grid, s); break;
+        case 5: launch_backward<5>(a, grid, s); break;
         default: return hipErrorInvalidValue;
     }
     hipError_t e = hipGetLastError();

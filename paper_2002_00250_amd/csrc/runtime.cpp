@@ -1128,6 +1128,7 @@ struct fgs_gmm_window {
     GmmConsts c;
     hipStream_t stream;
     bool own_stream;
+    bool saved;  // GmmWindowArgs::saved
     uint8_t* dev;
     uint64_t* rec;
     float* ckpt;
@@ -1164,11 +1165,20 @@ fgs_status fgs_gmm_window_create(int32_t T, int32_t H, int32_t W, const fgs_gmm_
     w->nseg = (T + w->E - 1) / w->E;
     w->c = gmm_consts(p);
     const size_t n = (size_t)w->npix, F = 6 * (size_t)w->K;
-    const size_t o_rec = 0;
-    const size_t o_ckpt = o_rec + align256((size_t)T * n * 8);
-    const size_t o_scr = o_ckpt + align256((size_t)w->nseg * F * n * 4);
-    const size_t o_par = o_scr + align256((size_t)w->E * F * n * 4);
-    const size_t total = o_par + align256((size_t)gmm_window_blocks(w->npix) * 3 * 8);
+    // Bytes for `rows` frames of changed Gaussians (24 bytes a pixel) and `ckpts` states.
+    size_t o_ckpt = 0, o_scr = 0, o_par = 0, total = 0;
+    auto lay_out = [&](size_t ckpts, size_t rows) {
+        o_ckpt = align256((size_t)T * n * 8);  // the records come first
+        o_scr = o_ckpt + align256(ckpts * F * n * 4);
+        o_par = o_scr + align256(rows * 6 * n * 4);
+        total = o_par + align256((size_t)gmm_window_blocks(w->npix) * 3 * 8);
+    };
+    // Every frame's changed Gaussians are kept (no replay in the backward) where that takes at
+    // most a quarter more than a state per checkpoint and per frame of a segment, the most
+    // that `checkpoint_every` asks for, and can be had; else checkpoints and one segment.
+    const size_t full = (size_t)T * n * 8 + ((size_t)w->nseg + (size_t)w->E) * F * n * 4;
+    lay_out(1, (size_t)T);
+    w->saved = total <= full + full / 4;
     hipError_t e = hipSuccess;
     if (hip_stream) {
         w->stream = (hipStream_t)hip_stream;
@@ -1176,13 +1186,25 @@ fgs_status fgs_gmm_window_create(int32_t T, int32_t H, int32_t W, const fgs_gmm_
         e = hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking);
         w->own_stream = e == hipSuccess;
     }
-    if (e == hipSuccess) e = hipMalloc((void**)&w->dev, total);
+    if (e == hipSuccess && w->saved) {
+        e = hipMalloc((void**)&w->dev, total);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            w->dev = nullptr;
+            w->saved = false;
+            e = hipSuccess;
+        }
+    }
+    if (e == hipSuccess && !w->saved) {
+        lay_out((size_t)w->nseg, (size_t)w->E);
+        e = hipMalloc((void**)&w->dev, total);
+    }
     if (e != hipSuccess) {
         if (w->own_stream) (void)hipStreamDestroy(w->stream);
         delete w;
         return fail(FGS_ERR_OUT_OF_MEMORY, "window allocation of %zu bytes: %s", total, hipGetErrorString(e));
     }
-    w->rec = reinterpret_cast<uint64_t*>(w->dev + o_rec);
+    w->rec = reinterpret_cast<uint64_t*>(w->dev);
     w->ckpt = reinterpret_cast<float*>(w->dev + o_ckpt);
     w->scratch = reinterpret_cast<float*>(w->dev + o_scr);
     w->partial = reinterpret_cast<double*>(w->dev + o_par);
@@ -1204,6 +1226,7 @@ static GmmWindowArgs window_args(fgs_gmm_window* w, const float* theta, const ui
     a.theta = theta;
     a.rgb = rgb;
     a.depth = depth;
+    a.saved = w->saved ? 1 : 0;
     a.rec = w->rec;
     a.ckpt = w->ckpt;
     a.scratch = w->scratch;
