@@ -479,6 +479,25 @@ fgs_status fgs_gmm_window_records(fgs_gmm_window* w, uint64_t* out, fgs_mem wher
 fgs_status fgs_gmm_window_destroy(fgs_gmm_window* w);
 
 /*
+ * The window's loss: mean binary cross-entropy of sigmoid(Z / tau) against 0/255 ground truth
+ * over the scores with a term, from index i0 on (the scores of the frames from t0 on of a
+ * [T][H][W] window: i0 = t0*H*W, n = T*H*W).  With x = Z[i]/tau, y = gt[i] != 0, w = has[i]:
+ *   fgs_window_bce       *loss = sum_{i0<=i<n} w * ((1-y)*x - logsigmoid(x)) / max(sum w, 1)
+ *   fgs_window_bce_grad  dZ[i] = (sigmoid(x) - y) * w * gloss / max(sum w, 1) / tau; 0 for i < i0
+ * All arrays are device memory, dense: Z, dZ float[n]; has, gt uint8[n]; loss, gloss float[1];
+ * work double[FGS_WINDOW_BCE_WORK], written by fgs_window_bce and read by the gradient, which
+ * must be given the same Z, has, gt, i0, n and tau.  Sums are fp64 in a fixed order
+ * (deterministic).  Both run on hip_stream (NULL: the null stream) and return after enqueueing.
+ * INVALID_ARG for NULL or misaligned buffers or i0 outside 0..n-1; DEVICE if a launch fails.
+ */
+#define FGS_WINDOW_BCE_WORK 4098
+fgs_status fgs_window_bce(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n,
+                          float tau, double* work, float* loss, void* hip_stream);
+fgs_status fgs_window_bce_grad(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n,
+                               float tau, const double* work, const float* gloss, float* dZ,
+                               void* hip_stream);
+
+/*
  * Multi-stream serving.  Many camera streams on one GPU, every model resident in
  * device memory, frames batched continuously: a scheduler thread takes the next
  * queued frame of every stream whose previous frame has finished (at most one

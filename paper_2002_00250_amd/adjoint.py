@@ -105,9 +105,68 @@ class GmmWindowFunction(torch.autograd.Function):
         return d.to(theta.dtype), None, None, None
 
 
-def window_bce_loss(Z: torch.Tensor, has: torch.Tensor, gt: torch.Tensor, t0: int = 1, tau: float = 1.0):
-    """Mean BCE of sigmoid(Z/tau) against 0/255 ground truth over frames t >= t0 where Z has a term."""
+def _bce_torch(Z, has, gt, t0, tau):
     w = has[t0:].to(Z.dtype)
     y = (gt[t0:] != 0).to(Z.dtype)
     l = torch.nn.functional.binary_cross_entropy_with_logits(Z[t0:] / tau, y, weight=w, reduction="sum")
     return l / w.sum().clamp_min(1.0)
+
+
+def _bce_kernel_takes(Z, has, gt, t0, tau) -> bool:
+    """Whether the library's loss kernels compute this call: dense tensors of one shape on the
+    current GPU (float32 scores, uint8 flags, uint8 or bool truth), plain numbers t0 and tau, and
+    nothing watching the operations (vmap and the other function transforms, forward-mode
+    differentiation, tracing or compiling), which only the composed form answers."""
+    if not (type(Z) in (torch.Tensor, torch.nn.Parameter) and type(has) is torch.Tensor and type(gt) is torch.Tensor):
+        return False
+    if not (Z.is_cuda and Z.dtype == torch.float32 and has.dtype == torch.uint8 and
+            gt.dtype in (torch.uint8, torch.bool) and Z.device == has.device == gt.device and
+            Z.device.index == torch.cuda.current_device()):
+        return False
+    if type(t0) is not int or type(tau) not in (int, float) or Z.dim() < 1 or not 0 <= t0 < Z.shape[0]:
+        return False
+    if Z.numel() == 0 or Z.shape != has.shape or Z.shape != gt.shape or Z.layout != torch.strided or \
+            not (Z.is_contiguous() and has.is_contiguous() and gt.is_contiguous()):
+        return False
+    return not (torch._C._are_functorch_transforms_active() or torch.autograd.forward_ad._current_level >= 0 or
+                torch.jit.is_tracing() or torch.compiler.is_compiling())
+
+
+class _WindowBce(torch.autograd.Function):
+    """The loss in one pass over the scores, its gradient in another (fgs_window_bce, _grad)."""
+
+    @staticmethod
+    def forward(ctx, Z, has, gt, t0, tau):
+        loss = torch.empty((), dtype=torch.float32, device=Z.device)
+        work = torch.empty(fgs.FGS_WINDOW_BCE_WORK, dtype=torch.float64, device=Z.device)
+        i0 = t0 * (Z.numel() // Z.shape[0])
+        fgs.fgs_window_bce(Z.data_ptr(), has.data_ptr(), gt.data_ptr(), i0, Z.numel(), tau, work.data_ptr(),
+                           loss.data_ptr(), torch.cuda.current_stream(Z.device).cuda_stream)
+        ctx.save_for_backward(Z, has, gt, work)
+        ctx.i0, ctx.t0, ctx.tau = i0, t0, tau
+        return loss
+
+    @staticmethod
+    def backward(ctx, g):
+        Z, has, gt, work = ctx.saved_tensors
+        plain = type(g) is torch.Tensor and g.is_cuda and g.dtype == torch.float32 and g.numel() == 1 and \
+            torch._C._has_storage(g)          # (a batch of gradients has none of its own)
+        if not plain or torch.is_grad_enabled() or torch._C._are_functorch_transforms_active() or \
+                not _bce_kernel_takes(Z, has, gt, ctx.t0, ctx.tau):
+            # a gradient that is itself differentiated, or batched
+            w = has.to(Z.dtype)
+            d = (torch.sigmoid(Z / ctx.tau) - (gt != 0).to(Z.dtype)) * w
+            d = d * (torch.arange(Z.shape[0], device=Z.device) >= ctx.t0).reshape((-1,) + (1,) * (Z.dim() - 1))
+            return d * (g / w[ctx.t0:].sum().clamp_min(1.0)) / ctx.tau, None, None, None, None
+        dZ = torch.empty_like(Z)
+        fgs.fgs_window_bce_grad(Z.data_ptr(), has.data_ptr(), gt.data_ptr(), ctx.i0, Z.numel(), ctx.tau,
+                                work.data_ptr(), g.data_ptr(), dZ.data_ptr(),
+                                torch.cuda.current_stream(Z.device).cuda_stream)
+        return dZ, None, None, None, None
+
+
+def window_bce_loss(Z: torch.Tensor, has: torch.Tensor, gt: torch.Tensor, t0: int = 1, tau: float = 1.0):
+    """Mean BCE of sigmoid(Z/tau) against 0/255 ground truth over frames t >= t0 where Z has a term."""
+    if _bce_kernel_takes(Z, has, gt, t0, tau):
+        return _WindowBce.apply(Z, has, gt, t0, tau)
+    return _bce_torch(Z, has, gt, t0, tau)

@@ -146,6 +146,13 @@ int gmm_window_blocks(int npix);
 hipError_t gmm_window_launch_forward(const GmmWindowArgs& a, int K, hipStream_t s);
 hipError_t gmm_window_launch_backward(const GmmWindowArgs& a, int K, hipStream_t s);
 
+// The window's loss (window_loss.hip): scores i0 .. n - 1; work holds 2 + 2 kBceBlocks doubles.
+constexpr int kBceBlocks = (FGS_WINDOW_BCE_WORK - 2) / 2;
+hipError_t window_bce_launch(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
+                             double* work, float* loss, hipStream_t s);
+hipError_t window_bce_grad_launch(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
+                                  const double* work, const float* gloss, float* dZ, hipStream_t s);
+
 // --------------------------------------------------------------- PBAS ----
 // Device layout: samples in ceil(N/4) planes of 16-byte quads (slot k of pixel p
 // = word k & 3 of quad (k >> 2) * npix + p; padding slots zero), dhist[N] uint32

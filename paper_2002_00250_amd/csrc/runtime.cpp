@@ -1283,6 +1283,30 @@ fgs_status fgs_gmm_window_destroy(fgs_gmm_window* w) {
     return FGS_OK;
 }
 
+fgs_status fgs_window_bce(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
+                          double* work, float* loss, void* hip_stream) {
+    if (!Z || !has || !gt || !work || !loss) return fail(FGS_ERR_INVALID_ARG, "NULL argument");
+    if (((uintptr_t)Z & 3) || ((uintptr_t)loss & 3) || ((uintptr_t)work & 7))
+        return fail(FGS_ERR_INVALID_ARG, "misaligned device buffer");
+    if (i0 < 0 || i0 >= n || n > ((int64_t)1 << 40))
+        return fail(FGS_ERR_INVALID_ARG, "bad score range %lld..%lld", (long long)i0, (long long)n);
+    hipError_t e = window_bce_launch(Z, has, gt, i0, n, tau, work, loss, (hipStream_t)hip_stream);
+    if (e != hipSuccess) return fail(FGS_ERR_DEVICE, "window loss: %s", hipGetErrorString(e));
+    return FGS_OK;
+}
+
+fgs_status fgs_window_bce_grad(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
+                               const double* work, const float* gloss, float* dZ, void* hip_stream) {
+    if (!Z || !has || !gt || !work || !gloss || !dZ) return fail(FGS_ERR_INVALID_ARG, "NULL argument");
+    if (((uintptr_t)Z & 3) || ((uintptr_t)gloss & 3) || ((uintptr_t)dZ & 3) || ((uintptr_t)work & 7))
+        return fail(FGS_ERR_INVALID_ARG, "misaligned device buffer");
+    if (i0 < 0 || i0 >= n || n > ((int64_t)1 << 40))
+        return fail(FGS_ERR_INVALID_ARG, "bad score range %lld..%lld", (long long)i0, (long long)n);
+    hipError_t e = window_bce_grad_launch(Z, has, gt, i0, n, tau, work, gloss, dZ, (hipStream_t)hip_stream);
+    if (e != hipSuccess) return fail(FGS_ERR_DEVICE, "window loss gradient: %s", hipGetErrorString(e));
+    return FGS_OK;
+}
+
 fgs_status fgs_mask_median(const uint8_t* src, int64_t src_stride, uint8_t* dst, int64_t dst_stride,
                            int32_t H, int32_t W, int32_t radius, void* hip_stream) {
     constexpr int32_t kMaxSide = 1 << 30;

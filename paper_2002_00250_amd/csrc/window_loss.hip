@@ -1,0 +1,195 @@
+// The adjoint's loss: mean binary cross-entropy of sigmoid(Z / tau) against 0/255 ground truth,
+// weighted by the term flags, and its gradient with respect to Z.  Composed of elementwise
+// operations it takes some fifteen passes over the scores (64 frames of 640x480: about 600 us of
+// a training step, as much as the window's two kernels); here the loss is one pass that reads 6
+// bytes a score (38 us, 3.1 TB/s, bound by about 50 vector instructions a score) and the
+// gradient one that reads 6 and writes 4 (29 us, 6.8 TB/s, the copy rate).
+//
+// Per score i >= i0 (x = Z * (1 / tau), y = gt != 0, w = has), in float32:
+//   loss      w * ((1 - y) * x - logsigmoid(x)),  logsigmoid(x) = min(x, 0) - log1p(exp(-|x|))
+//   gradient  ((sigmoid(x) - y) * w * (g / max(sum w, 1))) * (1 / tau),  0 for i < i0
+// Sums are kept in fp64, in a fixed order (lane, wavefront, block, then one block over the
+// partials): deterministic.
+#include "device_common.h"
+#include "fgs_internal.h"
+
+namespace fgs {
+
+namespace {
+
+constexpr int kBlock = 256;
+constexpr int kGroup = 4;  // scores a lane takes at a time: 16 bytes of Z, 4 of the flags and truth
+
+// Scores 4 g .. 4 g + 3.  VEC: the arrays are aligned for whole groups and i0 is a multiple of 4.
+struct Group {
+    float z[kGroup];
+    uint32_t h[kGroup], t[kGroup];
+};
+template <bool VEC>
+__device__ __forceinline__ Group read_group(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i, int64_t n) {
+    Group r;
+    if (VEC && i + kGroup <= n) {
+        const float4 z = *reinterpret_cast<const float4*>(Z + i);
+        const uint32_t h = *reinterpret_cast<const uint32_t*>(has + i), t = *reinterpret_cast<const uint32_t*>(gt + i);
+        r.z[0] = z.x;
+        r.z[1] = z.y;
+        r.z[2] = z.z;
+        r.z[3] = z.w;
+#pragma unroll
+        for (int k = 0; k < kGroup; ++k) {
+            r.h[k] = (h >> (8 * k)) & 0xFFu;
+            r.t[k] = (t >> (8 * k)) & 0xFFu;
+        }
+        return r;
+    }
+#pragma unroll
+    for (int k = 0; k < kGroup; ++k) {
+        const bool in = i + k < n;
+        r.z[k] = in ? Z[i + k] : 0.0f;
+        r.h[k] = in ? has[i + k] : 0u;
+        r.t[k] = in ? gt[i + k] : 0u;
+    }
+    return r;
+}
+
+__device__ __forceinline__ void block_sum2(double& a, double& b, double (*sh)[2]) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        a += __shfl_xor(a, off, 64);
+        b += __shfl_xor(b, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sh[threadIdx.x >> 6][0] = a;
+        sh[threadIdx.x >> 6][1] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int w = 1; w < kBlock / 64; ++w) {
+            a += sh[w][0];
+            b += sh[w][1];
+        }
+}
+
+// log(1 + e) for 0 <= e <= 1 to about 2 ulp: log(1 + e) = 2 atanh(s), s = e / (2 + e) <= 1/3, by
+// its series to s^17 (the library's log1p serves every argument at three times the
+// instructions: the pass took 67 us with it).
+__device__ __forceinline__ float log1p_unit(float e) {
+    const float s = e * __builtin_amdgcn_rcpf(2.0f + e), q = s * s;
+    float p = 2.0f / 17.0f;
+    p = __builtin_fmaf(p, q, 2.0f / 15.0f);
+    p = __builtin_fmaf(p, q, 2.0f / 13.0f);
+    p = __builtin_fmaf(p, q, 2.0f / 11.0f);
+    p = __builtin_fmaf(p, q, 2.0f / 9.0f);
+    p = __builtin_fmaf(p, q, 2.0f / 7.0f);
+    p = __builtin_fmaf(p, q, 2.0f / 5.0f);
+    p = __builtin_fmaf(p, q, 2.0f / 3.0f);
+    return __builtin_fmaf(s * q, p, s + s);
+}
+
+// work[2 + 2 b], work[3 + 2 b]: block b's sums of the weighted losses and of the weights.
+template <bool VEC>
+__global__ __launch_bounds__(kBlock) void bce_sum_kernel(const float* __restrict__ Z, const uint8_t* __restrict__ has,
+                                                         const uint8_t* __restrict__ gt, int64_t i0, int64_t n, float by_tau,
+                                                         double* __restrict__ work) {
+    __shared__ double sh[kBlock / 64][2];
+    double sl = 0.0, sw = 0.0;
+    const int64_t step = (int64_t)gridDim.x * kBlock * kGroup;
+    for (int64_t i = i0 + ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kGroup; i < n; i += step) {
+        const Group g = read_group<VEC>(Z, has, gt, i, n);
+        float l = 0.0f;
+        uint32_t hs = 0u;
+#pragma unroll
+        for (int k = 0; k < kGroup; ++k) {
+            const float x = g.z[k] * by_tau;
+            const float y = g.t[k] ? 1.0f : 0.0f, w = (float)g.h[k];
+            const float ls = fminf(x, 0.0f) - log1p_unit(expf(-fabsf(x)));
+            l += i + k < n ? w * ((1.0f - y) * x - ls) : 0.0f;
+            hs += g.h[k];
+        }
+        sl += (double)l;
+        sw += (double)hs;
+    }
+    block_sum2(sl, sw, sh);
+    if (threadIdx.x == 0) {
+        work[2 + 2 * blockIdx.x] = sl;
+        work[3 + 2 * blockIdx.x] = sw;
+    }
+}
+
+// work[0], work[1]: the sum of the losses and max(sum of the weights, 1); *loss their quotient.
+__global__ __launch_bounds__(kBlock) void bce_finish_kernel(double* work, int blocks, float* loss) {
+    __shared__ double sh[kBlock / 64][2];
+    double sl = 0.0, sw = 0.0;
+    for (int b = threadIdx.x; b < blocks; b += kBlock) {
+        sl += work[2 + 2 * b];
+        sw += work[3 + 2 * b];
+    }
+    block_sum2(sl, sw, sh);
+    if (threadIdx.x == 0) {
+        sw = sw < 1.0 ? 1.0 : sw;
+        work[0] = sl;
+        work[1] = sw;
+        *loss = (float)(sl / sw);
+    }
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(kBlock) void bce_grad_kernel(const float* __restrict__ Z, const uint8_t* __restrict__ has,
+                                                          const uint8_t* __restrict__ gt, int64_t i0, int64_t n, float by_tau,
+                                                          const double* __restrict__ work, const float* __restrict__ gloss,
+                                                          float* __restrict__ dZ) {
+    const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kGroup;
+    if (i >= n) return;
+    const float scale = gloss[0] / (float)work[1];
+    const Group g = read_group<VEC>(Z, has, gt, i, n);
+    float d[kGroup];
+#pragma unroll
+    for (int k = 0; k < kGroup; ++k) {
+        const float x = g.z[k] * by_tau;
+        const float y = g.t[k] ? 1.0f : 0.0f, w = (float)g.h[k];
+        const float s = 1.0f / (1.0f + expf(-x));
+        d[k] = i + k >= i0 ? ((s - y) * w * scale) * by_tau : 0.0f;
+    }
+    if (VEC && i + kGroup <= n) {
+        *reinterpret_cast<float4*>(dZ + i) = make_float4(d[0], d[1], d[2], d[3]);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < kGroup; ++k)
+        if (i + k < n) dZ[i + k] = d[k];
+}
+
+bool aligned(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0) {
+    return (((uintptr_t)Z & 15) | ((uintptr_t)has & 3) | ((uintptr_t)gt & 3) | (uintptr_t)(i0 & 3)) == 0;
+}
+
+}  // namespace
+
+hipError_t window_bce_launch(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
+                             double* work, float* loss, hipStream_t s) {
+    const int64_t groups = (n - i0 + kGroup - 1) / kGroup;
+    int64_t blocks = (groups + kBlock - 1) / kBlock;
+    blocks = blocks < 1 ? 1 : (blocks > kBceBlocks ? kBceBlocks : blocks);
+    const dim3 grid((unsigned)blocks), block(kBlock);
+    if (aligned(Z, has, gt, i0)) hipLaunchKernelGGL(bce_sum_kernel<true>, grid, block, 0, s, Z, has, gt, i0, n, 1.0f / tau, work);
+    else hipLaunchKernelGGL(bce_sum_kernel<false>, grid, block, 0, s, Z, has, gt, i0, n, 1.0f / tau, work);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(bce_finish_kernel, dim3(1), block, 0, s, work, (int)blocks, loss);
+    return hipGetLastError();
+}
+
+hipError_t window_bce_grad_launch(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
+                                  const double* work, const float* gloss, float* dZ, hipStream_t s) {
+    const int64_t blocks = ((n + kGroup - 1) / kGroup + kBlock - 1) / kBlock;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block(kBlock);
+    if (aligned(Z, has, gt, 0) && ((uintptr_t)dZ & 15) == 0)
+        hipLaunchKernelGGL(bce_grad_kernel<true>, grid, block, 0, s, Z, has, gt, i0, n, 1.0f / tau, work, gloss, dZ);
+    else
+        hipLaunchKernelGGL(bce_grad_kernel<false>, grid, block, 0, s, Z, has, gt, i0, n, 1.0f / tau, work, gloss, dZ);
+    return hipGetLastError();
+}
+
+}  // namespace fgs

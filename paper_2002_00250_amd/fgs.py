@@ -118,6 +118,10 @@ def _load():
         "fgs_gmm_window_backward": (S, [c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]),
         "fgs_gmm_window_records": (S, [c_void_p, c_void_p, c_int32]),
         "fgs_gmm_window_destroy": (S, [c_void_p]),
+        "fgs_window_bce": (S, [c_void_p, c_void_p, c_void_p, c_int64, c_int64, ctypes.c_float, c_void_p, c_void_p,
+                               c_void_p]),
+        "fgs_window_bce_grad": (S, [c_void_p, c_void_p, c_void_p, c_int64, c_int64, ctypes.c_float, c_void_p,
+                                    c_void_p, c_void_p, c_void_p]),
         "fgs_server_now": (ctypes.c_double, []),
         "fgs_server_create": (S, [c_size_t, c_int32, POINTER(c_void_p)]),
         "fgs_server_open": (S, [c_void_p, c_int32, c_int32, c_int32, c_void_p, POINTER(c_int32)]),
@@ -338,6 +342,21 @@ def fgs_gmm_window_records(w: int, out: int, where: int) -> None:
 
 def fgs_gmm_window_destroy(w: int) -> None:
     _check(_load().fgs_gmm_window_destroy(c_void_p(w)))
+
+
+FGS_WINDOW_BCE_WORK = 4098
+
+
+def fgs_window_bce(Z: int, has: int, gt: int, i0: int, n: int, tau: float, work: int, loss: int,
+                   hip_stream: int | None = None) -> None:
+    _check(_load().fgs_window_bce(c_void_p(Z), c_void_p(has), c_void_p(gt), i0, n, tau, c_void_p(work),
+                                  c_void_p(loss), c_void_p(hip_stream or 0)))
+
+
+def fgs_window_bce_grad(Z: int, has: int, gt: int, i0: int, n: int, tau: float, work: int, gloss: int, dZ: int,
+                        hip_stream: int | None = None) -> None:
+    _check(_load().fgs_window_bce_grad(c_void_p(Z), c_void_p(has), c_void_p(gt), i0, n, tau, c_void_p(work),
+                                       c_void_p(gloss), c_void_p(dZ), c_void_p(hip_stream or 0)))
 
 
 def fgs_server_now() -> float:
