@@ -219,14 +219,16 @@ hipError_t pbas_launch_flush(const PbasPlanes& m, int H, int W, uint32_t t_prev,
 hipError_t pbas_launch_export(const PbasPlanes& m, int npix, int N, uint8_t* out, hipStream_t s);
 hipError_t pbas_launch_import(const PbasPlanes& m, int npix, int N, const uint8_t* in,
                               hipStream_t s);
+// Quad planes <-> slot-major planes of the payload.
+hipError_t pbas_launch_export_quads(const uint32_t* quads, int npix, int N, uint8_t* out, hipStream_t s);
+hipError_t pbas_launch_import_quads(uint32_t* quads, int npix, int N, const uint8_t* in, hipStream_t s);
 
 // ------------------------------------------- PBAS, gradient magnitudes ----
-// The gradient-magnitude variant (pbas_grad_kernels.hip): slot k of pixel p is word
-// k * npix + p of the plain slot planes `samples` (bytes R, G, B, depth code) and
-// `gsamples` (colour magnitudes m_R, m_G, m_B, 0); D[k * npix + p] holds the four
-// channels' d_min as float4, S their float sums; `last` and `last_g` the pixel's
-// value and magnitudes of the previous frame (pending neighbour writes carry them);
-// gsum[4 * (t mod 3) + j] the sum of frame t's colour magnitudes m_j (frame t adds
+// The gradient-magnitude variant (pbas_grad_kernels.hip): `samples` (bytes R, G, B, depth
+// code) and `gsamples` (colour magnitudes m_R, m_G, m_B, 0) in quad planes as above;
+// D[k * npix + p] holds the four channels' d_min of slot k as float4, S their float sums; `last`
+// and `last_g` the pixel's value and magnitudes of the previous frame (pending neighbour writes
+// carry them); gsum[4 * (t mod 3) + j] the sum of frame t's colour magnitudes m_j (frame t adds
 // into its slot, reads frame t-1's and clears frame t+1's).
 struct PbasGradPlanes {
     uint32_t* samples;
@@ -252,6 +254,7 @@ struct PbasGradArgs {
     FrameGeom geom;
     uint32_t t;
     int32_t apply_pending;
+    int32_t streaming;  // 1: non-temporal sample traffic
     PbasConsts c;
 };
 

@@ -9,9 +9,16 @@
 // neighbour update through fire bytes and the LDS scatter of pbas_device.h, R and T) is
 // the plain variant's, so the random draws and decisions follow the same rules.
 //
-// Layout (fgs_internal.h, PbasGradPlanes): plain slot planes rather than the plain
-// variant's quad planes.  This variant trades speed for the second feature: every
-// slot's two words are read per frame and a changed slot is written back by word.
+// Layout (fgs_internal.h, PbasGradPlanes): samples and magnitudes in the plain variant's quad
+// planes, so that a wavefront moves 1 KiB contiguous per access and a changed sector is written
+// back whole; D as one float4 per slot and pixel.
+//
+// Measured at 640x480, N = 20, static background (T = 2): the first version read slot by slot, each
+// read behind the previous slot's possible write, and wrote single words and bytes: 60 us a frame
+// (one model after another frame of its own, 81 in turn with two others); now 41 (2 models of
+// 1280x720 392 -> 242, N = 35 93 -> 53).  It moves 570 bytes a pixel at 4.2 TB/s: the samples, the
+// D lines of random slots and the changed sectors; the 1,200 tiles are 1.2 rounds of the four a
+// CU holds (114 registers; at 96 the spills cost more than the second round, 44.8 us).
 #include <cstring>
 
 #include "device_common.h"
@@ -24,29 +31,56 @@ using namespace pbas;
 
 namespace {
 
-constexpr int kGradNmax = 64;
+// Register capacity classes (a sample and a magnitude word per slot): class NMAX serves N from
+// grad_class_min(NMAX) to NMAX.  Fewer than the plain variant's: twelve registers a step.
+constexpr int grad_class_min(int nmax) {
+    return nmax <= 8 ? 2 : nmax <= 16 ? 9 : nmax <= 20 ? 17 : nmax <= 24 ? 21 : nmax <= 32 ? 25 : nmax <= 40 ? 33 : 41;
+}
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// The three colour magnitudes of pixel (x, y) as bytes m_R | m_G << 8 | m_B << 16.
+struct __attribute__((packed, aligned(1))) Bytes12 {
+    uint32_t w[3];
+};
+
+// Byte i (0..8) of three packed pixels.
+__device__ __forceinline__ int byte_of(const uint32_t (&w)[3], int i) { return (int)((w[i >> 2] >> (8 * (i & 3))) & 0xFFu); }
+
+// The three colour magnitudes of pixel (x, y) as bytes m_R | m_G << 8 | m_B << 16.  Inside the
+// image a row's three pixels are one 12-byte read (9 of them used: it ends inside the row for
+// x <= W - 3); at the sides they are read one by one at clamped columns.
 __device__ __forceinline__ uint32_t colour_magnitudes(const uint8_t* rgb, int64_t stride, int x, int y, int W,
                                                       int H) {
-    int v[3][3][3];
+    uint32_t w[3][3];
 #pragma unroll
     for (int dy = 0; dy < 3; ++dy) {
         const uint8_t* row = rgb + (int64_t)clampi(y + dy - 1, 0, H - 1) * stride;
+        if (x >= 1 && x <= W - 3) {
+            const Bytes12 b = *reinterpret_cast<const Bytes12*>(row + 3 * (x - 1));
 #pragma unroll
-        for (int dx = 0; dx < 3; ++dx) {
-            const uint8_t* px = row + 3 * clampi(x + dx - 1, 0, W - 1);
+            for (int i = 0; i < 3; ++i) w[dy][i] = b.w[i];
+        } else {
+            uint32_t px[3];
 #pragma unroll
-            for (int j = 0; j < 3; ++j) v[dy][dx][j] = px[j];
+            for (int dx = 0; dx < 3; ++dx) {
+                const uint8_t* q = row + 3 * clampi(x + dx - 1, 0, W - 1);
+                px[dx] = (uint32_t)q[0] | ((uint32_t)q[1] << 8) | ((uint32_t)q[2] << 16);
+            }
+            w[dy][0] = px[0] | (px[1] << 24);
+            w[dy][1] = (px[1] >> 8) | (px[2] << 16);
+            w[dy][2] = px[2] >> 16;
         }
     }
     uint32_t out = 0u;
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        const int gx = (v[0][2][j] + 2 * v[1][2][j] + v[2][2][j]) - (v[0][0][j] + 2 * v[1][0][j] + v[2][0][j]);
-        const int gy = (v[2][0][j] + 2 * v[2][1][j] + v[2][2][j]) - (v[0][0][j] + 2 * v[0][1][j] + v[0][2][j]);
+        int v[3][3];
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) v[dy][dx] = byte_of(w[dy], 3 * dx + j);
+        const int gx = (v[0][2] + 2 * v[1][2] + v[2][2]) - (v[0][0] + 2 * v[1][0] + v[2][0]);
+        const int gy = (v[2][0] + 2 * v[2][1] + v[2][2]) - (v[0][0] + 2 * v[0][1] + v[0][2]);
         out |= (uint32_t)((abs(gx) + abs(gy)) >> 3) << (8 * j);
     }
     return out;
@@ -57,14 +91,14 @@ __device__ __forceinline__ uint32_t colour_magnitudes(const uint8_t* rgb, int64_
 // t+1's slot, which nothing reads or writes during frame t.
 __device__ __forceinline__ void add_magnitudes(unsigned long long* gsum, uint32_t t, uint32_t mw, bool inside) {
     __shared__ uint32_t part[kBlock / 64][3];
-    uint32_t c[3];
+    // two channels per word: a wavefront's sum is at most 64 * 255 < 2^16
+    uint32_t rb = inside ? mw & 0x00FF00FFu : 0u, g = inside ? (mw >> 8) & 0xFFu : 0u;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        uint32_t v = inside ? (mw >> (8 * j)) & 0xFFu : 0u;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        c[j] = v;
+    for (int off = 32; off > 0; off >>= 1) {
+        rb += __shfl_xor(rb, off, 64);
+        g += __shfl_xor(g, off, 64);
     }
+    const uint32_t c[3] = {rb & 0xFFFFu, g, rb >> 16};
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
         for (int j = 0; j < 3; ++j) part[threadIdx.x >> 6][j] = c[j];
@@ -97,19 +131,21 @@ __global__ __launch_bounds__(kBlock) void pbas_grad_fill_kernel(PbasGradArgs a) 
     const uint32_t mw = colour_magnitudes(a.rgb, a.rgb_stride, x, y, a.W, a.H);
     add_magnitudes(a.m.gsum, a.t, mw, inside);
     if (!inside) return;
-    const int64_t o = (int64_t)a.t * a.npix + p;
-    a.m.samples[o] = v;
-    a.m.gsamples[o] = mw;
+    *reinterpret_cast<uint32_t*>(sample_byte(a.m.samples, a.npix, (int)a.t, p, 0)) = v;
+    *reinterpret_cast<uint32_t*>(sample_byte(a.m.gsamples, a.npix, (int)a.t, p, 0)) = mw;
     a.m.last[p] = v;
     a.m.last_g[p] = mw;
     a.m.mask[p] = 0;
 }
 
-// One updating frame on a 64x4 tile (the plain variant's tiling, so the fire-byte
-// halo and the LDS scatter of pending neighbour writes are shared).
-__global__ __launch_bounds__(kBlock) void pbas_grad_step_kernel(PbasGradArgs a) {
-    __shared__ PbasLds<kGradNmax> sh;
-    constexpr int NW = PbasLds<kGradNmax>::NW;
+// One updating frame on a 64x4 tile: the plain variant's tiling, fire-byte halo, LDS scatter of
+// pending neighbour writes, register merges and whole-sector write-back (pbas_device.h), on two
+// words per slot.
+template <int NMAX, bool NT>
+__global__ __launch_bounds__(kBlock, NMAX <= 24 ? 4 : (NMAX <= 40 ? 3 : 2)) void pbas_grad_step_kernel(PbasGradArgs a) {
+    constexpr int NLO = grad_class_min(NMAX);
+    constexpr int NW = PbasLds<NMAX>::NW;
+    __shared__ PbasLds<NMAX> sh;
     const int tid = threadIdx.x;
     const int tiles_x = (a.W + kTileW - 1) / kTileW;
     const int bx = (int)blockIdx.x % tiles_x, by = (int)blockIdx.x / tiles_x;
@@ -127,9 +163,32 @@ __global__ __launch_bounds__(kBlock) void pbas_grad_step_kernel(PbasGradArgs a) 
         for (int w = 0; w < NW; ++w) sh.pend[w * kBlock + tid] = 0u;
         fin = load_fire(a.m.fire[(a.t - 1u) & 1u], x0, y0, a.H, a.W);
     }
+    const float4 Tv = a.m.T[p];
     bool valid;
     const uint32_t Iw = frame_word(a, x, y, valid);
     const uint32_t Mw = colour_magnitudes(a.rgb, a.rgb_stride, x, y, a.W, a.H);
+    const float4 Rv = a.m.R[p], Sv = a.m.S[p];
+    const uint32_t lastw = a.m.last[p], lastg = a.m.last_g[p];
+
+    uint32_t sm[NMAX], gm[NMAX];
+    const int64_t p0 = (int64_t)y0 * a.W + x0;  // tile origin, < npix
+    const int64_t qleft = (npix - p0) * 16;
+    const uint32_t qrange = qleft > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)qleft;
+    const uint32_t voff = (uint32_t)(p - p0) * 16u;
+#pragma unroll
+    for (int q = 0; q < NMAX / 4; ++q) {
+        const bool used = 4 * q < NLO || 4 * q < N;
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+        const u32x4 v = used ? ld_quad<NT>(a.m.samples + p0 * 4, npix, qrange, q, voff) : zero;
+        const u32x4 g = used ? ld_quad<NT>(a.m.gsamples + p0 * 4, npix, qrange, q, voff) : zero;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sm[4 * q + i] = v[i];
+            gm[4 * q + i] = g[i];
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
     // weights from the previous frame's magnitude sums
     float wgt[3];
 #pragma unroll
@@ -140,80 +199,99 @@ __global__ __launch_bounds__(kBlock) void pbas_grad_step_kernel(PbasGradArgs a) 
     }
     if (a.apply_pending) {
         __syncthreads();  // bit-words cleared
-        scatter_fired<kGradNmax>(sh, fin, N, a.t - 1u, a.c.key0, a.c.key1);
-        __syncthreads();  // every write aimed at the tile recorded
+        scatter_fired<NMAX>(sh, fin, N, a.t - 1u, a.c.key0, a.c.key1);
     }
-    add_magnitudes(a.m.gsum, a.t, Mw, inside);  // frame t's sums (after the reads of t-1's slot)
+    // Self-update candidates (the 1/T test with T from before this frame) and the D they replace.
+    float T[4] = {Tv.x, Tv.y, Tv.z, Tv.w};
+    const bool active[4] = {true, true, true, valid};
+    const float inv16 = 1.0f / 65536.0f;
+    const U32x4 w0 = philox4x32_10((uint32_t)p, a.t, 0u, 0u, a.c.key0, a.c.key1);
+    bool cand[4];
+    int ks[4];
+    float dold[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t a0 = w0.v[j];
+        cand[j] = active[j] && (float)(a0 >> 16) * inv16 * T[j] < 1.0f;
+        ks[j] = (int)(__umul24(a0 & 0xFFFFu, (uint32_t)N) >> 16);
+        dold[j] = cand[j] ? reinterpret_cast<const float*>(a.m.D + (int64_t)ks[j] * npix + p)[j] : 0.0f;
+    }
+    if (a.apply_pending) __syncthreads();  // every write aimed at the tile recorded
+    add_magnitudes(a.m.gsum, a.t, Mw, inside);  // frame t's sums
     if (!inside) return;
 
-    const float4 Tv = a.m.T[p], Rv = a.m.R[p], Sv = a.m.S[p];
     float R[4] = {Rv.x, Rv.y, Rv.z, Rv.w};
-    float T[4] = {Tv.x, Tv.y, Tv.z, Tv.w};
     float S[4] = {Sv.x, Sv.y, Sv.z, Sv.w};
-    const uint32_t lastw = a.m.last[p], lastg = a.m.last_g[p];
-    const bool active[4] = {true, true, true, valid};
 
-    // Frame t-1's neighbour writes into this pixel (its previous value and magnitudes)
-    // are merged slot by slot, then each slot is classified.
-    // (bit-word k >> 3 read from LDS when its first slot comes: a register array
-    // indexed by a run-time slot would go to scratch memory)
+    // Frame t-1's neighbour writes into this pixel (its previous value and magnitudes) are
+    // merged slot by slot, then each slot is classified: bytes become floats in one
+    // instruction, differences and their absolute values are exact.
+    uint32_t pw[NW];
     const uint32_t keep = (lastw >> 24) != 0u ? 0xFFFFFFFFu : 0x00FFFFFFu;  // depth at t-1?
+#pragma unroll
+    for (int w = 0; w < NW; ++w) pw[w] = a.apply_pending ? sh.pend[w * kBlock + tid] & keep : 0u;
+    const float fi[4] = {(float)(Iw & 0xFFu), (float)((Iw >> 8) & 0xFFu), (float)((Iw >> 16) & 0xFFu), (float)(Iw >> 24)};
+    const float fm[3] = {(float)(Mw & 0xFFu), (float)((Mw >> 8) & 0xFFu), (float)((Mw >> 16) & 0xFFu)};
     int cnt[4] = {0, 0, 0, 0};
     float dmin[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
-    uint32_t pw = 0u;
-    for (int k = 0; k < N; ++k) {
-        const int64_t o = (int64_t)k * npix + p;
-        uint32_t s = a.m.samples[o], g = a.m.gsamples[o];
-        if ((k & 7) == 0) pw = a.apply_pending ? sh.pend[(k >> 3) * kBlock + tid] & keep : 0u;
-        const uint32_t bm = slot_byte_mask(pw, k);
-        if (bm) {
-            s = (s & ~bm) | (lastw & bm);
-            g = (g & ~(bm & 0x00FFFFFFu)) | (lastg & bm & 0x00FFFFFFu);
-            a.m.samples[o] = s;
-            a.m.gsamples[o] = g;
-        }
+    uint32_t dirty_s = 0u, dirty_g = 0u, chg_s = 0u, chg_g = 0u;
+    uint32_t byte_ids;
+    asm("v_mov_b32 %0, 0x03020100" : "=v"(byte_ids));
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const int dv = abs((int)((s >> (8 * j)) & 0xFFu) - (int)((Iw >> (8 * j)) & 0xFFu));
-            const int dm = abs((int)((g >> (8 * j)) & 0xFFu) - (int)((Mw >> (8 * j)) & 0xFFu));
-            const float d = wgt[j] * (float)dm + (float)dv;
-            cnt[j] += d < R[j] ? 1 : 0;
-            dmin[j] = fminf(dmin[j], d);
+    for (int k = 0; k < NMAX; ++k) {
+        if ((k & 3) == 0) __builtin_amdgcn_sched_barrier(0);  // a slot's work stays next to its words
+        const uint32_t s0 = sm[k], g0 = gm[k];
+        sm[k] = merge_slot(s0, lastw, pw[k >> 3], k, byte_ids);
+        gm[k] = merge_slot(g0, lastg, pw[k >> 3], k, byte_ids);  // (byte 3 is 0 on both sides)
+        chg_s |= sm[k] ^ s0;
+        chg_g |= gm[k] ^ g0;
+        if ((k & 3) == 3) {
+            dirty_s |= (chg_s != 0u ? 1u : 0u) << (k >> 2);
+            dirty_g |= (chg_g != 0u ? 1u : 0u) << (k >> 2);
+            chg_s = chg_g = 0u;
+            asm volatile("" : "+v"(dirty_s), "+v"(dirty_g));  // (each quad's test next to its slots)
         }
-        const uint32_t sd = s >> 24;
-        if (sd != 0u) {  // a depth byte 0 in a sample: nothing recorded
-            const float d = (float)abs((int)sd - (int)(Iw >> 24));
+        if (k < NLO || k < N) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const float dv = (float)((sm[k] >> (8 * j)) & 0xFFu) - fi[j];
+                const float dm = (float)((gm[k] >> (8 * j)) & 0xFFu) - fm[j];
+                const float d = wgt[j] * fabsf(dm) + fabsf(dv);
+                cnt[j] += d < R[j] ? 1 : 0;
+                dmin[j] = fminf(dmin[j], d);
+            }
+            const float sd = (float)(sm[k] >> 24);
+            const float d = sd != 0.0f ? fabsf(sd - fi[3]) : INFINITY;  // a depth byte 0: nothing recorded
             cnt[3] += d < R[3] ? 1 : 0;
             dmin[3] = fminf(dmin[3], d);
+            // (a slot is finished before the next: left to itself the scheduler keeps the
+            // distances of many slots and needs 40 more registers)
+            asm volatile("" : "+v"(dmin[0]), "+v"(dmin[1]), "+v"(dmin[2]), "+v"(dmin[3]));
+            asm volatile("" : "+v"(cnt[0]), "+v"(cnt[1]), "+v"(cnt[2]), "+v"(cnt[3]));
         }
     }
+    __builtin_amdgcn_sched_barrier(0);
     if (dmin[3] == INFINITY) dmin[3] = 255.0f;
 
-    bool F[4];
+    bool F[4], upd[4];
     bool fg = false;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         F[j] = active[j] && cnt[j] < a.c.min_matches;
         fg = fg || F[j];
+        upd[j] = cand[j] && !F[j];
     }
     a.m.mask[p] = fg ? (uint8_t)255 : (uint8_t)0;
 
-    // Self-update with probability 1/T (T from before this frame): slot k of channel j
-    // takes the value (and magnitude), its D slot d_min, S = (S - D_k) + d_min.
-    const float inv16 = 1.0f / 65536.0f;
-    const U32x4 w0 = philox4x32_10((uint32_t)p, a.t, 0u, 0u, a.c.key0, a.c.key1);
+    // Self-update: slot ks[j] of channel j takes the value (and magnitude), its D slot d_min,
+    // S = (S - D_k) + d_min.
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint32_t a0 = w0.v[j];
-        if (!active[j] || F[j] || !((float)(a0 >> 16) * inv16 * T[j] < 1.0f)) continue;
-        const int k = (int)(__umul24(a0 & 0xFFFFu, (uint32_t)N) >> 16);
-        const int64_t o = (int64_t)k * npix + p;
-        reinterpret_cast<uint8_t*>(a.m.samples + o)[j] = (uint8_t)(Iw >> (8 * j));
-        if (j < 3) reinterpret_cast<uint8_t*>(a.m.gsamples + o)[j] = (uint8_t)(Mw >> (8 * j));
-        float* dk = reinterpret_cast<float*>(a.m.D + o) + j;
-        S[j] = (S[j] - *dk) + dmin[j];
-        *dk = dmin[j];
-    }
+    for (int j = 0; j < 4; ++j)
+        if (upd[j]) {
+            S[j] = (S[j] - dold[j]) + dmin[j];
+            if (__float_as_uint(dold[j]) != __float_as_uint(dmin[j]))
+                reinterpret_cast<float*>(a.m.D + (int64_t)ks[j] * npix + p)[j] = dmin[j];
+        }
 
     // Neighbour update with probability 1/T: record the channels that fired.
     const U32x4 w1 = philox4x32_10((uint32_t)p, a.t, 1u, 0u, a.c.key0, a.c.key1);
@@ -241,9 +319,54 @@ __global__ __launch_bounds__(kBlock) void pbas_grad_step_kernel(PbasGradArgs a) 
         const float tt = F[j] ? T[j] + q : T[j] - q;
         T[j] = fminf(fmaxf(tt, a.c.T_lower), a.c.T_upper);
     }
-    a.m.R[p] = make_float4(R[0], R[1], R[2], R[3]);
-    a.m.T[p] = make_float4(T[0], T[1], T[2], T[3]);
-    a.m.S[p] = make_float4(S[0], S[1], S[2], S[3]);
+
+    // The self-update's bit-words, built in the lane's own LDS words (read above, touched by no
+    // other lane since the scatter's barrier), then merged quad by quad at the store; a quad goes
+    // back only where a byte of it changed in one of the 4 pixels of its 64-byte sector.
+    uint32_t sw[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) sh.pend[w * kBlock + tid] = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (upd[j])
+            __hip_atomic_fetch_or(&sh.pend[(ks[j] >> 3) * kBlock + tid], 1u << (8 * j + (ks[j] & 7)),
+                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) sw[w] = sh.pend[w * kBlock + tid];
+    uint32_t* sbase = a.m.samples + p0 * 4;
+    uint32_t* gbase = a.m.gsamples + p0 * 4;
+    asm volatile("" : "+s"(sbase), "+s"(gbase));
+#pragma unroll
+    for (int q = 0; q < NMAX / 4; ++q) {
+        if (!(4 * q < NLO || 4 * q < N)) continue;
+        uint32_t cs = 0u, cg = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = 4 * q + i;
+            const uint32_t s0 = sm[k], g0 = gm[k];
+            sm[k] = merge_slot(s0, Iw, sw[k >> 3], k, byte_ids);
+            gm[k] = merge_slot(g0, Mw, sw[k >> 3], k, byte_ids);
+            cs |= sm[k] ^ s0;
+            cg |= gm[k] ^ g0;
+        }
+        int d = (int)(((dirty_s >> q) & 1u) | (cs != 0u ? 1u : 0u)) | (int)((((dirty_g >> q) & 1u) | (cg != 0u ? 1u : 0u)) << 1);
+        d |= __builtin_amdgcn_update_dpp(0, d, 0xB1, 0xF, 0xF, false);
+        d |= __builtin_amdgcn_update_dpp(0, d, 0x4E, 0xF, 0xF, false);
+        if (d & 1) {
+            const u32x4 v = {sm[4 * q], sm[4 * q + 1], sm[4 * q + 2], sm[4 * q + 3]};
+            st_quad<NT>(sbase, npix, qrange, q, voff, v);
+        }
+        if (d & 2) {
+            const u32x4 g = {gm[4 * q], gm[4 * q + 1], gm[4 * q + 2], gm[4 * q + 3]};
+            st_quad<NT>(gbase, npix, qrange, q, voff, g);
+        }
+    }
+    const float4 Rn = make_float4(R[0], R[1], R[2], R[3]);
+    const float4 Tn = make_float4(T[0], T[1], T[2], T[3]);
+    const float4 Sn = make_float4(S[0], S[1], S[2], S[3]);
+    if (differs(Rn, Rv)) a.m.R[p] = Rn;
+    if (differs(Tn, Tv)) a.m.T[p] = Tn;
+    if (differs(Sn, Sv)) a.m.S[p] = Sn;
     a.m.last[p] = Iw;
     a.m.last_g[p] = Mw;
     a.m.fire[a.t & 1u][p] = (uint8_t)fire;
@@ -272,9 +395,8 @@ __global__ __launch_bounds__(256) void pbas_grad_flush_kernel(PbasGradPlanes m, 
             intent_of(w1.v[j], N, dq, slot);
             const uint32_t val = (lastw >> (8 * j)) & 0xFFu;
             if (dq != 7 - d || (j == 3 && val == 0u)) continue;
-            const int64_t o = (int64_t)slot * npix + p;
-            reinterpret_cast<uint8_t*>(m.samples + o)[j] = (uint8_t)val;
-            if (j < 3) reinterpret_cast<uint8_t*>(m.gsamples + o)[j] = (uint8_t)(lastg >> (8 * j));
+            *sample_byte(m.samples, npix, slot, p, j) = (uint8_t)val;
+            if (j < 3) *sample_byte(m.gsamples, npix, slot, p, j) = (uint8_t)(lastg >> (8 * j));
         }
     }
 }
@@ -332,6 +454,12 @@ __global__ void pbas_grad_sums_kernel(unsigned long long* gsum, uint32_t* canon,
 
 inline unsigned blocks1d(int64_t n) { return (unsigned)((n + 255) / 256); }
 
+template <int NMAX>
+void launch_step(const PbasGradArgs& a, dim3 grid, hipStream_t s) {
+    if (a.streaming) hipLaunchKernelGGL((pbas_grad_step_kernel<NMAX, true>), grid, dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((pbas_grad_step_kernel<NMAX, false>), grid, dim3(kBlock), 0, s, a);
+}
+
 }  // namespace
 
 hipError_t pbas_grad_launch_init_state(const PbasGradPlanes& m, int npix, const PbasConsts& c, hipStream_t s) {
@@ -346,7 +474,15 @@ hipError_t pbas_grad_launch_step(const PbasGradArgs& a, hipStream_t s) {
     } else {
         const int64_t tiles = (int64_t)((a.W + kTileW - 1) / kTileW) * ((a.H + kTileH - 1) / kTileH);
         if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(pbas_grad_step_kernel, dim3((unsigned)tiles), dim3(kBlock), 0, s, a);
+        const dim3 grid((unsigned)tiles);
+        const int N = a.c.N;
+        if (N <= 8) launch_step<8>(a, grid, s);
+        else if (N <= 16) launch_step<16>(a, grid, s);
+        else if (N <= 20) launch_step<20>(a, grid, s);
+        else if (N <= 24) launch_step<24>(a, grid, s);
+        else if (N <= 32) launch_step<32>(a, grid, s);
+        else if (N <= 40) launch_step<40>(a, grid, s);
+        else launch_step<64>(a, grid, s);
     }
     return hipGetLastError();
 }
@@ -361,8 +497,8 @@ hipError_t pbas_grad_launch_flush(const PbasGradPlanes& m, int H, int W, uint32_
 hipError_t pbas_grad_launch_export(const PbasGradPlanes& m, int npix, int N, int64_t t, uint8_t* out,
                                    hipStream_t s) {
     const size_t plane = (size_t)npix * 4;
-    hipError_t e = hipMemcpyAsync(out, m.samples, plane * N, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(out + plane * N, m.gsamples, plane * N, hipMemcpyDeviceToDevice, s);
+    hipError_t e = pbas_launch_export_quads(m.samples, npix, N, out, s);
+    if (e == hipSuccess) e = pbas_launch_export_quads(m.gsamples, npix, N, out + plane * N, s);
     if (e != hipSuccess) return e;
     float* dout = reinterpret_cast<float*>(out + 2 * plane * N);
     float* rts = reinterpret_cast<float*>(out + 6 * plane * N);
@@ -377,8 +513,8 @@ hipError_t pbas_grad_launch_export(const PbasGradPlanes& m, int npix, int N, int
 hipError_t pbas_grad_launch_import(const PbasGradPlanes& m, int npix, int N, int64_t t, const uint8_t* in,
                                    hipStream_t s) {
     const size_t plane = (size_t)npix * 4;
-    hipError_t e = hipMemcpyAsync(m.samples, in, plane * N, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(m.gsamples, in + plane * N, plane * N, hipMemcpyDeviceToDevice, s);
+    hipError_t e = pbas_launch_import_quads(m.samples, npix, N, in, s);
+    if (e == hipSuccess) e = pbas_launch_import_quads(m.gsamples, npix, N, in + plane * N, s);
     if (e != hipSuccess) return e;
     const float* din = reinterpret_cast<const float*>(in + 2 * plane * N);
     const float* rts = reinterpret_cast<const float*>(in + 6 * plane * N);

@@ -222,13 +222,23 @@ hipError_t pbas_launch_flush(const PbasPlanes& m, int H, int W, uint32_t t_prev,
     return hipGetLastError();
 }
 
+hipError_t pbas_launch_export_quads(const uint32_t* quads, int npix, int N, uint8_t* out, hipStream_t s) {
+    hipLaunchKernelGGL(pbas_export_samples_kernel, dim3(blocks1d(npix)), dim3(256), 0, s,
+                       reinterpret_cast<const uint4*>(quads), reinterpret_cast<uint32_t*>(out), npix, N);
+    return hipGetLastError();
+}
+
+hipError_t pbas_launch_import_quads(uint32_t* quads, int npix, int N, const uint8_t* in, hipStream_t s) {
+    hipLaunchKernelGGL(pbas_import_samples_kernel, dim3(blocks1d(npix)), dim3(256), 0, s,
+                       reinterpret_cast<uint4*>(quads), reinterpret_cast<const uint32_t*>(in), npix, N);
+    return hipGetLastError();
+}
+
 // Canonical payload: samples[N] u32, dhist[N] u32, R[4] f32, T[4] f32, S[4] u16
 // (out and in are 4-byte aligned device buffers).
 hipError_t pbas_launch_export(const PbasPlanes& m, int npix, int N, uint8_t* out, hipStream_t s) {
     const size_t plane = (size_t)npix * 4;
-    hipLaunchKernelGGL(pbas_export_samples_kernel, dim3(blocks1d(npix)), dim3(256), 0, s,
-                       reinterpret_cast<const uint4*>(m.samples), reinterpret_cast<uint32_t*>(out), npix, N);
-    hipError_t e = hipGetLastError();
+    hipError_t e = pbas_launch_export_quads(m.samples, npix, N, out, s);
     if (e != hipSuccess) return e;
     e = hipMemcpyAsync(out + plane * N, m.dhist, plane * N, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return e;
@@ -241,9 +251,7 @@ hipError_t pbas_launch_export(const PbasPlanes& m, int npix, int N, uint8_t* out
 hipError_t pbas_launch_import(const PbasPlanes& m, int npix, int N, const uint8_t* in,
                               hipStream_t s) {
     const size_t plane = (size_t)npix * 4;
-    hipLaunchKernelGGL(pbas_import_samples_kernel, dim3(blocks1d(npix)), dim3(256), 0, s,
-                       reinterpret_cast<uint4*>(m.samples), reinterpret_cast<const uint32_t*>(in), npix, N);
-    hipError_t e = hipGetLastError();
+    hipError_t e = pbas_launch_import_quads(m.samples, npix, N, in, s);
     if (e != hipSuccess) return e;
     e = hipMemcpyAsync(m.dhist, in + plane * N, plane * N, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return e;

@@ -287,6 +287,7 @@ void fgs::model_next_pbas_grad(fgs_model* m, const uint8_t* rgb, int64_t rs, con
     a->geom = frame_geom(m->H, m->W, rs, ds, dh, dw);
     a->t = (uint32_t)m->t;
     a->apply_pending = m->pending ? 1 : 0;
+    a->streaming = model_use_streaming(m) ? 1 : 0;
     a->c = m->pc;
     m->pending = m->t >= m->pp.N;
     m->t += 1;
@@ -450,8 +451,8 @@ fgs_status fgs_create(fgs_algo algo, int32_t H, int32_t W, const void* params, v
         off += align256((size_t)gmm_planes(m->gp.Kc, m->gp.Kd, m->gp.var_mode) * n * 16);
     } else if (m->pp.gradient) {
         const size_t N = (size_t)m->pp.N;
-        o_samples = off; off += align256(N * n * 4);
-        o_gs = off;      off += align256(N * n * 4);
+        o_samples = off; off += align256((size_t)((N + 3) & ~3) * n * 4);  // quad planes
+        o_gs = off;      off += align256((size_t)((N + 3) & ~3) * n * 4);
         o_dhist = off;   off += align256(N * n * 16);
         o_R = off;       off += align256(n * 16);
         o_T = off;       off += align256(n * 16);
@@ -1051,8 +1052,10 @@ fgs_status fgs_get_state(fgs_model* m, fgs_state_field* fields, int32_t capacity
         const uint8_t* smp = reinterpret_cast<const uint8_t*>(m->pg.samples);
         const uint8_t* gsm = reinterpret_cast<const uint8_t*>(m->pg.gsamples);
         const uint8_t* dh = reinterpret_cast<const uint8_t*>(m->pg.D);
-        for (int k = 0; k < N; ++k) add("samples", k, 0, FGS_DTYPE_U32, 4, smp + (int64_t)k * n * 4, 4);
-        for (int k = 0; k < N; ++k) add("gsamples", k, 0, FGS_DTYPE_U32, 4, gsm + (int64_t)k * n * 4, 4);
+        for (int k = 0; k < N; ++k)  // quad planes, as below
+            add("samples", k, 0, FGS_DTYPE_U32, 4, smp + (int64_t)(k >> 2) * n * 16 + 4 * (k & 3), 16);
+        for (int k = 0; k < N; ++k)
+            add("gsamples", k, 0, FGS_DTYPE_U32, 4, gsm + (int64_t)(k >> 2) * n * 16 + 4 * (k & 3), 16);
         for (int k = 0; k < N; ++k)
             for (int j = 0; j < 4; ++j) add("dhist", k, j, FGS_DTYPE_F32, 4, dh + (int64_t)k * n * 16 + 4 * j, 16);
         for (int j = 0; j < 4; ++j)
