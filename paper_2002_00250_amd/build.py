@@ -24,7 +24,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libfgs.so")
-SOURCES = ["gmm_kernels.hip", "gmm_window.hip", "window_loss.hip", "pbas_kernels.hip", "pbas_grad_kernels.hip", "serve_kernels.hip", "diag_kernels.hip", "eval_kernels.hip", "postfilter_kernels.hip", "static_kernels.hip",
+SOURCES = ["gmm_kernels.hip", "gmm_window.hip", "window_loss.hip", "mask_kernels.hip", "pbas_kernels.hip", "pbas_grad_kernels.hip", "serve_kernels.hip", "diag_kernels.hip", "eval_kernels.hip", "postfilter_kernels.hip", "static_kernels.hip",
            "runtime.cpp", "server.cpp"]
 ARCH = os.environ.get("FGS_OFFLOAD_ARCH", "gfx950")
 

@@ -28,6 +28,9 @@ struct fgs_model {
     uint8_t* dev_in;
     hipEvent_t stage_done;
     bool stage_busy;
+    // pinned bytes a host mask read goes through (allocated on the first one)
+    uint8_t* mask_stage;
+    size_t mask_stage_bytes;
     // evaluation (allocated on the first fgs_eval_accumulate)
     unsigned long long* eval_acc;  // device: TP, TN, FP, FN, kEvalSlots partial sums each
     uint8_t* gt_stage;             // pinned host copy of a host ground truth

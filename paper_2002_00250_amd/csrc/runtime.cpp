@@ -148,6 +148,15 @@ fgs_status check_pbas(const fgs_pbas_params& p) {
     return FGS_OK;
 }
 
+// H rows of `row` bytes, `stride` apart, to packed rows.
+void copy_rows(uint8_t* dst, const uint8_t* src, int64_t stride, size_t row, int H) {
+    if (stride == (int64_t)row) {
+        std::memcpy(dst, src, row * (size_t)H);
+        return;
+    }
+    for (int y = 0; y < H; ++y) std::memcpy(dst + (size_t)y * row, src + (int64_t)y * stride, row);
+}
+
 fgs_status ensure_staging(fgs_model* m) {
     if (m->host_stage) return FGS_OK;
     const size_t bytes = align256((size_t)m->npix * 3) + align256((size_t)m->npix * 2);
@@ -300,6 +309,82 @@ fgs_status static_after_push(fgs_model* m) {
     if (m->st_M <= 0) return FGS_OK;
     FGS_HIP(m, static_launch_update(m->mask, m->st_count, m->st_mask, m->npix, (uint32_t)m->st_M, m->stream));
     m->st_frames += 1;
+    return FGS_OK;
+}
+
+// A mask plane of the model to the caller's rows.  Host rows are reached through pinned memory
+// that the copy kernel writes: a copy of rows straight to pageable memory goes row by row (3.3 ms
+// for 480 rows of 640 bytes).  At most kMaskStage bytes are pinned; larger planes go in parts.
+constexpr size_t kMaskStage = (size_t)16 << 20;
+
+// What the runtime knows of a caller's pointer: device memory (and whose), or nothing.
+enum class Place { kUnknown, kThisDevice, kOtherDevice };
+Place place_of(const void* p, int device) {
+    hipPointerAttribute_t at;
+    std::memset(&at, 0, sizeof at);
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return Place::kUnknown;
+    }
+    if (at.type != hipMemoryTypeDevice) return Place::kUnknown;
+    return at.device == device ? Place::kThisDevice : Place::kOtherDevice;
+}
+
+// Whether [p, p + bytes) lies in one allocation of this device, so that a kernel may write it.
+bool kernel_may_write(void* p, size_t bytes, int device) {
+    if (place_of(p, device) != Place::kThisDevice) return false;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const size_t at = (size_t)((uintptr_t)p - (uintptr_t)base);
+    return at <= size && bytes <= size - at;
+}
+
+fgs_status read_plane(fgs_model* m, const uint8_t* plane, uint8_t* out, int64_t stride, fgs_mem where) {
+    if (where != FGS_MEM_HOST && where != FGS_MEM_DEVICE)
+        return fail(FGS_ERR_INVALID_ARG, "bad memory kind %d", (int)where);
+    const int64_t n = m->npix, W = m->W;
+    // The runtime's own copy, which checks what it is given: for memory that is not where `where`
+    // says, of another device or shorter than the rows, and where no memory can be pinned.
+    auto copy = [&](hipMemcpyKind kind) {
+        FGS_HIP(m, hipMemcpy2DAsync(out, (size_t)stride, plane, (size_t)W, (size_t)W, (size_t)m->H, kind, m->stream));
+        if (where == FGS_MEM_HOST) FGS_HIP(m, hipStreamSynchronize(m->stream));
+        return FGS_OK;
+    };
+    if (where == FGS_MEM_DEVICE) {
+        if (!kernel_may_write(out, (size_t)(m->H - 1) * (size_t)stride + (size_t)W, m->device))
+            return copy(hipMemcpyDeviceToDevice);
+        FGS_HIP(m, mask_launch_copy(plane, m->W, out, stride, 0, n, m->stream));
+        return FGS_OK;
+    }
+    if (place_of(out, m->device) != Place::kUnknown) return copy(hipMemcpyDeviceToHost);
+    if (!m->mask_stage) {
+        const size_t bytes = std::min((size_t)n, kMaskStage);
+        if (hipHostMalloc((void**)&m->mask_stage, bytes, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            m->mask_stage = nullptr;
+            return copy(hipMemcpyDeviceToHost);
+        }
+        m->mask_stage_bytes = bytes;
+    }
+    for (int64_t at = 0; at < n; at += (int64_t)m->mask_stage_bytes) {
+        const int64_t part = std::min(n - at, (int64_t)m->mask_stage_bytes);
+        // (as one row: the staging holds the part's bytes without gaps)
+        FGS_HIP(m, mask_launch_copy(plane + at, (int)part, m->mask_stage, part, 0, part, m->stream));
+        FGS_HIP(m, hipStreamSynchronize(m->stream));
+        if (stride == W) {
+            std::memcpy(out + at, m->mask_stage, (size_t)part);
+            continue;
+        }
+        for (int64_t i = at; i < at + part;) {
+            const int64_t y = i / W, x = i - y * W, run = std::min(W - x, at + part - i);
+            std::memcpy(out + y * stride + x, m->mask_stage + (i - at), (size_t)run);
+            i += run;
+        }
+    }
     return FGS_OK;
 }
 
@@ -543,6 +628,7 @@ fgs_status fgs_destroy(fgs_model* m) {
         (void)hipEventDestroy(m->gt_done);
         (void)hipHostFree(m->gt_stage);
     }
+    if (m->mask_stage) (void)hipHostFree(m->mask_stage);
     if (m->host_stage) {
         (void)hipEventDestroy(m->stage_done);
         (void)hipHostFree(m->host_stage);
@@ -587,13 +673,12 @@ fgs_status fgs_push_frame_scaled(fgs_model* m, const uint8_t* rgb, int64_t rgb_s
         const size_t rgb_bytes = (size_t)m->npix * 3;
         uint8_t* hr = m->host_stage;
         uint8_t* hd = m->host_stage + align256(rgb_bytes);
-        for (int y = 0; y < m->H; ++y)
-            std::memcpy(hr + (size_t)y * 3 * m->W, rgb + (size_t)y * rgb_stride, (size_t)3 * m->W);
-        for (int y = 0; y < depth_H; ++y)
-            std::memcpy(hd + (size_t)y * 2 * depth_W, reinterpret_cast<const uint8_t*>(depth) + (size_t)y * depth_stride,
-                        (size_t)2 * depth_W);
-        const size_t bytes = align256(rgb_bytes) + (size_t)m->npix * 2;
-        FGS_HIP(m, hipMemcpyAsync(m->dev_in, m->host_stage, bytes, hipMemcpyHostToDevice, m->stream));
+        // the colours are on their way while the depth map is copied
+        copy_rows(hr, rgb, rgb_stride, (size_t)3 * m->W, m->H);
+        FGS_HIP(m, hipMemcpyAsync(m->dev_in, hr, rgb_bytes, hipMemcpyHostToDevice, m->stream));
+        copy_rows(hd, reinterpret_cast<const uint8_t*>(depth), depth_stride, (size_t)2 * depth_W, depth_H);
+        FGS_HIP(m, hipMemcpyAsync(m->dev_in + align256(rgb_bytes), hd, (size_t)2 * depth_W * depth_H,
+                                  hipMemcpyHostToDevice, m->stream));
         FGS_HIP(m, hipEventRecord(m->stage_done, m->stream));
         m->stage_busy = true;
         drgb = m->dev_in;
@@ -707,17 +792,7 @@ fgs_status fgs_get_mask(fgs_model* m, uint8_t* mask, int64_t stride, fgs_mem whe
     if (m->poisoned) return fail(FGS_ERR_DEVICE, "model is poisoned by an earlier device error");
     if (stride < m->W) return fail(FGS_ERR_INVALID_ARG, "mask stride %lld < W", (long long)stride);
     if (m->t == 0) return fail(FGS_ERR_BAD_STATE, "no frame has been pushed");
-    if (where == FGS_MEM_HOST) {
-        FGS_HIP(m, hipMemcpy2DAsync(mask, (size_t)stride, m->mask, (size_t)m->W, (size_t)m->W,
-                                    (size_t)m->H, hipMemcpyDeviceToHost, m->stream));
-        FGS_HIP(m, hipStreamSynchronize(m->stream));
-    } else if (where == FGS_MEM_DEVICE) {
-        FGS_HIP(m, hipMemcpy2DAsync(mask, (size_t)stride, m->mask, (size_t)m->W, (size_t)m->W,
-                                    (size_t)m->H, hipMemcpyDeviceToDevice, m->stream));
-    } else {
-        return fail(FGS_ERR_INVALID_ARG, "bad memory kind %d", (int)where);
-    }
-    return FGS_OK;
+    return read_plane(m, m->mask, mask, stride, where);
 }
 
 fgs_status fgs_static_enable(fgs_model* m, int32_t M) {
@@ -757,11 +832,7 @@ fgs_status fgs_static_mask(fgs_model* m, uint8_t* out, int64_t stride, fgs_mem w
         return fail(FGS_ERR_INVALID_ARG, "bad memory kind %d", (int)where);
     if (m->st_M <= 0) return fail(FGS_ERR_BAD_STATE, "static-object detection is not enabled");
     if (m->st_frames == 0) return fail(FGS_ERR_BAD_STATE, "no frame has been counted since it was enabled");
-    FGS_HIP(m, hipMemcpy2DAsync(out, (size_t)stride, m->st_mask, (size_t)m->W, (size_t)m->W, (size_t)m->H,
-                                where == FGS_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice,
-                                m->stream));
-    if (where == FGS_MEM_HOST) FGS_HIP(m, hipStreamSynchronize(m->stream));
-    return FGS_OK;
+    return read_plane(m, m->st_mask, out, stride, where);
 }
 
 fgs_status fgs_mask_device_ptr(fgs_model* m, const uint8_t** out) {
@@ -819,8 +890,7 @@ fgs_status fgs_eval_accumulate(fgs_model* m, const uint8_t* gt, int64_t gt_strid
         st = ensure_gt_staging(m);
         if (st != FGS_OK) return st;
         if (m->gt_busy) FGS_HIP(m, hipEventSynchronize(m->gt_done));
-        for (int y = 0; y < m->H; ++y)
-            std::memcpy(m->gt_stage + (size_t)y * m->W, gt + (size_t)y * gt_stride, (size_t)m->W);
+        copy_rows(m->gt_stage, gt, gt_stride, (size_t)m->W, m->H);
         FGS_HIP(m, hipMemcpyAsync(m->gt_dev, m->gt_stage, (size_t)m->npix, hipMemcpyHostToDevice, m->stream));
         FGS_HIP(m, hipEventRecord(m->gt_done, m->stream));
         m->gt_busy = true;
