@@ -220,6 +220,21 @@ fgs_status fgs_push_frame_scaled(fgs_model* m, const uint8_t* rgb, int64_t rgb_s
                                  int32_t depth_W, fgs_mem where);
 
 /*
+ * Device work in the order of a stream of the caller's: fgs_push_frame_scaled (a depth map of the
+ * frame's size included), fgs_get_mask and fgs_eval_accumulate with FGS_MEM_DEVICE, to run after
+ * what is queued on hip_stream (NULL: the null stream) and before what is queued there later, and
+ * after the model's earlier work wherever that ran.  The result is that of the model's stream
+ * waiting for hip_stream, the call, and hip_stream waiting for the model's stream; a model whose
+ * stream the library made and fgs_stream never gave out runs on hip_stream itself.  Also inside a
+ * graph that hip_stream records.  Errors as the calls named; UNSUPPORTED if another device is
+ * current than the model's (nothing is queued then).
+ */
+fgs_status fgs_push_frame_on(fgs_model* m, const uint8_t* rgb, int64_t rgb_stride, const uint16_t* depth,
+                             int64_t depth_stride, int32_t depth_H, int32_t depth_W, void* hip_stream);
+fgs_status fgs_get_mask_on(fgs_model* m, uint8_t* mask, int64_t stride, void* hip_stream);
+fgs_status fgs_eval_accumulate_on(fgs_model* m, const uint8_t* gt, int64_t gt_stride, void* hip_stream);
+
+/*
  * Push one frame to each of n independent models (many cameras) with as few
  * launches as possible: the result is exactly that of fgs_push_frame(models[i],
  * rgb[i], rgb_stride[i], depth[i], depth_stride[i], FGS_MEM_DEVICE) for each i.
@@ -425,6 +440,26 @@ fgs_status fgs_stream(const fgs_model* m, void** hip_stream);
 /* Device bytes the model holds (state, scratch planes, mask, input staging).
  * INVALID_ARG for NULL arguments. */
 fgs_status fgs_device_bytes(const fgs_model* m, size_t* bytes);
+
+/*
+ * Ordering between two streams, for callers that queue work on a stream of their own beside a
+ * model's: a pair of reusable events of one stream (creating and destroying an event per wait
+ * costs as much as a small frame).
+ * fgs_order_create: for `hip_stream` (e.g. what fgs_stream returned; NULL is the null stream) on
+ *   the current device.
+ * fgs_order_enter: later work on hip_stream waits for what is queued on `other` now.
+ * fgs_order_leave: later work on `other` waits for what is queued on hip_stream now.
+ *   Both return at once and may be recorded into a HIP graph; `other` may be hip_stream itself
+ *   (nothing to wait for).  UNSUPPORTED if another device is current than at creation (nothing is
+ *   queued then).  Not thread-safe per object.
+ * fgs_order_destroy: NULL is accepted; the streams stay the caller's.
+ * Errors: INVALID_ARG (NULL), OUT_OF_MEMORY, UNSUPPORTED, DEVICE.
+ */
+typedef struct fgs_order fgs_order;
+fgs_status fgs_order_create(void* hip_stream, fgs_order** out);
+fgs_status fgs_order_enter(fgs_order* o, void* other);
+fgs_status fgs_order_leave(fgs_order* o, void* other);
+fgs_status fgs_order_destroy(fgs_order* o);
 
 /*
  * How the model's per-frame state traffic treats the last-level (Infinity)

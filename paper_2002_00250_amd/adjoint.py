@@ -24,9 +24,12 @@ class GmmWindow:
         self.device = torch.device(device or "cuda")
         self.stream = torch.cuda.Stream(self.device)
         self.handle = fgs.fgs_gmm_window_create(T, H, W, params, checkpoint_every, self.stream.cuda_stream)
+        with torch.cuda.device(self.device):
+            self._order = fgs.StreamOrder(self.stream.cuda_stream)
 
     def close(self):
         if getattr(self, "handle", None):
+            self._order.close()
             fgs.fgs_gmm_window_destroy(self.handle)
             self.handle = None
 
@@ -50,12 +53,12 @@ class GmmWindow:
         cur = torch.cuda.current_stream(self.device)
         Z = torch.empty((self.T, self.H, self.W), dtype=torch.float32, device=self.device)
         has = torch.empty((self.T, self.H, self.W), dtype=torch.uint8, device=self.device)
-        self.stream.wait_stream(cur)
+        self._order.enter(cur)
         fgs.fgs_gmm_window_forward(self.handle, theta.data_ptr(), rgb.data_ptr(), depth.data_ptr(),
                                    Z.data_ptr(), has.data_ptr())
-        cur.wait_stream(self.stream)
-        for x in (theta, rgb, depth, Z, has):
-            x.record_stream(self.stream)
+        # The current stream waits for the window's here, so the tensors' memory is free for work
+        # queued after this call only once the kernel is done with it (no record_stream needed).
+        self._order.leave(cur)
         self.forwards += 1
         return Z, has
 
@@ -65,12 +68,10 @@ class GmmWindow:
         dZ = dZ.detach().to(torch.float32).contiguous()
         cur = torch.cuda.current_stream(self.device)
         out = torch.empty(3, dtype=torch.float64, device=self.device)
-        self.stream.wait_stream(cur)
+        self._order.enter(cur)
         fgs.fgs_gmm_window_backward(self.handle, theta.data_ptr(), rgb.data_ptr(), depth.data_ptr(),
                                     dZ.data_ptr(), out.data_ptr())
-        cur.wait_stream(self.stream)
-        for x in (theta, rgb, depth, dZ, out):
-            x.record_stream(self.stream)
+        self._order.leave(cur)                # (as in forward)
         return out
 
     def records(self) -> np.ndarray:

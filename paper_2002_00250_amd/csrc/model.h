@@ -17,6 +17,13 @@ struct fgs_model {
     int device;
     hipStream_t stream;
     bool own_stream;
+    // Where the model's last work was queued: `stream`, or another stream that a call asked for
+    // (fgs_*_on), with `done` recorded behind that work.  Only a stream that nobody outside the
+    // library can name (own_stream, not stream_seen) is left for another.
+    hipStream_t at;
+    hipEvent_t done;
+    bool stream_seen;
+    hipEvent_t order_in, order_out;  // fgs_*_on through `stream` (made on the first one)
     uint8_t* dev;      // one allocation: state + scratch planes + mask
     size_t dev_bytes;
     float4* gmm_state;

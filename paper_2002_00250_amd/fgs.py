@@ -96,6 +96,9 @@ def _load():
         "fgs_destroy": (S, [c_void_p]),
         "fgs_push_frame": (S, [c_void_p, c_void_p, c_int64, c_void_p, c_int64, c_int32]),
         "fgs_push_frame_scaled": (S, [c_void_p, c_void_p, c_int64, c_void_p, c_int64, c_int32, c_int32, c_int32]),
+        "fgs_push_frame_on": (S, [c_void_p, c_void_p, c_int64, c_void_p, c_int64, c_int32, c_int32, c_void_p]),
+        "fgs_get_mask_on": (S, [c_void_p, c_void_p, c_int64, c_void_p]),
+        "fgs_eval_accumulate_on": (S, [c_void_p, c_void_p, c_int64, c_void_p]),
         "fgs_push_frames": (S, [POINTER(c_void_p), c_int32, POINTER(c_void_p), POINTER(c_int64),
                                 POINTER(c_void_p), POINTER(c_int64)]),
         "fgs_get_mask": (S, [c_void_p, c_void_p, c_int64, c_int32]),
@@ -111,6 +114,10 @@ def _load():
         "fgs_sync": (S, [c_void_p]),
         "fgs_stream": (S, [c_void_p, POINTER(c_void_p)]),
         "fgs_device_bytes": (S, [c_void_p, POINTER(c_size_t)]),
+        "fgs_order_create": (S, [c_void_p, POINTER(c_void_p)]),
+        "fgs_order_enter": (S, [c_void_p, c_void_p]),
+        "fgs_order_leave": (S, [c_void_p, c_void_p]),
+        "fgs_order_destroy": (S, [c_void_p]),
         "fgs_set_cache_policy": (S, [c_void_p, c_int32]),
         "fgs_gmm_window_create": (S, [c_int32, c_int32, c_int32, POINTER(fgs_gmm_params), c_int32, c_void_p,
                                       POINTER(c_void_p)]),
@@ -204,6 +211,19 @@ def fgs_push_frame_scaled(m: int, rgb: int, rgb_stride: int, depth: int, depth_s
                           depth_W: int, where: int) -> None:
     _check(_load().fgs_push_frame_scaled(c_void_p(m), c_void_p(rgb), rgb_stride, c_void_p(depth),
                                          depth_stride, depth_H, depth_W, where))
+
+
+def fgs_push_frame_on(m: int, rgb: int, rgb_stride: int, depth: int, depth_stride: int, depth_H: int, depth_W: int,
+                      hip_stream: int) -> None:
+    _check(_load().fgs_push_frame_on(m, rgb, rgb_stride, depth, depth_stride, depth_H, depth_W, hip_stream))
+
+
+def fgs_get_mask_on(m: int, mask: int, stride: int, hip_stream: int) -> None:
+    _check(_load().fgs_get_mask_on(m, mask, stride, hip_stream))
+
+
+def fgs_eval_accumulate_on(m: int, gt: int, gt_stride: int, hip_stream: int) -> None:
+    _check(_load().fgs_eval_accumulate_on(m, gt, gt_stride, hip_stream))
 
 
 def fgs_push_frames(models, rgb, rgb_stride, depth, depth_stride) -> None:
@@ -312,6 +332,60 @@ def fgs_device_bytes(m: int) -> int:
     out = c_size_t()
     _check(_load().fgs_device_bytes(c_void_p(m), byref(out)))
     return out.value
+
+
+def fgs_order_create(hip_stream: int) -> int:
+    out = c_void_p()
+    _check(_load().fgs_order_create(c_void_p(hip_stream), byref(out)))
+    return out.value
+
+
+def fgs_order_enter(o: int, other: int) -> None:
+    _check(_load().fgs_order_enter(o, other))
+
+
+def fgs_order_leave(o: int, other: int) -> None:
+    _check(_load().fgs_order_leave(o, other))
+
+
+def fgs_order_destroy(o: int) -> None:
+    _check(_load().fgs_order_destroy(c_void_p(o)))
+
+
+class StreamOrder:
+    """Orders one stream with whatever stream is torch's current one (fgs_order_*): the waits of
+    torch.cuda.Stream.wait_stream with two events kept instead of one made for each wait."""
+
+    def __init__(self, stream_handle: int):
+        import torch
+        self._torch = torch
+        self._stream, self._device = stream_handle, torch.cuda.current_device()
+        self._handle = fgs_order_create(stream_handle)
+        lib = _load()
+        self._enter, self._leave = lib.fgs_order_enter, lib.fgs_order_leave
+
+    def enter(self, other=None) -> None:
+        """The stream waits for the work queued on `other` (torch's current stream)."""
+        other = self._torch.cuda.current_stream() if other is None else other
+        st = self._enter(self._handle, other.cuda_stream)
+        if st == FGS_ERR_UNSUPPORTED:         # another device is current
+            self._torch.cuda.ExternalStream(self._stream, device=self._device).wait_stream(other)
+        elif st != FGS_OK:
+            _check(st)
+
+    def leave(self, other=None) -> None:
+        """`other` (torch's current stream) waits for the work queued on the stream."""
+        other = self._torch.cuda.current_stream() if other is None else other
+        st = self._leave(self._handle, other.cuda_stream)
+        if st == FGS_ERR_UNSUPPORTED:
+            other.wait_stream(self._torch.cuda.ExternalStream(self._stream, device=self._device))
+        elif st != FGS_OK:
+            _check(st)
+
+    def close(self) -> None:
+        if self._handle:
+            fgs_order_destroy(self._handle)
+            self._handle = None
 
 
 def fgs_set_cache_policy(m: int, policy: int) -> None:
@@ -532,9 +606,9 @@ class Model:
     or uint16).
 
     The model runs on its own stream (or the one given).  Device tensors are ordered with
-    torch's current stream: the model's stream waits for the work queued there before a
-    call that reads or writes a tensor, and torch's current stream then waits for the
-    model, so a tensor the model wrote is ready and one it read may be reused or freed."""
+    torch's current stream: a call that reads or writes a tensor runs after the work queued
+    there and before what is queued there later (fgs_push_frame_on and the like), so a tensor
+    the model wrote is ready and one it read may be reused or freed."""
 
     def __init__(self, algo: int, H: int, W: int, params=None, stream=None):
         import torch
@@ -544,7 +618,8 @@ class Model:
         handle = stream.cuda_stream if stream is not None else 0
         self.handle = fgs_create(algo, H, W, params, handle)
         self._mask_ptr = fgs_mask_device_ptr(self.handle)
-        self._ext = None
+        self._order = None
+        self._device = torch.cuda.current_device()
 
     @property
     def mask_ptr(self) -> int:
@@ -552,20 +627,34 @@ class Model:
         by every push in the model's stream order (fgs_mask_device_ptr)."""
         return self._mask_ptr
 
-    def _model_stream(self):
-        if self._ext is None:
-            self._ext = self._torch.cuda.ExternalStream(fgs_stream(self.handle))
-        return self._ext
+    def _stream_order(self):
+        if self._order is None:
+            self._order = StreamOrder(fgs_stream(self.handle))
+        return self._order
 
     def _model_waits_for_torch(self):
-        self._model_stream().wait_stream(self._torch.cuda.current_stream())
+        self._stream_order().enter()
 
     def _torch_waits_for_model(self):
-        self._torch.cuda.current_stream().wait_stream(self._model_stream())
+        self._stream_order().leave()
+
+    def _in_torch_order(self, call, *args):
+        """call(handle, *args, torch's current stream); `args` are addresses and numbers."""
+        stream = self._torch.cuda.current_stream()
+        st = call(self.handle, *args, stream.cuda_stream)
+        if st == FGS_ERR_UNSUPPORTED:         # another device is current than the model's
+            own = self._torch.cuda.ExternalStream(fgs_stream(self.handle), device=self._device)
+            own.wait_stream(stream)
+            with self._torch.cuda.stream(own):
+                st = call(self.handle, *args, own.cuda_stream)
+            stream.wait_stream(own)
+        _check(st)
 
     def close(self):
         if getattr(self, "handle", None):
-            self._ext = None              # wraps the model's stream, destroyed next
+            order, self._order = self._order, None
+            if order is not None:         # its stream is destroyed next
+                order.close()
             fgs_destroy(self.handle)
             self.handle = None
 
@@ -617,15 +706,11 @@ class Model:
         ds = (depth.stride(0) * 2) if not isinstance(depth, np.ndarray) else depth.strides[0]
         dh, dw = int(depth.shape[0]), int(depth.shape[1])
         if wr == FGS_MEM_DEVICE:
-            self._model_waits_for_torch()
-        if (dh, dw) == (self.H, self.W):
-            fgs_push_frame(self.handle, pr, rs, pd, ds, wr)
+            # (no record_stream: later work of the current stream, a reuse of the frames' memory
+            # included, comes after the step)
+            self._in_torch_order(_load().fgs_push_frame_on, pr, rs, pd, ds, dh, dw)
         else:
             fgs_push_frame_scaled(self.handle, pr, rs, pd, ds, dh, dw, wr)
-        if wr == FGS_MEM_DEVICE:
-            # torch's stream may reuse the frames' memory only after the model has read them
-            # (no record_stream: the model's stream can be destroyed before the tensors are)
-            self._torch_waits_for_model()
 
     def mask_host(self) -> np.ndarray:
         out = np.empty((self.H, self.W), np.uint8)
@@ -640,9 +725,7 @@ class Model:
             fgs_eval_accumulate(self.handle, g.ctypes.data, g.strides[0], FGS_MEM_HOST)
         else:
             self._check_plane(gt, "gt")
-            self._model_waits_for_torch()
-            fgs_eval_accumulate(self.handle, gt.data_ptr(), gt.stride(0), FGS_MEM_DEVICE)
-            self._torch_waits_for_model()
+            self._in_torch_order(_load().fgs_eval_accumulate_on, gt.data_ptr(), gt.stride(0))
 
     def static_enable(self, M: int) -> None:
         """Static-object detection: 255 where the mask was foreground in each of the last
@@ -668,9 +751,7 @@ class Model:
     def mask_into(self, out) -> None:
         """Device-to-device copy of the latest mask into a uint8 [H, W] cuda tensor."""
         self._check_plane(out, "out")
-        self._model_waits_for_torch()
-        fgs_get_mask(self.handle, out.data_ptr(), out.stride(0), FGS_MEM_DEVICE)
-        self._torch_waits_for_model()
+        self._in_torch_order(_load().fgs_get_mask_on, out.data_ptr(), out.stride(0))
 
     def state_blob(self) -> np.ndarray:
         n = fgs_state_size(self.handle)
