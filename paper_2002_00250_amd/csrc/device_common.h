@@ -39,6 +39,21 @@ __device__ __forceinline__ uint32_t load_depth(const uint8_t* depth, int64_t str
     return *reinterpret_cast<const uint16_t*>(depth + (int64_t)yd * stride + 2 * xd);
 }
 
+// The serialised state's header: written by the first workgroup's first lanes, or compared.
+__device__ __forceinline__ void write_header(uint32_t* payload, int has, const StateWords& h) {
+    if (has && blockIdx.x == 0 && threadIdx.x < 16) payload[(int)threadIdx.x - 16] = h.w[threadIdx.x];
+}
+__device__ __forceinline__ bool header_matches(const StateCheck& c) {
+    if (!c.header) return true;
+    if (c.seen && blockIdx.x == 0 && threadIdx.x < 16) c.seen[threadIdx.x] = c.header[threadIdx.x];
+    bool ok = true;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ok = ok && c.header[i] == c.want.w[i];
+    ok = ok && c.header[9] == 0u && c.header[8] != 0xFFFFFFFFu;  // 0 <= frames < 2^32 - 1
+    if (!c.any_seed) ok = ok && c.header[10] == c.want.w[10] && c.header[11] == c.want.w[11];
+    return ok;
+}
+
 struct U32x4 {
     uint32_t v[4];
 };

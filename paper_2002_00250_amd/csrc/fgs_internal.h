@@ -10,6 +10,22 @@
 
 namespace fgs {
 
+// ------------------------------------------------- serialised state ----
+// The 64-byte header of a serialised state as words (include/fgs.h): magic, version, algo, H, W,
+// A, B, flags, frames (2), seed (2), reserved (4).
+struct StateWords {
+    uint32_t w[16];
+};
+// An import from device memory reads the header where it lies: every workgroup compares it with
+// `want` and leaves the model as it is unless it matches; the first one copies it to `seen` (pinned
+// host memory), from which the host says what was wrong.  header == nullptr: the host has checked.
+struct StateCheck {
+    const uint32_t* header;
+    uint32_t* seen;
+    StateWords want;
+    int32_t any_seed;  // the seed words are not compared (GMM)
+};
+
 // ------------------------------------------------------------- batches ----
 // Up to kBatchMax models of one kind and class stepped by one launch (their
 // arguments travel by value): workgroup w belongs to model i when
@@ -112,10 +128,11 @@ hipError_t gmm_launch_step(const GmmStepArgs& a, int Kc, int Kd, hipStream_t s);
 hipError_t gmm_launch_step_batch(const GmmStepArgs* a, int n, int Kc, int Kd, hipStream_t s);
 int gmm_batch_key(const GmmStepArgs& a, int Kc, int Kd);
 // canonical planar float32 <-> device layout
+// (header: written to the 64 bytes before `out`; nullptr: not written)
 hipError_t gmm_launch_export(const float4* state, float* out, int Kc, int Kd, int var_mode, int npix,
-                             hipStream_t s);
+                             const StateWords* header, hipStream_t s);
 hipError_t gmm_launch_import(float4* state, const float* in, int Kc, int Kd, int var_mode, int npix,
-                             hipStream_t s);
+                             const StateCheck& check, hipStream_t s);
 
 // --------------------------------------------------------- GMM adjoint ----
 // A window of T frames from a fresh model; checkpoints every E frames.  Frames
@@ -216,12 +233,15 @@ hipError_t pbas_launch_step_batch(const PbasStepArgs* a, int n, hipStream_t s);
 int pbas_batch_key(const PbasStepArgs& a);  // -1: a fill frame (its own launch)
 hipError_t pbas_launch_flush(const PbasPlanes& m, int H, int W, uint32_t t_prev, const PbasConsts& c,
                              hipStream_t s);
-hipError_t pbas_launch_export(const PbasPlanes& m, int npix, int N, uint8_t* out, hipStream_t s);
-hipError_t pbas_launch_import(const PbasPlanes& m, int npix, int N, const uint8_t* in,
+// `pending`: frame t_prev's neighbour writes are applied to what is written out, not to the model.
+hipError_t pbas_launch_export(const PbasPlanes& m, int H, int W, bool pending, uint32_t t_prev, const PbasConsts& c,
+                              uint8_t* out, const StateWords* header, hipStream_t s);
+hipError_t pbas_launch_import(const PbasPlanes& m, int npix, int N, const uint8_t* in, const StateCheck& check,
                               hipStream_t s);
 // Quad planes <-> slot-major planes of the payload.
 hipError_t pbas_launch_export_quads(const uint32_t* quads, int npix, int N, uint8_t* out, hipStream_t s);
-hipError_t pbas_launch_import_quads(uint32_t* quads, int npix, int N, const uint8_t* in, hipStream_t s);
+hipError_t pbas_launch_import_quads(uint32_t* quads, int npix, int N, const uint8_t* in, const StateCheck& check,
+                                    hipStream_t s);
 
 // ------------------------------------------- PBAS, gradient magnitudes ----
 // The gradient-magnitude variant (pbas_grad_kernels.hip): `samples` (bytes R, G, B, depth
@@ -265,9 +285,9 @@ hipError_t pbas_grad_launch_flush(const PbasGradPlanes& m, int H, int W, uint32_
                                   hipStream_t s);
 // Canonical payload (see include/fgs.h) <-> device layout; `t` = frames pushed.
 hipError_t pbas_grad_launch_export(const PbasGradPlanes& m, int npix, int N, int64_t t, uint8_t* out,
-                                   hipStream_t s);
+                                   const StateWords* header, hipStream_t s);
 hipError_t pbas_grad_launch_import(const PbasGradPlanes& m, int npix, int N, int64_t t, const uint8_t* in,
-                                   hipStream_t s);
+                                   const StateCheck& check, hipStream_t s);
 
 // ------------------------------------------------------------ serving ----
 // One entry of a serving batch: the next frame of one stream.  GMM entries are

@@ -55,24 +55,14 @@ __global__ __launch_bounds__(kBlock) void gmm_step_kernel(GmmBatch<NB> b) {
 }
 
 // Run-time Kc, Kd indices of the extra-plane fields (fgs_internal.h).
-__device__ __forceinline__ int x_wc(int Kc, int Kd, int k) { return gmm_x_wc(Kc, Kd, k); }
-__device__ __forceinline__ int x_wd(int Kc, int Kd, int k) { return gmm_x_wd(Kc, Kd, k); }
-__device__ __forceinline__ int x_mud(int Kc, int Kd, int k) { return gmm_x_mud(Kc, Kd, k); }
 __device__ __forceinline__ int x_vd(int Kc, int Kd, int k) { return gmm_x_vd(Kc, Kd, k); }
 __device__ __forceinline__ int x_vg(int Kc, int Kd, int k) { return gmm_x_vg(Kc, Kd, k); }
 __device__ __forceinline__ int x_vb(int Kc, int Kd, int k) { return gmm_x_vb(Kc, Kd, k); }
 
 __device__ __forceinline__ float* f4(float4* s, int64_t i) { return reinterpret_cast<float*>(s + i); }
-__device__ __forceinline__ const float* f4(const float4* s, int64_t i) {
-    return reinterpret_cast<const float*>(s + i);
-}
 __device__ __forceinline__ float* xf(float4* s, int Kc, int64_t n, int64_t p, int idx) {
     return f4(s, (int64_t)(Kc + idx / 4) * n + p) + idx % 4;
 }
-__device__ __forceinline__ float xg(const float4* s, int Kc, int64_t n, int64_t p, int idx) {
-    return f4(s, (int64_t)(Kc + idx / 4) * n + p)[idx % 4];
-}
-
 // Fresh model: w = 0, mu = 0, v = v_init (both mixtures; every colour channel's
 // variance when they are per channel).
 __global__ void gmm_init_kernel(float4* state, int Kc, int Kd, int var_mode, int npix, float v_init_c,
@@ -92,52 +82,67 @@ __global__ void gmm_init_kernel(float4* state, int Kc, int Kd, int var_mode, int
 }
 
 // Canonical order: w_c[Kc], mu_c[Kc][3], v_c[Kc] (per-channel: v_c[Kc][3]), w_d[Kd],
-// mu_d[Kd], v_d[Kd], planes of npix.
-__global__ void gmm_export_kernel(const float4* state, float* out, int Kc, int Kd, int var_mode, int npix) {
+// mu_d[Kd], v_d[Kd], planes of npix.  The plane of float i of the extra planes, -1: padding.
+__device__ __forceinline__ int canon_plane(int i, int Kc, int Kd, int nv) {
+    const int d0 = (4 + nv) * Kc;
+    if (i < Kc) return i;
+    i -= Kc;
+    if (i < Kd) return d0 + i;
+    i -= Kd;
+    if (i < 2 * Kd) return d0 + (1 + (i & 1)) * Kd + (i >> 1);
+    i -= 2 * Kd;
+    return nv == 3 && i < 2 * Kc ? 4 * Kc + 3 * (i >> 1) + 1 + (i & 1) : -1;
+}
+
+// One 16-byte read per plane and pixel, one store per float (and the reverse).
+__global__ __launch_bounds__(kBlock) void gmm_export_kernel(const float4* __restrict__ state, float* __restrict__ out,
+                                                            int Kc, int Kd, int var_mode, int npix, int has_header,
+                                                            StateWords header) {
+    write_header(reinterpret_cast<uint32_t*>(out), has_header, header);
     const int p = blockIdx.x * kBlock + threadIdx.x;
     if (p >= npix) return;
     const int64_t n = npix;
-    const int nv = var_mode ? 3 : 1;
+    const int nv = var_mode ? 3 : 1, E = gmm_extra_planes(Kc, Kd, var_mode);
+#pragma unroll 4
     for (int k = 0; k < Kc; ++k) {
-        const float* c = f4(state, (int64_t)k * n + p);
-        out[(int64_t)k * n + p] = xg(state, Kc, n, p, x_wc(Kc, Kd, k));
-        for (int ch = 0; ch < 3; ++ch) out[(int64_t)(Kc + 3 * k + ch) * n + p] = c[ch];
-        out[(int64_t)(4 * Kc + nv * k) * n + p] = c[3];
-        if (var_mode) {
-            out[(int64_t)(4 * Kc + nv * k + 1) * n + p] = xg(state, Kc, n, p, x_vg(Kc, Kd, k));
-            out[(int64_t)(4 * Kc + nv * k + 2) * n + p] = xg(state, Kc, n, p, x_vb(Kc, Kd, k));
-        }
+        const float4 c = state[(int64_t)k * n + p];
+        out[(int64_t)(Kc + 3 * k) * n + p] = c.x;
+        out[(int64_t)(Kc + 3 * k + 1) * n + p] = c.y;
+        out[(int64_t)(Kc + 3 * k + 2) * n + p] = c.z;
+        out[(int64_t)(4 * Kc + nv * k) * n + p] = c.w;
     }
-    const int d0 = (4 + nv) * Kc;
-    for (int k = 0; k < Kd; ++k) {
-        out[(int64_t)(d0 + k) * n + p] = xg(state, Kc, n, p, x_wd(Kc, Kd, k));
-        out[(int64_t)(d0 + Kd + k) * n + p] = xg(state, Kc, n, p, x_mud(Kc, Kd, k));
-        out[(int64_t)(d0 + 2 * Kd + k) * n + p] = xg(state, Kc, n, p, x_vd(Kc, Kd, k));
+#pragma unroll 4
+    for (int e = 0; e < E; ++e) {
+        const float4 x = state[(int64_t)(Kc + e) * n + p];
+        const float v[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int plane = canon_plane(4 * e + i, Kc, Kd, nv);
+            if (plane >= 0) out[(int64_t)plane * n + p] = v[i];
+        }
     }
 }
 
-__global__ void gmm_import_kernel(float4* state, const float* in, int Kc, int Kd, int var_mode, int npix) {
+__global__ __launch_bounds__(kBlock) void gmm_import_kernel(float4* __restrict__ state, const float* __restrict__ in,
+                                                            int Kc, int Kd, int var_mode, int npix, StateCheck check) {
+    if (!header_matches(check)) return;
     const int p = blockIdx.x * kBlock + threadIdx.x;
     if (p >= npix) return;
     const int64_t n = npix;
-    const int E = gmm_extra_planes(Kc, Kd, var_mode);
-    const int nv = var_mode ? 3 : 1;
-    for (int e = 0; e < E; ++e) state[(int64_t)(Kc + e) * n + p] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int k = 0; k < Kc; ++k) {
-        float* c = f4(state, (int64_t)k * n + p);
-        for (int ch = 0; ch < 3; ++ch) c[ch] = in[(int64_t)(Kc + 3 * k + ch) * n + p];
-        c[3] = in[(int64_t)(4 * Kc + nv * k) * n + p];
-        *xf(state, Kc, n, p, x_wc(Kc, Kd, k)) = in[(int64_t)k * n + p];
-        if (var_mode) {
-            *xf(state, Kc, n, p, x_vg(Kc, Kd, k)) = in[(int64_t)(4 * Kc + nv * k + 1) * n + p];
-            *xf(state, Kc, n, p, x_vb(Kc, Kd, k)) = in[(int64_t)(4 * Kc + nv * k + 2) * n + p];
+    const int nv = var_mode ? 3 : 1, E = gmm_extra_planes(Kc, Kd, var_mode);
+#pragma unroll 4
+    for (int k = 0; k < Kc; ++k)
+        state[(int64_t)k * n + p] = make_float4(in[(int64_t)(Kc + 3 * k) * n + p], in[(int64_t)(Kc + 3 * k + 1) * n + p],
+                                                in[(int64_t)(Kc + 3 * k + 2) * n + p], in[(int64_t)(4 * Kc + nv * k) * n + p]);
+#pragma unroll 4
+    for (int e = 0; e < E; ++e) {
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int plane = canon_plane(4 * e + i, Kc, Kd, nv);
+            v[i] = plane >= 0 ? in[(int64_t)plane * n + p] : 0.0f;
         }
-    }
-    const int d0 = (4 + nv) * Kc;
-    for (int k = 0; k < Kd; ++k) {
-        *xf(state, Kc, n, p, x_wd(Kc, Kd, k)) = in[(int64_t)(d0 + k) * n + p];
-        *xf(state, Kc, n, p, x_mud(Kc, Kd, k)) = in[(int64_t)(d0 + Kd + k) * n + p];
-        *xf(state, Kc, n, p, x_vd(Kc, Kd, k)) = in[(int64_t)(d0 + 2 * Kd + k) * n + p];
+        state[(int64_t)(Kc + e) * n + p] = make_float4(v[0], v[1], v[2], v[3]);
     }
 }
 
@@ -223,16 +228,17 @@ hipError_t gmm_launch_init(float4* state, int Kc, int Kd, int npix, const GmmCon
 }
 
 hipError_t gmm_launch_export(const float4* state, float* out, int Kc, int Kd, int var_mode, int npix,
-                             hipStream_t s) {
+                             const StateWords* header, hipStream_t s) {
     const unsigned grid = (unsigned)((npix + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(gmm_export_kernel, dim3(grid), dim3(kBlock), 0, s, state, out, Kc, Kd, var_mode, npix);
+    hipLaunchKernelGGL(gmm_export_kernel, dim3(grid), dim3(kBlock), 0, s, state, out, Kc, Kd, var_mode, npix,
+                       header ? 1 : 0, header ? *header : StateWords());
     return hipGetLastError();
 }
 
 hipError_t gmm_launch_import(float4* state, const float* in, int Kc, int Kd, int var_mode, int npix,
-                             hipStream_t s) {
+                             const StateCheck& check, hipStream_t s) {
     const unsigned grid = (unsigned)((npix + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(gmm_import_kernel, dim3(grid), dim3(kBlock), 0, s, state, in, Kc, Kd, var_mode, npix);
+    hipLaunchKernelGGL(gmm_import_kernel, dim3(grid), dim3(kBlock), 0, s, state, in, Kc, Kd, var_mode, npix, check);
     return hipGetLastError();
 }
 

@@ -38,6 +38,8 @@ struct fgs_model {
     // pinned bytes a host mask read goes through (allocated on the first one)
     uint8_t* mask_stage;
     size_t mask_stage_bytes;
+    bool fields_seen;  // in-place addresses were handed out: a state copy settles the model itself
+    uint32_t* header_seen;  // pinned: the header an import read in device memory
     // evaluation (allocated on the first fgs_eval_accumulate)
     unsigned long long* eval_acc;  // device: TP, TN, FP, FN, kEvalSlots partial sums each
     uint8_t* gt_stage;             // pinned host copy of a host ground truth

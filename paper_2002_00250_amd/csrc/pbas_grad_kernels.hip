@@ -409,7 +409,9 @@ __global__ void pbas_grad_init_kernel(PbasGradPlanes m, int npix, float4 Rl, flo
 }
 
 // Canonical planes: D [N][4] float32, R, T, S [4] float32 <-> float4 per pixel.
-__global__ void pbas_grad_export_kernel(PbasGradPlanes m, int npix, int N, float* dout, float* rts) {
+__global__ void pbas_grad_export_kernel(PbasGradPlanes m, int npix, int N, float* dout, float* rts, uint32_t* out,
+                                        int has_header, StateWords header) {
+    write_header(out, has_header, header);
     const int p = blockIdx.x * 256 + threadIdx.x;
     if (p >= npix) return;
     const int64_t n = npix;
@@ -425,7 +427,9 @@ __global__ void pbas_grad_export_kernel(PbasGradPlanes m, int npix, int N, float
     for (int i = 0; i < 12; ++i) rts[i * n + p] = v[i];
 }
 
-__global__ void pbas_grad_import_kernel(PbasGradPlanes m, int npix, int N, const float* din, const float* rts) {
+__global__ void pbas_grad_import_kernel(PbasGradPlanes m, int npix, int N, const float* din, const float* rts,
+                                        StateCheck check) {
+    if (!header_matches(check)) return;
     const int p = blockIdx.x * 256 + threadIdx.x;
     if (p >= npix) return;
     const int64_t n = npix;
@@ -439,7 +443,11 @@ __global__ void pbas_grad_import_kernel(PbasGradPlanes m, int npix, int N, const
 
 // The last pushed frame's sums <-> slot (t - 1) mod 3; the other two slots cleared.
 // The payload's sums are moved as 32-bit halves (a caller's buffer is 4-byte aligned).
-__global__ void pbas_grad_sums_kernel(unsigned long long* gsum, uint32_t* canon, int64_t t, int to_canon) {
+// (An import whose header lies in device memory takes the frame count from there.)
+__global__ void pbas_grad_sums_kernel(unsigned long long* gsum, uint32_t* canon, int64_t t, int to_canon,
+                                      StateCheck check) {
+    if (!header_matches(check)) return;
+    if (check.header) t = (int64_t)check.header[8];
     const int j = threadIdx.x;  // 0..2
     const int prev = (int)((t + 2) % 3);
     if (to_canon) {
@@ -495,34 +503,35 @@ hipError_t pbas_grad_launch_flush(const PbasGradPlanes& m, int H, int W, uint32_
 }
 
 hipError_t pbas_grad_launch_export(const PbasGradPlanes& m, int npix, int N, int64_t t, uint8_t* out,
-                                   hipStream_t s) {
+                                   const StateWords* header, hipStream_t s) {
     const size_t plane = (size_t)npix * 4;
     hipError_t e = pbas_launch_export_quads(m.samples, npix, N, out, s);
     if (e == hipSuccess) e = pbas_launch_export_quads(m.gsamples, npix, N, out + plane * N, s);
     if (e != hipSuccess) return e;
     float* dout = reinterpret_cast<float*>(out + 2 * plane * N);
     float* rts = reinterpret_cast<float*>(out + 6 * plane * N);
-    hipLaunchKernelGGL(pbas_grad_export_kernel, dim3(blocks1d(npix)), dim3(256), 0, s, m, npix, N, dout, rts);
+    hipLaunchKernelGGL(pbas_grad_export_kernel, dim3(blocks1d(npix)), dim3(256), 0, s, m, npix, N, dout, rts,
+                       reinterpret_cast<uint32_t*>(out), header ? 1 : 0, header ? *header : StateWords());
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     uint32_t* canon = reinterpret_cast<uint32_t*>(out + 6 * plane * N + 12 * plane);
-    hipLaunchKernelGGL(pbas_grad_sums_kernel, dim3(1), dim3(3), 0, s, m.gsum, canon, t, 1);
+    hipLaunchKernelGGL(pbas_grad_sums_kernel, dim3(1), dim3(3), 0, s, m.gsum, canon, t, 1, StateCheck());
     return hipGetLastError();
 }
 
 hipError_t pbas_grad_launch_import(const PbasGradPlanes& m, int npix, int N, int64_t t, const uint8_t* in,
-                                   hipStream_t s) {
+                                   const StateCheck& check, hipStream_t s) {
     const size_t plane = (size_t)npix * 4;
-    hipError_t e = pbas_launch_import_quads(m.samples, npix, N, in, s);
-    if (e == hipSuccess) e = pbas_launch_import_quads(m.gsamples, npix, N, in + plane * N, s);
+    hipError_t e = pbas_launch_import_quads(m.samples, npix, N, in, check, s);
+    if (e == hipSuccess) e = pbas_launch_import_quads(m.gsamples, npix, N, in + plane * N, check, s);
     if (e != hipSuccess) return e;
     const float* din = reinterpret_cast<const float*>(in + 2 * plane * N);
     const float* rts = reinterpret_cast<const float*>(in + 6 * plane * N);
-    hipLaunchKernelGGL(pbas_grad_import_kernel, dim3(blocks1d(npix)), dim3(256), 0, s, m, npix, N, din, rts);
+    hipLaunchKernelGGL(pbas_grad_import_kernel, dim3(blocks1d(npix)), dim3(256), 0, s, m, npix, N, din, rts, check);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     uint32_t* canon = const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(in + 6 * plane * N + 12 * plane));
-    hipLaunchKernelGGL(pbas_grad_sums_kernel, dim3(1), dim3(3), 0, s, m.gsum, canon, t, 0);
+    hipLaunchKernelGGL(pbas_grad_sums_kernel, dim3(1), dim3(3), 0, s, m.gsum, canon, t, 0, check);
     return hipGetLastError();
 }
 

@@ -705,6 +705,12 @@ fgs_status fgs_create(fgs_algo algo, int32_t H, int32_t W, const void* params, v
         delete m;
         return fail(FGS_ERR_DEVICE, "model initialisation: %s", hipGetErrorString(e));
     }
+    // (made here: an allocation during fgs_set_state would break another thread's stream capture;
+    // without it a device header is copied to the host first)
+    if (hipHostMalloc((void**)&m->header_seen, kHeaderBytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        m->header_seen = nullptr;
+    }
     m->at = m->stream;
     m->stream_seen = !m->own_stream;
     m->cache_policy = FGS_CACHE_AUTO;
@@ -728,6 +734,7 @@ fgs_status fgs_destroy(fgs_model* m) {
         (void)hipHostFree(m->gt_stage);
     }
     if (m->mask_stage) (void)hipHostFree(m->mask_stage);
+    if (m->header_seen) (void)hipHostFree(m->header_seen);
     if (m->host_stage) {
         (void)hipEventDestroy(m->stage_done);
         (void)hipHostFree(m->host_stage);
@@ -1126,8 +1133,9 @@ fgs_status copy_state_impl(fgs_model* m, void* dst, size_t bytes, fgs_mem where,
     if (where == FGS_MEM_DEVICE && ((uintptr_t)dst & 3))
         return fail(FGS_ERR_INVALID_ARG, "device state buffer must be 4-byte aligned");
     FGS_TRY(run_on(m, m->stream));
-    fgs_status st = flush_pending(m);
-    if (st != FGS_OK) return st;
+    // The plain PBAS export applies the pending writes to what it writes and leaves them pending,
+    // unless someone may look at the model in place.
+    if (m->algo == FGS_PBAS && (m->pp.gradient || m->fields_seen)) FGS_TRY(flush_pending(m));
 
     StateHeader h;
     std::memset(&h, 0, sizeof h);
@@ -1152,19 +1160,20 @@ fgs_status copy_state_impl(fgs_model* m, void* dst, size_t bytes, fgs_mem where,
             target = tmp;
         }
     }
+    StateWords words;
+    std::memcpy(&words, &h, sizeof words);
+    const StateWords* header = where == FGS_MEM_DEVICE ? &words : nullptr;
     hipError_t e = m->algo == FGS_GMM
                        ? gmm_launch_export(m->gmm_state, reinterpret_cast<float*>(target), m->gp.Kc,
-                                           m->gp.Kd, m->gp.var_mode, m->npix, m->stream)
-                       : m->pp.gradient ? pbas_grad_launch_export(m->pg, m->npix, m->pp.N, m->t, target, m->stream)
-                                        : pbas_launch_export(m->pb, m->npix, m->pp.N, target, m->stream);
-    if (e == hipSuccess) {
-        if (where == FGS_MEM_HOST) {
-            std::memcpy(dst, &h, sizeof h);
-            e = hipMemcpyAsync(reinterpret_cast<uint8_t*>(dst) + kHeaderBytes, target, payload,
-                               hipMemcpyDeviceToHost, m->stream);
-        } else {
-            e = hipMemcpyAsync(dst, &h, sizeof h, hipMemcpyHostToDevice, m->stream);
-        }
+                                           m->gp.Kd, m->gp.var_mode, m->npix, header, m->stream)
+                       : m->pp.gradient
+                             ? pbas_grad_launch_export(m->pg, m->npix, m->pp.N, m->t, target, header, m->stream)
+                             : pbas_launch_export(m->pb, m->H, m->W, m->pending, (uint32_t)(m->t - 1), m->pc, target,
+                                                  header, m->stream);
+    if (e == hipSuccess && where == FGS_MEM_HOST) {
+        std::memcpy(dst, &h, sizeof h);
+        e = hipMemcpyAsync(reinterpret_cast<uint8_t*>(dst) + kHeaderBytes, target, payload, hipMemcpyDeviceToHost,
+                           m->stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
     if (tmp) (void)hipFree(tmp);
@@ -1207,21 +1216,48 @@ fgs_status fgs_set_state(fgs_model* m, const void* src, size_t bytes, fgs_mem wh
     if (where == FGS_MEM_DEVICE && ((uintptr_t)src & 3))
         return fail(FGS_ERR_INVALID_ARG, "device state blob must be 4-byte aligned");
     FGS_TRY(run_on(m, m->stream));
+    const int A = m->algo == FGS_GMM ? m->gp.Kc : m->pp.N;
+    const int B = m->algo == FGS_GMM ? m->gp.Kd : 0;
+    const int flags = m->algo == FGS_GMM ? m->gp.var_mode : (m->pp.gradient ? 2 : 0);
     StateHeader h;
-    if (where == FGS_MEM_HOST) {
+    auto checked = [&]() -> fgs_status {
+        if (h.magic != kStateMagic || h.version != kStateVersion || h.algo != (uint32_t)m->algo || h.H != m->H ||
+            h.W != m->W || h.A != A || h.B != B || h.frames < 0 || h.frames >= 0xFFFFFFFFll || h.flags != flags)
+            return fail(FGS_ERR_INVALID_ARG, "state header does not match this model");
+        if (m->algo == FGS_PBAS && h.seed != m->pp.seed)
+            return fail(FGS_ERR_INVALID_ARG, "state was taken with another PBAS seed");
+        return FGS_OK;
+    };
+    // A header in device memory is compared there by the import itself, which leaves the model as
+    // it is if it does not match, and read by the host afterwards: no wait before the import.
+    StateCheck check;
+    std::memset(&check, 0, sizeof check);
+    const bool later = where == FGS_MEM_DEVICE && m->header_seen &&
+                       kernel_may_write(const_cast<void*>(src), bytes, m->device);
+    if (later) {
+        StateHeader want;
+        std::memset(&want, 0, sizeof want);
+        want.magic = kStateMagic;
+        want.version = kStateVersion;
+        want.algo = (uint32_t)m->algo;
+        want.H = m->H;
+        want.W = m->W;
+        want.A = A;
+        want.B = B;
+        want.flags = flags;
+        want.seed = m->algo == FGS_PBAS ? m->pp.seed : 0;
+        check.header = reinterpret_cast<const uint32_t*>(src);
+        check.seen = m->header_seen;
+        std::memcpy(&check.want, &want, sizeof check.want);
+        check.any_seed = m->algo == FGS_GMM ? 1 : 0;
+        std::memset(&h, 0, sizeof h);
+    } else if (where == FGS_MEM_HOST) {
         std::memcpy(&h, src, sizeof h);
     } else {
         FGS_HIP(m, hipMemcpyAsync(&h, src, sizeof h, hipMemcpyDeviceToHost, m->stream));
         FGS_HIP(m, hipStreamSynchronize(m->stream));
     }
-    const int A = m->algo == FGS_GMM ? m->gp.Kc : m->pp.N;
-    const int B = m->algo == FGS_GMM ? m->gp.Kd : 0;
-    if (h.magic != kStateMagic || h.version != kStateVersion || h.algo != (uint32_t)m->algo ||
-        h.H != m->H || h.W != m->W || h.A != A || h.B != B || h.frames < 0 || h.frames >= 0xFFFFFFFFll ||
-        h.flags != (m->algo == FGS_GMM ? m->gp.var_mode : (m->pp.gradient ? 2 : 0)))
-        return fail(FGS_ERR_INVALID_ARG, "state header does not match this model");
-    if (m->algo == FGS_PBAS && h.seed != m->pp.seed)
-        return fail(FGS_ERR_INVALID_ARG, "state was taken with another PBAS seed");
+    if (!later) FGS_TRY(checked());
 
     uint8_t* tmp = nullptr;
     const uint8_t* srcp = reinterpret_cast<const uint8_t*>(src) + kHeaderBytes;
@@ -1232,12 +1268,16 @@ fgs_status fgs_set_state(fgs_model* m, const void* src, size_t bytes, fgs_mem wh
         srcp = tmp;
     }
     if (e == hipSuccess)
-        e = m->algo == FGS_GMM ? gmm_launch_import(m->gmm_state, reinterpret_cast<const float*>(srcp),
-                                                   m->gp.Kc, m->gp.Kd, m->gp.var_mode, m->npix, m->stream)
-                               : m->pp.gradient
-                                     ? pbas_grad_launch_import(m->pg, m->npix, m->pp.N, h.frames, srcp, m->stream)
-                                     : pbas_launch_import(m->pb, m->npix, m->pp.N, srcp, m->stream);
+        e = m->algo == FGS_GMM
+                ? gmm_launch_import(m->gmm_state, reinterpret_cast<const float*>(srcp), m->gp.Kc, m->gp.Kd,
+                                    m->gp.var_mode, m->npix, check, m->stream)
+                : m->pp.gradient ? pbas_grad_launch_import(m->pg, m->npix, m->pp.N, h.frames, srcp, check, m->stream)
+                                 : pbas_launch_import(m->pb, m->npix, m->pp.N, srcp, check, m->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
+    if (e == hipSuccess && later) {
+        std::memcpy(&h, m->header_seen, sizeof h);
+        FGS_TRY(checked());
+    }
     if (tmp) (void)hipFree(tmp);
     if (e != hipSuccess) return device_fail(m, e, "set_state");
     m->t = h.frames;
@@ -1314,6 +1354,7 @@ fgs_status fgs_get_state(fgs_model* m, fgs_state_field* fields, int32_t capacity
     FGS_TRY(run_on(m, m->stream));
     fgs_status s = flush_pending(m);
     if (s != FGS_OK) return s;
+    m->fields_seen = true;
     std::copy(f.begin(), f.end(), fields);
     return FGS_OK;
 }
