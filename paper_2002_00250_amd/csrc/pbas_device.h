@@ -203,8 +203,8 @@ __device__ __forceinline__ void scatter_fired(PbasLds<NMAX>& sh, const FireIn& f
 // Classification runs two channels per 32-bit word (16-bit lanes: R|B and G|D).
 // The depth lane holds code - 1, so an empty depth slot (code 0) becomes 0xFFFF,
 // whose distance to any valid code is above every threshold and every d_min.
-template <int NMAX, int NLO, bool NT>
-__device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by, PbasLds<NMAX>& sh) {
+template <int NMAX, int NLO, bool NT, bool TWO>
+__device__ __forceinline__ void pbas_tile_m(const PbasStepArgs& a, int bx, int by, PbasLds<NMAX>& sh) {
     static_assert(NLO >= 1 && NLO <= NMAX, "bad register capacity class");
     constexpr int NW = PbasLds<NMAX>::NW;
     const int tid = threadIdx.x;
@@ -327,7 +327,7 @@ __device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by,
     const u16x2 one5 = {15, 15};
     const u16x2 dep1 = {0, 1};
     u16x2 cnt_rb = {0, 0}, cnt_gd = {0, 0};
-    u16x2 dmn_rb = {255, 255}, dmn_gd = {255, 255};
+    u16x2 dmn_rb = {0xFFFF, 0xFFFF}, dmn_gd = {0xFFFF, 0xFFFF};  // (used where min_matches >= 1 matched: < 256)
 
     // Frame t-1's neighbour writes into this pixel come first: slot k of channel j
     // takes this pixel's previous value where its bit is set.
@@ -342,6 +342,13 @@ __device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by,
     uint32_t dirty = 0u, chg = 0u;
     uint32_t byte_ids;  // an opaque register, so the constant is not rematerialised per merge
     asm("v_mov_b32 %0, 0x03020100" : "=v"(byte_ids));
+    // TWO (min_matches = 2, the paper's #min): a channel matches iff its second smallest
+    // distance is below the threshold, so the two smallest are kept: 3 packed instructions
+    // for a pair of channels and slot, where a count next to the smallest takes 4, and 5 with
+    // the depth lane's cap.  128 fewer VALU instructions of 2,065 at N = 35, the registers the
+    // same.  640x480, N = 20: 20.3 -> 19.6 us a launch, N = 48: 37.6 -> 37.0; 1280x720, N = 35:
+    // 72.1 -> 71.7; four of those, bound by HBM, 334.8 -> 334.2.
+    u16x2 sec_rb = {0xFFFF, 0xFFFF}, sec_gd = {0xFFFF, 0xFFFF};
 #pragma unroll
     for (int k = 0; k < NMAX; ++k) {
         // Keep the per-slot work next to its sample: without the fence the scheduler
@@ -363,21 +370,27 @@ __device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by,
             const u16x2 s_gd = h2(__builtin_amdgcn_perm(0u, s, 0x0C030C01u)) - dep1;
             const u16x2 d_rb = __builtin_elementwise_max(s_rb, I_rb) - __builtin_elementwise_min(s_rb, I_rb);
             const u16x2 d_gd = __builtin_elementwise_max(s_gd, I_gd) - __builtin_elementwise_min(s_gd, I_gd);
+            if (TWO) {
+                sec_rb = __builtin_elementwise_min(sec_rb, __builtin_elementwise_max(dmn_rb, d_rb));
+                sec_gd = __builtin_elementwise_min(sec_gd, __builtin_elementwise_max(dmn_gd, d_gd));
+            } else {
+                // (min(d, 512) - lim) is negative, bit 15 set, iff d < lim
+                cnt_rb = cnt_rb + ((d_rb - L_rb) >> one5);
+                cnt_gd = cnt_gd + ((__builtin_elementwise_min(d_gd, cap) - L_gd) >> one5);
+            }
             dmn_rb = __builtin_elementwise_min(dmn_rb, d_rb);
             dmn_gd = __builtin_elementwise_min(dmn_gd, d_gd);
-            // (min(d, 512) - lim) is negative, bit 15 set, iff d < lim
-            cnt_rb = cnt_rb + ((d_rb - L_rb) >> one5);
-            cnt_gd = cnt_gd + ((__builtin_elementwise_min(d_gd, cap) - L_gd) >> one5);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
     const int cnt[4] = {cnt_rb.x, cnt_gd.x, cnt_rb.y, cnt_gd.y};
     const int dmn[4] = {dmn_rb.x, dmn_gd.x, dmn_rb.y, dmn_gd.y};
+    const uint32_t sec[4] = {sec_rb.x, sec_gd.x, sec_rb.y, sec_gd.y};
     bool F[4], upd[4];
     bool fg = false;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        F[j] = active[j] && cnt[j] < a.c.min_matches;
+        F[j] = active[j] && !(TWO ? sec[j] < lim[j] : cnt[j] >= a.c.min_matches);
         fg = fg || F[j];
         upd[j] = cand[j] && !F[j];
     }
@@ -493,6 +506,16 @@ __device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by,
 #pragma unroll
     for (int j = 0; j < 4; ++j) rfl |= (__float_as_uint(R[j]) == __float_as_uint(a.c.R_lower[j]) ? 1u : 0u) << j;
     a.m.fire[a.t & 1u][p] = (uint8_t)(fire | (rfl << 4));
+}
+
+// The tile with the classification of the model's min_matches (a branch per workgroup around the
+// whole frame: around the slot loop alone it took 148 VGPRs instead of 95 at N = 35).
+template <int NMAX, int NLO, bool NT>
+__device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by, PbasLds<NMAX>& sh) {
+    if (a.c.min_matches == 2)
+        pbas_tile_m<NMAX, NLO, NT, true>(a, bx, by, sh);
+    else
+        pbas_tile_m<NMAX, NLO, NT, false>(a, bx, by, sh);
 }
 
 // Frames 0..N-1: sample slot t takes the frame; the mask is empty.
