@@ -57,6 +57,7 @@ constexpr float kTiny = 1.0e-35f;
 
 __device__ __forceinline__ bool any_lane(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0; }
 __device__ __forceinline__ uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
+__device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
 // What the classification of one mixture finds.
 struct MixClass {
@@ -66,7 +67,21 @@ struct MixClass {
     int ks;       // the matched rank, -1: none
     bool sure;    // the approximate choices are certain to be the rounded ones', and every
                   // weight, variance and distance is in [0, kBig)
+    float d2, v;  // classify_approx with ARG: delta's squared distance and variance
 };
+
+// Squared distance of X to Gaussian k.
+template <int K, int C, int CV>
+__device__ __forceinline__ float dist2(const Mix<K, C, CV>& m, const float (&X)[C], int k) {
+    float e = X[0] - m.mu[k][0];
+    float d2 = e * e;
+#pragma unroll
+    for (int c = 1; c < C; ++c) {
+        e = X[c] - m.mu[k][c];
+        d2 = d2 + e * e;
+    }
+    return d2;
+}
 
 // Squared distance of X to Gaussian k over its variance, correctly rounded step by step.
 template <int K, int C, int CV>
@@ -80,21 +95,15 @@ __device__ __forceinline__ float q_rounded(const Mix<K, C, CV>& m, const float (
         acc = acc + (e * e) / m.vx[k][1];
         return acc;
     } else {
-        float e = X[0] - m.mu[k][0];
-        float d2 = e * e;
-#pragma unroll
-        for (int c = 1; c < C; ++c) {
-            e = X[c] - m.mu[k][c];
-            d2 = d2 + e * e;
-        }
-        return d2 / m.v[k];
+        return dist2(m, X, k) / m.v[k];
     }
 }
 
-// The same with approximate reciprocals.
+// The same with approximate reciprocals; d2 (CV = 1): the squared distance.
 template <int K, int C, int CV>
-__device__ __forceinline__ float q_approx(const Mix<K, C, CV>& m, const float (&X)[C], int k) {
+__device__ __forceinline__ float q_approx(const Mix<K, C, CV>& m, const float (&X)[C], int k, float& d2) {
     if constexpr (CV == 3) {
+        d2 = 0.0f;
         float e = X[0] - m.mu[k][0];
         float acc = (e * e) * __builtin_amdgcn_rcpf(m.v[k]);
         e = X[1] - m.mu[k][1];
@@ -102,13 +111,7 @@ __device__ __forceinline__ float q_approx(const Mix<K, C, CV>& m, const float (&
         e = X[2] - m.mu[k][2];
         return acc + (e * e) * __builtin_amdgcn_rcpf(m.vx[k][1]);
     } else {
-        float e = X[0] - m.mu[k][0];
-        float d2 = e * e;
-#pragma unroll
-        for (int c = 1; c < C; ++c) {
-            e = X[c] - m.mu[k][c];
-            d2 = d2 + e * e;
-        }
+        d2 = dist2(m, X, k);
         return d2 * __builtin_amdgcn_rcpf(m.v[k]);
     }
 }
@@ -172,12 +175,12 @@ __device__ __forceinline__ MixClass classify_rounded(const Mix<K, C, CV>& m, con
 // attaining delta counts as a choice too (its runner-up must be clearly above it).
 template <int K, int C, int CV, bool ARG>
 __device__ __forceinline__ MixClass classify_approx(const Mix<K, C, CV>& m, const float (&X)[C], float lam2, float T_bg) {
-    float q[K];
+    float q[K], d2[K];
     uint32_t top = 0u;  // the largest bit pattern: at or above kBig's for a sign, an infinity or a NaN
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        q[k] = q_approx(m, X, k);
+        q[k] = q_approx(m, X, k, d2[k]);
         ok = ok && fabsf(q[k] - lam2) > kMargin * lam2;
         top = umax(top, umax(__float_as_uint(q[k]), __float_as_uint(m.v[k])));
         top = umax(top, __float_as_uint(m.w[k]));
@@ -188,9 +191,47 @@ __device__ __forceinline__ MixClass classify_approx(const Mix<K, C, CV>& m, cons
     MixClass r;
     r.used = m.w[0] > 0.0f;
     const float next = choose(r, m, q, bg, lam2);
+    if constexpr (ARG) {
+        r.d2 = d2[0];
+        r.v = m.v[0];
+#pragma unroll
+        for (int k = 1; k < K; ++k) {
+            r.d2 = k == r.amin ? d2[k] : r.d2;
+            r.v = k == r.amin ? m.v[k] : r.v;
+        }
+    }
     if constexpr (ARG && K > 1) ok = ok && next > __builtin_fmaf(kMargin, r.delta, r.delta) + kTiny;
     r.sure = ok && top < __float_as_uint(kBig);
     return r;
+}
+
+// w[k] / S, correctly rounded, S the sum of the w.  Where no lane holds a value outside
+// [2^-60, 2^60] but zero weights, the quotients share one reciprocal (Markstein's method: the
+// hardware's refined once, then each product corrected by its fused remainder: 3 instructions a
+// quotient instead of a division's 11 and its own reciprocal); no step there rounds in the
+// subnormal range or overflows.  Compared with the division over all 2^46 pairs of significands
+// on gfx950: no quotient differs (without the refinement 47,045 do).  With the ranking on
+// products below, the window's forward at 640x480, K = 3, 64 frames, bound by its instructions:
+// 270 -> 251 us; the per-frame steps, bound by memory, within 1 % (K = 5 at 640x480 14.56 -> 14.40).
+template <int K>
+__device__ __forceinline__ void normalise(float (&w)[K], float S, bool plain) {
+    constexpr uint32_t kLow = 67u << 23, kHigh = 187u << 23;  // 2^-60, 2^60
+    uint32_t low = 0xFFFFFFFFu;  // the least nonzero pattern, less one
+#pragma unroll
+    for (int k = 0; k < K; ++k) low = umin(low, __float_as_uint(w[k]) - 1u);
+    const bool safe = low >= kLow - 1u && __float_as_uint(S) - kLow <= kHigh - kLow;
+    if (plain && !any_lane(!safe)) {
+        const float r0 = __builtin_amdgcn_rcpf(S);
+        const float r = __builtin_fmaf(__builtin_fmaf(-S, r0, 1.0f), r0, r0);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const float q = w[k] * r;
+            w[k] = __builtin_fmaf(__builtin_fmaf(-S, q, w[k]), r, q);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < K; ++k) w[k] = w[k] / S;
+    }
 }
 
 // Update of the mixture after its classification found the match ks: weights, the matched
@@ -313,12 +354,11 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
     float S = m.w[0];
 #pragma unroll
     for (int k = 1; k < K; ++k) S = S + m.w[k];
-#pragma unroll
-    for (int k = 0; k < K; ++k) m.w[k] = m.w[k] / S;
+    normalise(m.w, S, plain);
 
     // Rank by w / sqrt(v), descending, stable.  In a static scene the order rarely changes, so
-    // first look whether every adjacent pair is certain to be in order: clearly apart on
-    // approximate keys, or the lower one unused (w = 0, key 0).  Only a
+    // first look whether every adjacent pair is certain to be in order: the squared keys'
+    // products clearly apart, or the lower one unused (w = 0, key 0).  Only a
     // wavefront with a pair that is not computes the rounded keys, and the insertion network
     // of adjacent compare-exchanges (strictly-greater swaps only, so equal keys keep their
     // order) runs only if one of those is out of order.
@@ -327,16 +367,15 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
     for (int k = 0; k < K; ++k) pr |= (uint32_t)k << (3 * k);
     uint32_t at = 1u << tgt;       // the ranks where the changed Gaussian is now
     bool inorder = plain;
-    {
-        float above = m.w[0] * __builtin_amdgcn_rsqf(var_sum(m, 0));
 #pragma unroll
-        for (int k = 1; k < K; ++k) {
-            const float ka = m.w[k] * __builtin_amdgcn_rsqf(var_sum(m, k));
-            // (keys below kTiny, where rounding is no longer relative, are not apart)
-            const bool apart = __builtin_fmaf(above, 1.0f - kMargin, -kTiny) > ka;
-            inorder = inorder && (apart || m.w[k] == 0.0f);
-            above = ka;
-        }
+    for (int k = 1; k < K; ++k) {
+        // key above > key below as w^2 times the other's variance (weights are at most 1 here, so
+        // that the first product holds all the precision the second can show); products below
+        // kTiny, where rounding is no longer relative, are not apart
+        const float above = (m.w[k - 1] * var_sum(m, k)) * m.w[k - 1];
+        const float below = (m.w[k] * var_sum(m, k - 1)) * m.w[k];
+        const bool apart = __builtin_fmaf(above, 1.0f - 2.0f * kMargin, -kTiny) > below;
+        inorder = inorder && (apart || m.w[k] == 0.0f);
     }
     if (K > 1 && any_lane(!inorder)) {
         float key[K];
@@ -404,18 +443,7 @@ __device__ __forceinline__ void mixture_step_rec(Mix<K, C>& m, const float (&X)[
     if (!plain) {
         r = classify_rounded(m, X, lam2, T_bg);
     } else {
-        Mix<1, C> s;  // the Gaussian attaining delta: one rounded division instead of K
-#pragma unroll
-        for (int c = 0; c < C; ++c) s.mu[0][c] = m.mu[0][c];
-        s.v[0] = m.v[0];
-#pragma unroll
-        for (int k = 1; k < K; ++k) {
-            const bool here = k == r.amin;
-#pragma unroll
-            for (int c = 0; c < C; ++c) s.mu[0][c] = here ? m.mu[k][c] : s.mu[0][c];
-            s.v[0] = here ? m.v[k] : s.v[0];
-        }
-        r.delta = q_rounded(s, X, 0);
+        r.delta = r.d2 / r.v;  // one rounded division instead of K
     }
     used = r.used;
     delta = r.delta;
