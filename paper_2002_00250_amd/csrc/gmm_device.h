@@ -234,6 +234,35 @@ __device__ __forceinline__ void normalise(float (&w)[K], float S, bool plain) {
     }
 }
 
+// Sort the Gaussians by key, descending, with an insertion network of adjacent
+// compare-exchanges; equal keys keep their order.  idx: their ranks before; AGAIN: the Gaussians
+// may have been moved already, and equal keys go by idx.
+template <bool AGAIN, int K, int C, int CV>
+__device__ __forceinline__ void sort_ranks(Mix<K, C, CV>& m, float (&key)[K], int (&idx)[K]) {
+#pragma unroll
+    for (int i = 1; i < K; ++i) {
+#pragma unroll
+        for (int j = i; j > 0; --j) {
+            const bool sw = key[j] > key[j - 1] || (AGAIN && key[j] == key[j - 1] && idx[j] < idx[j - 1]);
+            auto swap = [sw](auto& a, auto& b) {
+                const auto t = sw ? a : b;
+                a = sw ? b : a;
+                b = t;
+            };
+            swap(key[j], key[j - 1]);
+            swap(idx[j], idx[j - 1]);
+            swap(m.w[j], m.w[j - 1]);
+            swap(m.v[j], m.v[j - 1]);
+            if constexpr (CV == 3) {
+                swap(m.vx[j][0], m.vx[j - 1][0]);
+                swap(m.vx[j][1], m.vx[j - 1][1]);
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) swap(m.mu[j][c], m.mu[j - 1][c]);
+        }
+    }
+}
+
 // Update of the mixture after its classification found the match ks: weights, the matched
 // Gaussian or the replaced last one, renormalisation, ranking.  With `chg`, also report which
 // ranks may hold a different (mean, variance) than before the step: bit r is set when the
@@ -358,15 +387,13 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
 
     // Rank by w / sqrt(v), descending, stable.  In a static scene the order rarely changes, so
     // first look whether every adjacent pair is certain to be in order: the squared keys'
-    // products clearly apart, or the lower one unused (w = 0, key 0).  Only a
-    // wavefront with a pair that is not computes the rounded keys, and the insertion network
-    // of adjacent compare-exchanges (strictly-greater swaps only, so equal keys keep their
-    // order) runs only if one of those is out of order.
+    // products clearly apart, or the lower one unused (w = 0, key 0).  A wavefront with a pair
+    // that is not sorts by approximate keys if those decide, else by the rounded ones.
     uint32_t moved = 0u, pr = 0u;  // ranks that got another Gaussian; 3 bits per rank: which
 #pragma unroll
     for (int k = 0; k < K; ++k) pr |= (uint32_t)k << (3 * k);
     uint32_t at = 1u << tgt;       // the ranks where the changed Gaussian is now
-    bool inorder = plain;
+    bool inorder = plain, swapped = plain;  // swapped: certain to be out of order where not in order
 #pragma unroll
     for (int k = 1; k < K; ++k) {
         // key above > key below as w^2 times the other's variance (weights are at most 1 here, so
@@ -374,50 +401,44 @@ __device__ __forceinline__ void mixture_update(Mix<K, C, CV>& m, const float (&X
         // kTiny, where rounding is no longer relative, are not apart
         const float above = (m.w[k - 1] * var_sum(m, k)) * m.w[k - 1];
         const float below = (m.w[k] * var_sum(m, k - 1)) * m.w[k];
-        const bool apart = __builtin_fmaf(above, 1.0f - 2.0f * kMargin, -kTiny) > below;
-        inorder = inorder && (apart || m.w[k] == 0.0f);
+        const bool apart = __builtin_fmaf(above, 1.0f - 2.0f * kMargin, -kTiny) > below || m.w[k] == 0.0f;
+        inorder = inorder && apart;
+        swapped = swapped && (apart || __builtin_fmaf(below, 1.0f - 2.0f * kMargin, -kTiny) > above);
     }
     if (K > 1 && any_lane(!inorder)) {
         float key[K];
         int idx[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            key[k] = m.w[k] / sqrtf(var_sum(m, k));
-            idx[k] = k;
-        }
-        bool unsorted = false;
+        for (int k = 0; k < K; ++k) idx[k] = k;
+        bool network = false, rounded = true;
+        if (REC && !any_lane(!swapped)) {
+            // Adjacent ranks are all clearly apart, some the other way round: sort by approximate
+            // keys, and where the sorted ones are clearly apart too, that is the rounded keys' order.
 #pragma unroll
-        for (int k = 1; k < K; ++k) unsorted = unsorted || key[k] > key[k - 1];
-        if (any_lane(unsorted)) {
+            for (int k = 0; k < K; ++k) key[k] = m.w[k] * __builtin_amdgcn_rsqf(var_sum(m, k));
+            sort_ranks<false>(m, key, idx);
+            network = true;
+            bool sure = true;
 #pragma unroll
-            for (int i = 1; i < K; ++i) {
-#pragma unroll
-                for (int j = i; j > 0; --j) {
-                    const bool sw = key[j] > key[j - 1];
-                    float t;
-#define FGS_CSWAP(A, B)      \
-    t = sw ? (A) : (B);      \
-    (A) = sw ? (B) : (A);    \
-    (B) = t;
-                    FGS_CSWAP(key[j], key[j - 1]);
-                    {
-                        const int ti = sw ? idx[j] : idx[j - 1];
-                        idx[j] = sw ? idx[j - 1] : idx[j];
-                        idx[j - 1] = ti;
-                    }
-                    FGS_CSWAP(m.w[j], m.w[j - 1]);
-                    FGS_CSWAP(m.v[j], m.v[j - 1]);
-                    if constexpr (CV == 3) {
-                        FGS_CSWAP(m.vx[j][0], m.vx[j - 1][0]);
-                        FGS_CSWAP(m.vx[j][1], m.vx[j - 1][1]);
-                    }
-#pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        FGS_CSWAP(m.mu[j][c], m.mu[j - 1][c]);
-                    }
-#undef FGS_CSWAP
-                }
+            for (int k = 0; k < K; ++k) {
+                sure = sure && (m.w[k] == 0.0f || key[k] > kTiny);
+                if (k > 0) sure = sure && (m.w[k] == 0.0f || __builtin_fmaf(key[k - 1], 1.0f - kMargin, -kTiny) > key[k]);
             }
+            rounded = any_lane(!sure);
+        }
+        if (rounded) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) key[k] = m.w[k] / sqrtf(var_sum(m, k));
+            bool unsorted = false;
+#pragma unroll
+            for (int k = 1; k < K; ++k)
+                unsorted = unsorted || key[k] > key[k - 1] || (REC && key[k] == key[k - 1] && idx[k] < idx[k - 1]);
+            if (any_lane(unsorted)) {
+                sort_ranks<REC>(m, key, idx);
+                network = true;
+            }
+        }
+        if (network) {
             pr = 0u;
             at = 0u;
 #pragma unroll
