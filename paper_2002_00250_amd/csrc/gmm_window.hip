@@ -26,11 +26,14 @@
 //
 // Measured, 64 frames of 640x480, K = 3 (forward, backward): with the whole state stored to
 // scratch per frame (72 bytes a pixel and frame) 310 and 657 us; with the changed Gaussians and
-// a replay 275 and 409; with the changed Gaussians of every frame kept 273 and 240.  The forward
-// is bound by its vector instructions (about 500 per wavefront and frame, the ALUs 95 % busy);
-// the backward reads 45 bytes a pixel and frame (3.7 TB/s) beside 380 instructions.  4,800
-// wavefronts are 4.7 a SIMD, hence the launch bound of 5 (96 registers) for K <= 3: with 111
+// a replay 275 and 409; with the changed Gaussians of every frame kept 273 and 240; with weights
+// and ranks as in gmm_device.h 240 and 251; with 32-bit lane offsets (lane_of, opaque) 231 and 217.
+// The forward is bound by its vector instructions (450 per wavefront and frame, the ALUs all but
+// always busy); the backward reads 45 bytes a pixel and frame (4.1 TB/s) beside 380 instructions.
+// 4,800 wavefronts are 4.7 a SIMD, hence the launch bound of 5 (96 registers) for K <= 3: with 111
 // registers a sixth of them ran in a second round.
+#include <type_traits>
+
 #include "device_common.h"
 #include "fgs_internal.h"
 #include "gmm_device.h"
@@ -50,6 +53,22 @@ __device__ __forceinline__ uint32_t pack_rec(const MixRec<C>& r, bool term, bool
            ((uint32_t)(r.kstar < 0 ? 7 : r.kstar) << 5) | (r.clamp ? 256u : 0u) | (r.perm << 9);
 }
 
+// Element p of a plane whose base is the same for the whole launch, through a 32-bit byte offset
+// (p < 2^28 and elements of at most 16 bytes): the base stays in scalar registers.
+template <class T>
+__device__ __forceinline__ T& lane_of(T* base, uint32_t p) {
+    char* b = reinterpret_cast<char*>(const_cast<std::remove_const_t<T>*>(base));
+    return *reinterpret_cast<T*>(b + (uint32_t)(p * (uint32_t)sizeof(T)));
+}
+
+// The lane's pixel, opaque to the compiler in each frame: it would otherwise carry a 64-bit address
+// per plane and lane through the loop (two registers and a 64-bit addition each), and keep the
+// addresses used in the last frame only in scratch memory.
+__device__ __forceinline__ uint32_t opaque(uint32_t p) {
+    asm volatile("" : "+v"(p));
+    return p;
+}
+
 // Plane order of the mean/variance snapshots: colour mu[k][c], colour v[k],
 // depth mu[k], depth v[k]; F = 6K floats per pixel.
 template <int K>
@@ -58,26 +77,26 @@ struct MV {
 };
 
 template <int K>
-__device__ __forceinline__ void store_mv(const MV<K>& s, float* base, int64_t npix, int p) {
+__device__ __forceinline__ void store_mv(const MV<K>& s, float* base, int64_t npix, uint32_t p) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) base[(int64_t)(3 * k + c) * npix + p] = s.muc[k][c];
-        base[(int64_t)(3 * K + k) * npix + p] = s.vc[k];
-        base[(int64_t)(4 * K + k) * npix + p] = s.mud[k];
-        base[(int64_t)(5 * K + k) * npix + p] = s.vd[k];
+        for (int c = 0; c < 3; ++c) lane_of(base + (int64_t)(3 * k + c) * npix, p) = s.muc[k][c];
+        lane_of(base + (int64_t)(3 * K + k) * npix, p) = s.vc[k];
+        lane_of(base + (int64_t)(4 * K + k) * npix, p) = s.mud[k];
+        lane_of(base + (int64_t)(5 * K + k) * npix, p) = s.vd[k];
     }
 }
 
 template <int K>
-__device__ __forceinline__ void load_mv(MV<K>& s, const float* base, int64_t npix, int p) {
+__device__ __forceinline__ void load_mv(MV<K>& s, const float* base, int64_t npix, uint32_t p) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) s.muc[k][c] = base[(int64_t)(3 * k + c) * npix + p];
-        s.vc[k] = base[(int64_t)(3 * K + k) * npix + p];
-        s.mud[k] = base[(int64_t)(4 * K + k) * npix + p];
-        s.vd[k] = base[(int64_t)(5 * K + k) * npix + p];
+        for (int c = 0; c < 3; ++c) s.muc[k][c] = lane_of(base + (int64_t)(3 * k + c) * npix, p);
+        s.vc[k] = lane_of(base + (int64_t)(3 * K + k) * npix, p);
+        s.mud[k] = lane_of(base + (int64_t)(4 * K + k) * npix, p);
+        s.vd[k] = lane_of(base + (int64_t)(5 * K + k) * npix, p);
     }
 }
 
@@ -95,7 +114,7 @@ struct Raw {
 };
 __device__ __forceinline__ Raw read_input(const GmmWindowArgs& a, int t, uint32_t p) {
     const uint8_t* px = a.rgb + (int64_t)t * a.npix * 3 + 3u * p;
-    return Raw{px[0], px[1], px[2], (a.depth + (int64_t)t * a.npix)[p]};
+    return Raw{px[0], px[1], px[2], lane_of(a.depth + (int64_t)t * a.npix, p)};
 }
 __device__ __forceinline__ Input input_of(const GmmWindowArgs& a, const Raw& raw) {
     Input in;
@@ -131,7 +150,8 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_ker
 #pragma unroll 1
     for (int t = 0, e = 0; t < a.T; ++t, e = e + 1 == a.E ? 0 : e + 1) {
         const Raw raw = next;
-        next = read_input(a, min(t + 1, a.T - 1), p);
+        const uint32_t up = opaque(p);
+        next = read_input(a, min(t + 1, a.T - 1), up);
         __builtin_amdgcn_sched_barrier(0);
         if (SAVED ? t + 1 == a.T : e == 0) {
             MV<K> s;
@@ -143,7 +163,7 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_ker
                 s.mud[k] = md.mu[k][0];
                 s.vd[k] = md.v[k];
             }
-            store_mv<K>(s, a.ckpt + (int64_t)(SAVED ? 0 : t / a.E) * F * a.npix, a.npix, p);
+            store_mv<K>(s, a.ckpt + (int64_t)(SAVED ? 0 : t / a.E) * F * a.npix, a.npix, up);
         }
         const Input in = input_of(a, raw);
         bool used_c, used_d;
@@ -155,17 +175,17 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_ker
         mixture_step_rec(md, in.Xd, in.valid, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_d, a.c.v_min_d, sane,
                          used_d, dd, rd);
         if (SAVED) {
-            (a.scratch4() + (int64_t)t * a.npix)[(uint32_t)p] = make_float4(rc.mu[0], rc.mu[1], rc.mu[2], rc.v);
-            (a.scratch2() + (int64_t)t * a.npix)[(uint32_t)p] = make_float2(rd.mu[0], rd.v);
+            lane_of(a.scratch4() + (int64_t)t * a.npix, up) = make_float4(rc.mu[0], rc.mu[1], rc.mu[2], rc.v);
+            lane_of(a.scratch2() + (int64_t)t * a.npix, up) = make_float2(rd.mu[0], rd.v);
         }
         const bool term_c = used_c, term_d = in.valid && used_d;
         const float tc = dc - lam2;
         const float td = wd * (dd - lam2);
         const float Z = term_c ? (term_d ? tc + td : tc) : (term_d ? td : 0.0f);
         const int64_t o = (int64_t)t * a.npix;
-        (a.Z + o)[(uint32_t)p] = Z;
-        (a.has + o)[(uint32_t)p] = (term_c || term_d) ? 1 : 0;
-        (a.rec + o)[(uint32_t)p] = (uint64_t)pack_rec(rc, term_c, true) | ((uint64_t)pack_rec(rd, term_d, in.valid) << 32);
+        lane_of(a.Z + o, up) = Z;
+        lane_of(a.has + o, up) = (term_c || term_d) ? 1 : 0;
+        lane_of(a.rec + o, up) = (uint64_t)pack_rec(rc, term_c, true) | ((uint64_t)pack_rec(rd, term_d, in.valid) << 32);
     }
 }
 
@@ -369,7 +389,6 @@ template <int K, bool SAVED>
 __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_kernel(GmmWindowArgs a) {
     __shared__ double sh[kBlock / 64][3];
     const int p = blockIdx.x * kBlock + threadIdx.x;
-    const uint32_t up = (uint32_t)p;
     double acc[3] = {0.0, 0.0, 0.0};  // alpha, lambda, w_depth
     if (p < a.npix) {
         const float alpha = a.theta[0], lam = a.theta[1], wd = a.theta[2];
@@ -391,7 +410,7 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_ke
             float muc[K][3], vc[K], mud[K][1], vd[K];
             {
                 MV<K> s;
-                load_mv<K>(s, a.ckpt + (int64_t)seg * F * npix, npix, p);
+                load_mv<K>(s, a.ckpt + (int64_t)seg * F * npix, npix, opaque(p));
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
 #pragma unroll
@@ -402,15 +421,16 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_ke
                 }
             }
             if (!SAVED) {
-                Raw nraw = read_input(a, t0, up);
-                uint64_t nrec = (a.rec + (int64_t)t0 * npix)[up];
+                Raw nraw = read_input(a, t0, p);
+                uint64_t nrec = lane_of(a.rec + (int64_t)t0 * npix, p);
 #pragma unroll 1
                 for (int t = t0; t < t1; ++t) {
                     const Raw raw = nraw;
                     const uint64_t rr = nrec;
+                    const uint32_t up = opaque(p);
                     const int tn = min(t + 1, t1 - 1);
                     nraw = read_input(a, tn, up);
-                    nrec = (a.rec + (int64_t)tn * npix)[up];
+                    nrec = lane_of(a.rec + (int64_t)tn * npix, up);
                     __builtin_amdgcn_sched_barrier(0);
                     const Input in = input_of(a, raw);
                     const bool last = t + 1 == t1;
@@ -418,17 +438,18 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_ke
                     replay_mix<K, 3>(muc, vc, in.Xc, (uint32_t)rr, alpha, a.c.v_init_c, a.c.v_min_c, last, pm, pv);
                     replay_mix<K, 1>(mud, vd, in.Xd, (uint32_t)(rr >> 32), alpha, a.c.v_init_d, a.c.v_min_d, last, qm,
                                      qv);
-                    (sc + (int64_t)(t - t0) * npix)[up] = make_float4(pm[0], pm[1], pm[2], pv);
-                    (sd + (int64_t)(t - t0) * npix)[up] = make_float2(qm[0], qv);
+                    lane_of(sc + (int64_t)(t - t0) * npix, up) = make_float4(pm[0], pm[1], pm[2], pv);
+                    lane_of(sd + (int64_t)(t - t0) * npix, up) = make_float2(qm[0], qv);
                 }
             }
             auto read = [&](int t) {
                 BackRead b;
+                const uint32_t up = opaque(p);
                 b.raw = read_input(a, t, up);
-                b.rec = (a.rec + (int64_t)t * npix)[up];
-                b.pc = (sc + (int64_t)(t - t0) * npix)[up];
-                b.pd = (sd + (int64_t)(t - t0) * npix)[up];
-                b.g = (a.dZ + (int64_t)t * npix)[up];
+                b.rec = lane_of(a.rec + (int64_t)t * npix, up);
+                b.pc = lane_of(sc + (int64_t)(t - t0) * npix, up);
+                b.pd = lane_of(sd + (int64_t)(t - t0) * npix, up);
+                b.g = lane_of(a.dZ + (int64_t)t * npix, up);
                 return b;
             };
             BackRead next = read(t1 - 1);
