@@ -159,7 +159,7 @@ struct GmmWindowArgs {
     }
 };
 bool gmm_window_supported(int K);
-int gmm_window_blocks(int npix);
+int gmm_window_blocks(int K, int npix);  // of the backward: rows of `partial`
 hipError_t gmm_window_launch_forward(const GmmWindowArgs& a, int K, hipStream_t s);
 hipError_t gmm_window_launch_backward(const GmmWindowArgs& a, int K, hipStream_t s);
 

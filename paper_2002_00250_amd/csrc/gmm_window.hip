@@ -77,14 +77,18 @@ struct MV {
 };
 
 template <int K>
-__device__ __forceinline__ void store_mv(const MV<K>& s, float* base, int64_t npix, uint32_t p) {
+__device__ __forceinline__ void store_mv(const MV<K>& s, float* base, int64_t npix, uint32_t p, bool colour, bool depth) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
+        if (colour) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) lane_of(base + (int64_t)(3 * k + c) * npix, p) = s.muc[k][c];
-        lane_of(base + (int64_t)(3 * K + k) * npix, p) = s.vc[k];
-        lane_of(base + (int64_t)(4 * K + k) * npix, p) = s.mud[k];
-        lane_of(base + (int64_t)(5 * K + k) * npix, p) = s.vd[k];
+            for (int c = 0; c < 3; ++c) lane_of(base + (int64_t)(3 * k + c) * npix, p) = s.muc[k][c];
+            lane_of(base + (int64_t)(3 * K + k) * npix, p) = s.vc[k];
+        }
+        if (depth) {
+            lane_of(base + (int64_t)(4 * K + k) * npix, p) = s.mud[k];
+            lane_of(base + (int64_t)(5 * K + k) * npix, p) = s.vd[k];
+        }
     }
 }
 
@@ -126,10 +130,20 @@ __device__ __forceinline__ Input input_of(const GmmWindowArgs& a, const Raw& raw
     return in;
 }
 
-template <int K, bool SAVED>
+// SPLIT: the mixtures of a pixel run on two wavefronts of a workgroup of 128 pixels, the depth
+// mixture's handing its term to the colour mixture's through LDS once a frame.  A small window
+// leaves SIMDs idle while each wavefront walks its chain of T frames through both mixtures.
+template <int K, bool SAVED, bool SPLIT>
 __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_kernel(GmmWindowArgs a) {
-    const int p = blockIdx.x * kBlock + threadIdx.x;
-    if (p >= a.npix) return;
+    constexpr int kPixels = SPLIT ? kBlock / 2 : kBlock;
+    __shared__ float term_of[SPLIT ? 2 : 1][SPLIT ? kPixels : 1];  // by frame parity: w_d (delta_d - lambda^2)
+    __shared__ uint8_t used_of[SPLIT ? 2 : 1][SPLIT ? kPixels : 1];
+    const int lane = (int)threadIdx.x % kPixels;
+    const int part = SPLIT ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kPixels) : 0;
+    const bool do_c = !SPLIT || part == 0, do_d = !SPLIT || part == 1;
+    const bool inside = (int)blockIdx.x * kPixels + lane < a.npix;
+    if (!SPLIT && !inside) return;
+    const uint32_t p = inside ? blockIdx.x * kPixels + lane : a.npix - 1;  // (every lane meets the barriers)
     const float alpha = a.theta[0], lam = a.theta[1], wd = a.theta[2];
     const float lam2 = lam * lam;
     const bool sane = alpha > 0.0f && alpha < 1.0f &&
@@ -153,7 +167,7 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_ker
         const uint32_t up = opaque(p);
         next = read_input(a, min(t + 1, a.T - 1), up);
         __builtin_amdgcn_sched_barrier(0);
-        if (SAVED ? t + 1 == a.T : e == 0) {
+        if ((SAVED ? t + 1 == a.T : e == 0) && inside) {
             MV<K> s;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -163,29 +177,48 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_ker
                 s.mud[k] = md.mu[k][0];
                 s.vd[k] = md.v[k];
             }
-            store_mv<K>(s, a.ckpt + (int64_t)(SAVED ? 0 : t / a.E) * F * a.npix, a.npix, up);
+            store_mv<K>(s, a.ckpt + (int64_t)(SAVED ? 0 : t / a.E) * F * a.npix, a.npix, up, do_c, do_d);
         }
         const Input in = input_of(a, raw);
-        bool used_c, used_d;
-        float dc, dd;
+        const int64_t o = (int64_t)t * a.npix;
+        bool used_c = false, used_d = false;
+        float dc = 0.0f, dd = 0.0f;
         MixRec<3> rc;
         MixRec<1> rd;
-        mixture_step_rec(mc, in.Xc, true, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_c, a.c.v_min_c, sane,
-                         used_c, dc, rc);
-        mixture_step_rec(md, in.Xd, in.valid, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_d, a.c.v_min_d, sane,
-                         used_d, dd, rd);
-        if (SAVED) {
-            lane_of(a.scratch4() + (int64_t)t * a.npix, up) = make_float4(rc.mu[0], rc.mu[1], rc.mu[2], rc.v);
-            lane_of(a.scratch2() + (int64_t)t * a.npix, up) = make_float2(rd.mu[0], rd.v);
+        if (do_c) {
+            mixture_step_rec(mc, in.Xc, true, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_c, a.c.v_min_c, sane,
+                             used_c, dc, rc);
+            if (SAVED && inside) lane_of(a.scratch4() + o, up) = make_float4(rc.mu[0], rc.mu[1], rc.mu[2], rc.v);
         }
-        const bool term_c = used_c, term_d = in.valid && used_d;
+        if (do_d) {
+            mixture_step_rec(md, in.Xd, in.valid, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_d, a.c.v_min_d, sane,
+                             used_d, dd, rd);
+            if (SAVED && inside) lane_of(a.scratch2() + o, up) = make_float2(rd.mu[0], rd.v);
+        }
+        const bool term_c = used_c;
+        bool term_d = in.valid && used_d;
         const float tc = dc - lam2;
-        const float td = wd * (dd - lam2);
+        float td = wd * (dd - lam2);
+        if (SPLIT) {
+            uint32_t* halves = reinterpret_cast<uint32_t*>(a.rec + o);
+            if (do_d) {
+                term_of[t & 1][lane] = td;
+                used_of[t & 1][lane] = term_d ? 1 : 0;
+                if (inside) lane_of(halves + 1, 2 * up) = pack_rec(rd, term_d, in.valid);
+            }
+            __syncthreads();  // (the other parity's slots are written while these are read)
+            if (!do_c) continue;
+            td = term_of[t & 1][lane];
+            term_d = used_of[t & 1][lane] != 0;
+            if (!inside) continue;
+            lane_of(halves, 2 * up) = pack_rec(rc, term_c, true);
+        } else {
+            lane_of(a.rec + o, up) =
+                (uint64_t)pack_rec(rc, term_c, true) | ((uint64_t)pack_rec(rd, term_d, in.valid) << 32);
+        }
         const float Z = term_c ? (term_d ? tc + td : tc) : (term_d ? td : 0.0f);
-        const int64_t o = (int64_t)t * a.npix;
         lane_of(a.Z + o, up) = Z;
         lane_of(a.has + o, up) = (term_c || term_d) ? 1 : 0;
-        lane_of(a.rec + o, up) = (uint64_t)pack_rec(rc, term_c, true) | ((uint64_t)pack_rec(rd, term_d, in.valid) << 32);
     }
 }
 
@@ -385,10 +418,14 @@ struct BackRead {
     float g;
 };
 
-template <int K, bool SAVED>
+// SPLIT: the mixtures on wavefronts of their own, as in the forward (they share nothing here).
+template <int K, bool SAVED, bool SPLIT>
 __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_kernel(GmmWindowArgs a) {
     __shared__ double sh[kBlock / 64][3];
-    const int p = blockIdx.x * kBlock + threadIdx.x;
+    constexpr int kPixels = SPLIT ? kBlock / 2 : kBlock;
+    const int part = SPLIT ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kPixels) : 0;
+    const bool do_c = !SPLIT || part == 0, do_d = !SPLIT || part == 1;
+    const int p = blockIdx.x * kPixels + (int)threadIdx.x % kPixels;
     double acc[3] = {0.0, 0.0, 0.0};  // alpha, lambda, w_depth
     if (p < a.npix) {
         const float alpha = a.theta[0], lam = a.theta[1], wd = a.theta[2];
@@ -434,21 +471,21 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_ke
                     __builtin_amdgcn_sched_barrier(0);
                     const Input in = input_of(a, raw);
                     const bool last = t + 1 == t1;
-                    float pm[3], pv, qm[1], qv;
-                    replay_mix<K, 3>(muc, vc, in.Xc, (uint32_t)rr, alpha, a.c.v_init_c, a.c.v_min_c, last, pm, pv);
-                    replay_mix<K, 1>(mud, vd, in.Xd, (uint32_t)(rr >> 32), alpha, a.c.v_init_d, a.c.v_min_d, last, qm,
+                    float pm[3] = {}, pv = 0.0f, qm[1] = {}, qv = 0.0f;
+                    if (do_c) replay_mix<K, 3>(muc, vc, in.Xc, (uint32_t)rr, alpha, a.c.v_init_c, a.c.v_min_c, last, pm, pv);
+                    if (do_d) replay_mix<K, 1>(mud, vd, in.Xd, (uint32_t)(rr >> 32), alpha, a.c.v_init_d, a.c.v_min_d, last, qm,
                                      qv);
-                    lane_of(sc + (int64_t)(t - t0) * npix, up) = make_float4(pm[0], pm[1], pm[2], pv);
-                    lane_of(sd + (int64_t)(t - t0) * npix, up) = make_float2(qm[0], qv);
+                    if (do_c) lane_of(sc + (int64_t)(t - t0) * npix, up) = make_float4(pm[0], pm[1], pm[2], pv);
+                    if (do_d) lane_of(sd + (int64_t)(t - t0) * npix, up) = make_float2(qm[0], qv);
                 }
             }
             auto read = [&](int t) {
-                BackRead b;
+                BackRead b = {};
                 const uint32_t up = opaque(p);
                 b.raw = read_input(a, t, up);
                 b.rec = lane_of(a.rec + (int64_t)t * npix, up);
-                b.pc = lane_of(sc + (int64_t)(t - t0) * npix, up);
-                b.pd = lane_of(sd + (int64_t)(t - t0) * npix, up);
+                if (do_c) b.pc = lane_of(sc + (int64_t)(t - t0) * npix, up);
+                if (do_d) b.pd = lane_of(sd + (int64_t)(t - t0) * npix, up);
                 b.g = lane_of(a.dZ + (int64_t)t * npix, up);
                 return b;
             };
@@ -463,10 +500,10 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_ke
                 const uint32_t rc = (uint32_t)b.rec, rd = (uint32_t)(b.rec >> 32);
                 const float pm[3] = {b.pc.x, b.pc.y, b.pc.z}, qm[1] = {b.pd.x};
                 float dc = 0.f, dd = 0.f;
-                reverse_mix<K, 3>(muc, vc, in.Xc, rc, alpha, undo, pm, b.pc.w, b.g, amc, avc, acc[0], dc);
-                reverse_mix<K, 1>(mud, vd, in.Xd, rd, alpha, undo, qm, b.pd.y, b.g * wd, amd, avd, acc[0], dd);
-                if (rc & 1u) acc[1] += (double)(b.g * (-2.0f * lam));
-                if (rd & 1u) {
+                if (do_c) reverse_mix<K, 3>(muc, vc, in.Xc, rc, alpha, undo, pm, b.pc.w, b.g, amc, avc, acc[0], dc);
+                if (do_d) reverse_mix<K, 1>(mud, vd, in.Xd, rd, alpha, undo, qm, b.pd.y, b.g * wd, amd, avd, acc[0], dd);
+                if (do_c && (rc & 1u)) acc[1] += (double)(b.g * (-2.0f * lam));
+                if (do_d && (rd & 1u)) {
                     acc[1] += (double)(b.g * (-2.0f * lam) * wd);
                     acc[2] += (double)(b.g * (dd - lam2));
                 }
@@ -493,47 +530,83 @@ __global__ __launch_bounds__(kBlock) void gmm_window_reduce_kernel(const double*
 
 }  // namespace
 
-int gmm_window_blocks(int npix) { return (npix + kBlock - 1) / kBlock; }
-
 bool gmm_window_supported(int K) { return K >= 1 && K <= 5; }
 
 namespace {
 
-template <int K>
-void launch_forward(const GmmWindowArgs& a, dim3 grid, hipStream_t s) {
-    if (a.saved) hipLaunchKernelGGL((gmm_window_forward_kernel<K, true>), grid, dim3(kBlock), 0, s, a);
-    else hipLaunchKernelGGL((gmm_window_forward_kernel<K, false>), grid, dim3(kBlock), 0, s, a);
+// Up to kSplitPixels (with the mixtures split: four wavefronts a SIMD) and with three Gaussians or more
+// the mixtures run on wavefronts of their own: forward of 24 frames, with its call, 131x93, K = 5: 95.6 ->
+// 70.5 us, K = 3: 70.7 -> 56.2; 400x300, K = 5: 104 -> 90, K = 3: 77.5 -> 70.5.  Larger windows fill the
+// SIMDs anyway and read their frames twice for nothing (480x360, K = 3: 88 -> 92.6, K = 5: 126.5 ->
+// 124.7; 640x480, K = 3: 118 -> 157); K = 1, whose mixtures are short, 40-44 either way.  The
+// kernels alone, 131x93, K = 5: forward 71.3 -> 53.2 us, backward 39.2 -> 29.6.
+constexpr int kSplitPixels = 1 << 17;
+constexpr bool splits(int K, int npix) { return K >= 3 && npix <= kSplitPixels; }
+
+}  // namespace
+
+int gmm_window_blocks(int K, int npix) {
+    const int pixels = splits(K, npix) ? kBlock / 2 : kBlock;
+    return (npix + pixels - 1) / pixels;
+}
+
+namespace {
+
+template <int K, bool SAVED>
+void launch_forward_of(const GmmWindowArgs& a, hipStream_t s) {
+    if constexpr (splits(K, 1)) {
+        if (splits(K, a.npix)) {
+            hipLaunchKernelGGL((gmm_window_forward_kernel<K, SAVED, true>), dim3((unsigned)gmm_window_blocks(K, a.npix)),
+                               dim3(kBlock), 0, s, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((gmm_window_forward_kernel<K, SAVED, false>), dim3((unsigned)gmm_window_blocks(K, a.npix)),
+                       dim3(kBlock), 0, s, a);
 }
 template <int K>
-void launch_backward(const GmmWindowArgs& a, dim3 grid, hipStream_t s) {
-    if (a.saved) hipLaunchKernelGGL((gmm_window_backward_kernel<K, true>), grid, dim3(kBlock), 0, s, a);
-    else hipLaunchKernelGGL((gmm_window_backward_kernel<K, false>), grid, dim3(kBlock), 0, s, a);
+void launch_forward(const GmmWindowArgs& a, hipStream_t s) {
+    if (a.saved) launch_forward_of<K, true>(a, s);
+    else launch_forward_of<K, false>(a, s);
+}
+template <int K, bool SAVED>
+void launch_backward_of(const GmmWindowArgs& a, int blocks, hipStream_t s) {
+    if constexpr (splits(K, 1)) {
+        if (splits(K, a.npix)) {
+            hipLaunchKernelGGL((gmm_window_backward_kernel<K, SAVED, true>), dim3(blocks), dim3(kBlock), 0, s, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((gmm_window_backward_kernel<K, SAVED, false>), dim3(blocks), dim3(kBlock), 0, s, a);
+}
+template <int K>
+void launch_backward(const GmmWindowArgs& a, int blocks, hipStream_t s) {
+    if (a.saved) launch_backward_of<K, true>(a, blocks, s);
+    else launch_backward_of<K, false>(a, blocks, s);
 }
 
 }  // namespace
 
 hipError_t gmm_window_launch_forward(const GmmWindowArgs& a, int K, hipStream_t s) {
-    const dim3 grid(gmm_window_blocks(a.npix));
     switch (K) {
-        case 1: launch_forward<1>(a, grid, s); break;
-        case 2: launch_forward<2>(a, grid, s); break;
-        case 3: launch_forward<3>(a, grid, s); break;
-        case 4: launch_forward<4>(a, grid, s); break;
-        case 5: launch_forward<5>(a, grid, s); break;
+        case 1: launch_forward<1>(a, s); break;
+        case 2: launch_forward<2>(a, s); break;
+        case 3: launch_forward<3>(a, s); break;
+        case 4: launch_forward<4>(a, s); break;
+        case 5: launch_forward<5>(a, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 hipError_t gmm_window_launch_backward(const GmmWindowArgs& a, int K, hipStream_t s) {
-    const int nb = gmm_window_blocks(a.npix);
-    const dim3 grid(nb);
+    const int nb = gmm_window_blocks(K, a.npix);
     switch (K) {
-        case 1: launch_backward<1>(a, grid, s); break;
-        case 2: launch_backward<2>(a, grid, s); break;
-        case 3: launch_backward<3>(a, grid, s); break;
-        case 4: launch_backward<4>(a, grid, s); break;
-        case 5: launch_backward<5>(a, grid, s); break;
+        case 1: launch_backward<1>(a, nb, s); break;
+        case 2: launch_backward<2>(a, nb, s); break;
+        case 3: launch_backward<3>(a, nb, s); break;
+        case 4: launch_backward<4>(a, nb, s); break;
+        case 5: launch_backward<5>(a, nb, s); break;
         default: return hipErrorInvalidValue;
     }
     hipError_t e = hipGetLastError();

@@ -1526,7 +1526,7 @@ fgs_status fgs_gmm_window_create(int32_t T, int32_t H, int32_t W, const fgs_gmm_
         o_ckpt = align256((size_t)T * n * 8);  // the records come first
         o_scr = o_ckpt + align256(ckpts * F * n * 4);
         o_par = o_scr + align256(rows * 6 * n * 4);
-        total = o_par + align256((size_t)gmm_window_blocks(w->npix) * 3 * 8);
+        total = o_par + align256((size_t)gmm_window_blocks(w->K, w->npix) * 3 * 8);
     };
     // Every frame's changed Gaussians are kept (no replay in the backward) where that takes at
     // most a quarter more than a state per checkpoint and per frame of a segment, the most

@@ -52,3 +52,34 @@ def test_both_plans_give_the_same_gradient(K, H, W, alpha):
     rel = np.abs(out[0][3] - g_ref) / np.abs(g_ref)
     log(f"K={K} {H}x{W} alpha={alpha}: gradient {out[0][3]} rel to fp64 {rel}")
     assert np.all(rel <= 1e-5)
+
+
+@pytest.mark.parametrize("K,E", [(3, 4), (3, 1), (5, 4), (2, 4)])
+def test_large_window_equals_its_parts(K, E):
+    """A window beyond 2^17 pixels (both mixtures on one wavefront) against its two halves (a
+    wavefront each from K = 3 on), whose pixels do not meet: the same scores and records, and
+    gradients that add up (the sums are fp64 in another order: 1e-12)."""
+    from paper_2002_00250_amd.adjoint import GmmWindow
+    T, H, W = 5, 364, 363
+    assert H * W > 1 << 17 >= H // 2 * W
+    g = torch.Generator(device="cuda").manual_seed(K)
+    base = torch.randint(0, 256, (H, W, 3), device="cuda", generator=g)
+    rgb = (base + torch.randint(-40, 41, (T, H, W, 3), device="cuda", generator=g)).clamp(0, 255).to(torch.uint8)
+    dep = torch.randint(-400, 4000, (T, H, W), device="cuda", generator=g).clamp(min=0).to(torch.int16)
+    dZ = torch.randn((T, H, W), device="cuda", generator=g)
+    theta = torch.tensor([0.05, 2.5, 1.0], device="cuda")
+    p = _params_c(GmmParams(Kc=K, Kd=K))
+    whole = GmmWindow(T, H, W, p, checkpoint_every=E)
+    Z, has = whole.forward(theta, rgb, dep)
+    grad, rec, total = whole.backward(theta, rgb, dep, dZ).cpu(), whole.records(), torch.zeros(3, dtype=torch.float64)
+    for rows in (slice(0, H // 2), slice(H // 2, H)):
+        part = GmmWindow(T, H // 2, W, p, checkpoint_every=E)
+        r, d, z = (x[:, rows].contiguous() for x in (rgb, dep, dZ))
+        Zp, hp = part.forward(theta, r, d)
+        assert torch.equal(Zp.view(torch.int32), Z[:, rows].contiguous().view(torch.int32))
+        assert torch.equal(hp, has[:, rows]) and np.array_equal(part.records(), rec[:, rows])
+        total += part.backward(theta, r, d, z).cpu()
+        part.close()
+    # (fp64 sums of n terms of either sign and of order |dZ| x 10^3 at most: n eps times their size)
+    assert torch.all((total - grad).abs() <= 1e-12 * (grad.abs() + 1e3 * float(dZ.abs().sum()))), (total, grad)
+    whole.close()
