@@ -15,10 +15,12 @@
 //
 // Measured at 640x480, N = 20, static background (T = 2): the first version read slot by slot, each
 // read behind the previous slot's possible write, and wrote single words and bytes: 60 us a frame
-// (one model after another frame of its own, 81 in turn with two others); now 41 (2 models of
-// 1280x720 392 -> 242, N = 35 93 -> 53).  It moves 570 bytes a pixel at 4.2 TB/s: the samples, the
-// D lines of random slots and the changed sectors; the 1,200 tiles are 1.2 rounds of the four a
-// CU holds (114 registers; at 96 the spills cost more than the second round, 44.8 us).
+// (one model after another frame of its own, 81 in turn with two others); on quad planes held in
+// registers 41 (2 models of 1280x720 392 -> 242, N = 35 93 -> 53); with five workgroups a CU 38.6.
+// At 114 registers a CU held four: 1,200 tiles were 1.17 rounds.  T, R and S wait in LDS during the
+// slot loop, the candidates' slots share a word, the weights are scalars and the second smallest
+// distance replaces a count and R: 96 registers (forced to that before, spills cost more than the
+// second round, 44.8 us).  N = 16: 39.0 -> 35.7, N = 24: 44.3 -> 42.1, N = 40: 56.9 -> 54.5.
 #include <cstring>
 
 #include "device_common.h"
@@ -36,6 +38,9 @@ namespace {
 constexpr int grad_class_min(int nmax) {
     return nmax <= 8 ? 2 : nmax <= 16 ? 9 : nmax <= 20 ? 17 : nmax <= 24 ? 21 : nmax <= 32 ? 25 : nmax <= 40 ? 33 : 41;
 }
+
+// Workgroups a CU is to hold (its four SIMDs a wavefront of each).
+constexpr int grad_waves(int nmax) { return nmax <= 20 ? 5 : nmax <= 32 ? 4 : nmax <= 40 ? 3 : 2; }
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
@@ -141,11 +146,14 @@ __global__ __launch_bounds__(kBlock) void pbas_grad_fill_kernel(PbasGradArgs a) 
 // One updating frame on a 64x4 tile: the plain variant's tiling, fire-byte halo, LDS scatter of
 // pending neighbour writes, register merges and whole-sector write-back (pbas_device.h), on two
 // words per slot.
-template <int NMAX, bool NT>
-__global__ __launch_bounds__(kBlock, NMAX <= 24 ? 4 : (NMAX <= 40 ? 3 : 2)) void pbas_grad_step_kernel(PbasGradArgs a) {
+// TWO: min_matches = 2, decided by the second smallest distance (as in pbas_device.h; one v_med3_f32
+// where a count takes a comparison and an addition), so that the slot loop needs no R.
+template <int NMAX, bool NT, bool TWO>
+__global__ __launch_bounds__(kBlock, grad_waves(NMAX)) void pbas_grad_step_kernel(PbasGradArgs a) {
     constexpr int NLO = grad_class_min(NMAX);
     constexpr int NW = PbasLds<NMAX>::NW;
     __shared__ PbasLds<NMAX> sh;
+    __shared__ float4 park[3][kBlock];  // a lane's T, R and S during the slot loop
     const int tid = threadIdx.x;
     const int tiles_x = (a.W + kTileW - 1) / kTileW;
     const int bx = (int)blockIdx.x % tiles_x, by = (int)blockIdx.x / tiles_x;
@@ -196,32 +204,36 @@ __global__ __launch_bounds__(kBlock, NMAX <= 24 ? 4 : (NMAX <= 40 ? 3 : 2)) void
         const unsigned long long sum = a.m.gsum[4 * (((uint64_t)a.t + 2u) % 3u) + j];  // frame t-1's slot
         const float mean = (float)(double)sum / (float)a.npix;
         wgt[j] = a.c.grad_alpha / fmaxf(mean, 1.0f);
+        wgt[j] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wgt[j])));  // one value per frame
     }
     if (a.apply_pending) {
         __syncthreads();  // bit-words cleared
         scatter_fired<NMAX>(sh, fin, N, a.t - 1u, a.c.key0, a.c.key1);
     }
     // Self-update candidates (the 1/T test with T from before this frame) and the D they replace.
-    float T[4] = {Tv.x, Tv.y, Tv.z, Tv.w};
+    const float T0[4] = {Tv.x, Tv.y, Tv.z, Tv.w};
     const bool active[4] = {true, true, true, valid};
     const float inv16 = 1.0f / 65536.0f;
     const U32x4 w0 = philox4x32_10((uint32_t)p, a.t, 0u, 0u, a.c.key0, a.c.key1);
     bool cand[4];
-    int ks[4];
+    uint32_t slots = 0u;  // the candidates' slots, a byte each
     float dold[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const uint32_t a0 = w0.v[j];
-        cand[j] = active[j] && (float)(a0 >> 16) * inv16 * T[j] < 1.0f;
-        ks[j] = (int)(__umul24(a0 & 0xFFFFu, (uint32_t)N) >> 16);
-        dold[j] = cand[j] ? reinterpret_cast<const float*>(a.m.D + (int64_t)ks[j] * npix + p)[j] : 0.0f;
+        cand[j] = active[j] && (float)(a0 >> 16) * inv16 * T0[j] < 1.0f;
+        const int k = (int)(__umul24(a0 & 0xFFFFu, (uint32_t)N) >> 16);
+        slots |= (uint32_t)k << (8 * j);
+        dold[j] = cand[j] ? reinterpret_cast<const float*>(a.m.D + (int64_t)k * npix + p)[j] : 0.0f;
     }
+    park[0][tid] = Tv;
+    park[1][tid] = Rv;
+    park[2][tid] = Sv;
     if (a.apply_pending) __syncthreads();  // every write aimed at the tile recorded
     add_magnitudes(a.m.gsum, a.t, Mw, inside);  // frame t's sums
     if (!inside) return;
 
-    float R[4] = {Rv.x, Rv.y, Rv.z, Rv.w};
-    float S[4] = {Sv.x, Sv.y, Sv.z, Sv.w};
+    const float R0[4] = {Rv.x, Rv.y, Rv.z, Rv.w};
 
     // Frame t-1's neighbour writes into this pixel (its previous value and magnitudes) are
     // merged slot by slot, then each slot is classified: bytes become floats in one
@@ -233,7 +245,7 @@ __global__ __launch_bounds__(kBlock, NMAX <= 24 ? 4 : (NMAX <= 40 ? 3 : 2)) void
     const float fi[4] = {(float)(Iw & 0xFFu), (float)((Iw >> 8) & 0xFFu), (float)((Iw >> 16) & 0xFFu), (float)(Iw >> 24)};
     const float fm[3] = {(float)(Mw & 0xFFu), (float)((Mw >> 8) & 0xFFu), (float)((Mw >> 16) & 0xFFu)};
     int cnt[4] = {0, 0, 0, 0};
-    float dmin[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
+    float dmin[4] = {INFINITY, INFINITY, INFINITY, INFINITY}, dsec[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
     uint32_t dirty_s = 0u, dirty_g = 0u, chg_s = 0u, chg_g = 0u;
     uint32_t byte_ids;
     asm("v_mov_b32 %0, 0x03020100" : "=v"(byte_ids));
@@ -257,27 +269,39 @@ __global__ __launch_bounds__(kBlock, NMAX <= 24 ? 4 : (NMAX <= 40 ? 3 : 2)) void
                 const float dv = (float)((sm[k] >> (8 * j)) & 0xFFu) - fi[j];
                 const float dm = (float)((gm[k] >> (8 * j)) & 0xFFu) - fm[j];
                 const float d = wgt[j] * fabsf(dm) + fabsf(dv);
-                cnt[j] += d < R[j] ? 1 : 0;
+                if (TWO) dsec[j] = __builtin_amdgcn_fmed3f(dmin[j], dsec[j], d);
+                else cnt[j] += d < R0[j] ? 1 : 0;
                 dmin[j] = fminf(dmin[j], d);
             }
             const float sd = (float)(sm[k] >> 24);
             const float d = sd != 0.0f ? fabsf(sd - fi[3]) : INFINITY;  // a depth byte 0: nothing recorded
-            cnt[3] += d < R[3] ? 1 : 0;
+            if (TWO) dsec[3] = __builtin_amdgcn_fmed3f(dmin[3], dsec[3], d);
+            else cnt[3] += d < R0[3] ? 1 : 0;
             dmin[3] = fminf(dmin[3], d);
             // (a slot is finished before the next: left to itself the scheduler keeps the
             // distances of many slots and needs 40 more registers)
             asm volatile("" : "+v"(dmin[0]), "+v"(dmin[1]), "+v"(dmin[2]), "+v"(dmin[3]));
-            asm volatile("" : "+v"(cnt[0]), "+v"(cnt[1]), "+v"(cnt[2]), "+v"(cnt[3]));
+            if (TWO) asm volatile("" : "+v"(dsec[0]), "+v"(dsec[1]), "+v"(dsec[2]), "+v"(dsec[3]));
+            else asm volatile("" : "+v"(cnt[0]), "+v"(cnt[1]), "+v"(cnt[2]), "+v"(cnt[3]));
         }
     }
     __builtin_amdgcn_sched_barrier(0);
     if (dmin[3] == INFINITY) dmin[3] = 255.0f;
+    int back = tid;  // (opaque: the parked values are read again, not kept)
+    asm volatile("" : "+v"(back));
+    const float4 Tp = park[0][back], Rp = park[1][back], Sp = park[2][back];
+    float T[4] = {Tp.x, Tp.y, Tp.z, Tp.w};
+    float R[4] = {Rp.x, Rp.y, Rp.z, Rp.w};
+    float S[4] = {Sp.x, Sp.y, Sp.z, Sp.w};
+    int ks[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) ks[j] = (int)((slots >> (8 * j)) & 0xFFu);
 
     bool F[4], upd[4];
     bool fg = false;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        F[j] = active[j] && cnt[j] < a.c.min_matches;
+        F[j] = active[j] && !(TWO ? dsec[j] < R[j] : cnt[j] >= a.c.min_matches);
         fg = fg || F[j];
         upd[j] = cand[j] && !F[j];
     }
@@ -364,9 +388,9 @@ __global__ __launch_bounds__(kBlock, NMAX <= 24 ? 4 : (NMAX <= 40 ? 3 : 2)) void
     const float4 Rn = make_float4(R[0], R[1], R[2], R[3]);
     const float4 Tn = make_float4(T[0], T[1], T[2], T[3]);
     const float4 Sn = make_float4(S[0], S[1], S[2], S[3]);
-    if (differs(Rn, Rv)) a.m.R[p] = Rn;
-    if (differs(Tn, Tv)) a.m.T[p] = Tn;
-    if (differs(Sn, Sv)) a.m.S[p] = Sn;
+    if (differs(Rn, park[1][back])) a.m.R[p] = Rn;
+    if (differs(Tn, park[0][back])) a.m.T[p] = Tn;
+    if (differs(Sn, park[2][back])) a.m.S[p] = Sn;
     a.m.last[p] = Iw;
     a.m.last_g[p] = Mw;
     a.m.fire[a.t & 1u][p] = (uint8_t)fire;
@@ -462,10 +486,15 @@ __global__ void pbas_grad_sums_kernel(unsigned long long* gsum, uint32_t* canon,
 
 inline unsigned blocks1d(int64_t n) { return (unsigned)((n + 255) / 256); }
 
+template <int NMAX, bool TWO>
+void launch_step_of(const PbasGradArgs& a, dim3 grid, hipStream_t s) {
+    if (a.streaming) hipLaunchKernelGGL((pbas_grad_step_kernel<NMAX, true, TWO>), grid, dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((pbas_grad_step_kernel<NMAX, false, TWO>), grid, dim3(kBlock), 0, s, a);
+}
 template <int NMAX>
 void launch_step(const PbasGradArgs& a, dim3 grid, hipStream_t s) {
-    if (a.streaming) hipLaunchKernelGGL((pbas_grad_step_kernel<NMAX, true>), grid, dim3(kBlock), 0, s, a);
-    else hipLaunchKernelGGL((pbas_grad_step_kernel<NMAX, false>), grid, dim3(kBlock), 0, s, a);
+    if (a.c.min_matches == 2) launch_step_of<NMAX, true>(a, grid, s);
+    else launch_step_of<NMAX, false>(a, grid, s);
 }
 
 }  // namespace
