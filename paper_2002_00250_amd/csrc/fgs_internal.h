@@ -248,8 +248,11 @@ hipError_t pbas_launch_import_quads(uint32_t* quads, int npix, int N, const uint
 // code) and `gsamples` (colour magnitudes m_R, m_G, m_B, 0) in quad planes as above;
 // D[k * npix + p] holds the four channels' d_min of slot k as float4, S their float sums; `last`
 // and `last_g` the pixel's value and magnitudes of the previous frame (pending neighbour writes
-// carry them); gsum[4 * (t mod 3) + j] the sum of frame t's colour magnitudes m_j (frame t adds
-// into its slot, reads frame t-1's and clears frame t+1's).
+// carry them); gsum: slot t mod 3 the sums of frame t's colour magnitudes m_j (frame t adds into
+// its slot, reads frame t-1's and clears frame t+1's), each in kGradSlots parts, words 0..2 of
+// 256-byte lines of their own (workgroup b adds to part b mod kGradSlots: on one line the adds of a
+// frame's 1,200 tiles waited for each other).
+constexpr int kGradSlots = 16, kGradSlotWords = 32;
 struct PbasGradPlanes {
     uint32_t* samples;
     uint32_t* gsamples;

@@ -20,7 +20,9 @@
 // At 114 registers a CU held four: 1,200 tiles were 1.17 rounds.  T, R and S wait in LDS during the
 // slot loop, the candidates' slots share a word, the weights are scalars and the second smallest
 // distance replaces a count and R: 96 registers (forced to that before, spills cost more than the
-// second round, 44.8 us).  N = 16: 39.0 -> 35.7, N = 24: 44.3 -> 42.1, N = 40: 56.9 -> 54.5.
+// second round, 44.8 us).  N = 16: 39.0 -> 35.7, N = 24: 44.3 -> 42.1, N = 40: 56.9 -> 54.5.  With
+// the magnitude sums in 16 lines instead of one, which 3,600 adds a frame waited for: N = 20 38.6 ->
+// 38.1, N = 16 35.7 -> 34.5, N = 8 30.4 -> 25.5.
 #include <cstring>
 
 #include "device_common.h"
@@ -91,9 +93,14 @@ __device__ __forceinline__ uint32_t colour_magnitudes(const uint8_t* rgb, int64_
     return out;
 }
 
+// The word of part `part` of channel j's sum in slot f (frame number mod 3).
+__device__ __forceinline__ int sum_index(uint32_t f, int part, int j) {
+    return ((int)f * kGradSlots + part) * kGradSlotWords + j;
+}
+
 // Adds the block's colour magnitudes to frame t's sums (one 64-bit atomic per channel
 // and block; integer sums, so the order does not matter), and block 0 clears frame
-// t+1's slot, which nothing reads or writes during frame t.
+// t+1's parts, which nothing reads or writes during frame t.
 __device__ __forceinline__ void add_magnitudes(unsigned long long* gsum, uint32_t t, uint32_t mw, bool inside) {
     __shared__ uint32_t part[kBlock / 64][3];
     // two channels per word: a wavefront's sum is at most 64 * 255 < 2^16
@@ -112,9 +119,17 @@ __device__ __forceinline__ void add_magnitudes(unsigned long long* gsum, uint32_
         unsigned long long v = 0;
 #pragma unroll
         for (int w = 0; w < kBlock / 64; ++w) v += part[w][threadIdx.x];
-        if (v) atomicAdd(gsum + 4 * (t % 3u) + threadIdx.x, v);
-        if (blockIdx.x == 0) gsum[4 * (((uint64_t)t + 1u) % 3u) + threadIdx.x] = 0ull;
+        if (v) atomicAdd(gsum + sum_index(t % 3u, (int)(blockIdx.x % kGradSlots), (int)threadIdx.x), v);
     }
+    if (blockIdx.x == 0 && threadIdx.x < 3 * kGradSlots)
+        gsum[sum_index((uint32_t)(((uint64_t)t + 1u) % 3u), (int)threadIdx.x / 3, (int)threadIdx.x % 3)] = 0ull;
+}
+
+// A lane's part of slot f's sums: part s of channel j for lane 16 j + s of the first wavefront.
+__device__ __forceinline__ unsigned long long sum_part(const unsigned long long* gsum, uint32_t f) {
+    static_assert(kGradSlots == 16, "lanes 16 j + s");
+    const int lane = (int)threadIdx.x;
+    return lane < 48 ? gsum[sum_index(f, lane & 15, lane >> 4)] : 0ull;
 }
 
 __device__ __forceinline__ uint32_t frame_word(const PbasGradArgs& a, int x, int y, bool& valid) {
@@ -153,6 +168,7 @@ __global__ __launch_bounds__(kBlock, grad_waves(NMAX)) void pbas_grad_step_kerne
     constexpr int NLO = grad_class_min(NMAX);
     constexpr int NW = PbasLds<NMAX>::NW;
     __shared__ PbasLds<NMAX> sh;
+    __shared__ float weight[3];
     __shared__ float4 park[3][kBlock];  // a lane's T, R and S during the slot loop
     const int tid = threadIdx.x;
     const int tiles_x = (a.W + kTileW - 1) / kTileW;
@@ -171,6 +187,7 @@ __global__ __launch_bounds__(kBlock, grad_waves(NMAX)) void pbas_grad_step_kerne
         for (int w = 0; w < NW; ++w) sh.pend[w * kBlock + tid] = 0u;
         fin = load_fire(a.m.fire[(a.t - 1u) & 1u], x0, y0, a.H, a.W);
     }
+    const unsigned long long sums = tid < 64 ? sum_part(a.m.gsum, (uint32_t)(((uint64_t)a.t + 2u) % 3u)) : 0ull;
     const float4 Tv = a.m.T[p];
     bool valid;
     const uint32_t Iw = frame_word(a, x, y, valid);
@@ -197,14 +214,13 @@ __global__ __launch_bounds__(kBlock, grad_waves(NMAX)) void pbas_grad_step_kerne
     }
     __builtin_amdgcn_sched_barrier(0);
 
-    // weights from the previous frame's magnitude sums
-    float wgt[3];
+    // weights from the previous frame's magnitude sums, by the first wavefront for all
+    if (tid < 64) {
+        unsigned long long sum = sums;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const unsigned long long sum = a.m.gsum[4 * (((uint64_t)a.t + 2u) % 3u) + j];  // frame t-1's slot
+        for (int off = 1; off < kGradSlots; off <<= 1) sum += __shfl_xor(sum, off, 64);
         const float mean = (float)(double)sum / (float)a.npix;
-        wgt[j] = a.c.grad_alpha / fmaxf(mean, 1.0f);
-        wgt[j] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wgt[j])));  // one value per frame
+        if (tid < 48 && (tid & 15) == 0) weight[tid >> 4] = a.c.grad_alpha / fmaxf(mean, 1.0f);
     }
     if (a.apply_pending) {
         __syncthreads();  // bit-words cleared
@@ -230,8 +246,12 @@ __global__ __launch_bounds__(kBlock, grad_waves(NMAX)) void pbas_grad_step_kerne
     park[1][tid] = Rv;
     park[2][tid] = Sv;
     if (a.apply_pending) __syncthreads();  // every write aimed at the tile recorded
-    add_magnitudes(a.m.gsum, a.t, Mw, inside);  // frame t's sums
+    add_magnitudes(a.m.gsum, a.t, Mw, inside);  // frame t's sums; its barrier is the weights' too
     if (!inside) return;
+    float wgt[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j)  // (one value per frame: scalar registers)
+        wgt[j] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(weight[j])));
 
     const float R0[4] = {Rv.x, Rv.y, Rv.z, Rv.w};
 
@@ -473,15 +493,18 @@ __global__ void pbas_grad_sums_kernel(unsigned long long* gsum, uint32_t* canon,
     if (!header_matches(check)) return;
     if (check.header) t = (int64_t)check.header[8];
     const int j = threadIdx.x;  // 0..2
-    const int prev = (int)((t + 2) % 3);
+    const uint32_t prev = (uint32_t)((t + 2) % 3);
     if (to_canon) {
-        const unsigned long long v = t > 0 ? gsum[4 * prev + j] : 0ull;
+        unsigned long long v = 0ull;
+        if (t > 0)
+            for (int s = 0; s < kGradSlots; ++s) v += gsum[sum_index(prev, s, j)];
         canon[2 * j] = (uint32_t)v;
         canon[2 * j + 1] = (uint32_t)(v >> 32);
         return;
     }
     const unsigned long long v = (unsigned long long)canon[2 * j] | ((unsigned long long)canon[2 * j + 1] << 32);
-    for (int s = 0; s < 3; ++s) gsum[4 * s + j] = s == prev && t > 0 ? v : 0ull;
+    for (uint32_t f = 0; f < 3; ++f)
+        for (int s = 0; s < kGradSlots; ++s) gsum[sum_index(f, s, j)] = f == prev && s == 0 && t > 0 ? v : 0ull;
 }
 
 inline unsigned blocks1d(int64_t n) { return (unsigned)((n + 255) / 256); }

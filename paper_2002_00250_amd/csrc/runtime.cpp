@@ -642,7 +642,7 @@ fgs_status fgs_create(fgs_algo algo, int32_t H, int32_t W, const void* params, v
         o_lastg = off;   off += align256(n * 4);
         o_i0 = off;      off += align256(n);
         o_i1 = off;      off += align256(n);
-        o_gsum = off;    off += align256(12 * 8);
+        o_gsum = off;    off += align256(3 * kGradSlots * kGradSlotWords * 8);
     } else {
         const size_t N = (size_t)m->pp.N;
         o_samples = off; off += align256((size_t)((N + 3) & ~3) * n * 4);  // quad planes
