@@ -223,26 +223,9 @@ __global__ __launch_bounds__(256) void pbas_import_kernel(PbasPlanes m, int npix
 
 inline unsigned blocks1d(int n) { return (unsigned)((n + 255) / 256); }
 
-// A launch whose samples and D histories are at least three times the 256 MB Infinity Cache runs 3
-// workgroups per CU: its lines come from HBM in any case, and HBM serves them faster to fewer waves (4
-// models of 1280x720, N = 35: 339.6 -> 334.8 us a launch, N = 40: 368.8 -> 364.1; 3 models, N = 52:
-// 342.2 -> 339.3, N = 64: 389.0 -> 387.2).  Below, more waves pay: 2 models, N = 35, 144.9 -> 150.3;
-// 3 models, N = 24, 184.9 -> 189.6; 1920x1080, N = 35, 168.8 -> 171.3; and so they do for small
-// classes, whose waves each hold fewer bytes in flight (4 models, N = 12: 150.7 -> 181.3).
-constexpr unsigned kStreamLds = 44u << 10;  // with the kernel's own, 3 fit a CU's 160 KiB; nothing is kept there
-constexpr int64_t kStreamBytes = 768ll << 20;
-template <int NB, int NMAX>
-unsigned stream_lds(const PbasBatch<NB>& b) {
-    int64_t bytes = 0;
-    for (int i = 0; i < b.n; ++i) bytes += (int64_t)b.a[i].npix * b.a[i].c.N * 8;
-    return NMAX >= 24 && bytes >= kStreamBytes ? kStreamLds : 0;
-}
-
 template <int NB, int NMAX>
 void launch_step_nt(const PbasBatch<NB>& b, dim3 grid, hipStream_t s) {
-    if (b.a[0].streaming)
-        hipLaunchKernelGGL((pbas_step_kernel<NB, NMAX, true>), grid, dim3(kBlock), (stream_lds<NB, NMAX>(b)), s,
-                           b);
+    if (b.a[0].streaming) hipLaunchKernelGGL((pbas_step_kernel<NB, NMAX, true>), grid, dim3(kBlock), 0, s, b);
     else hipLaunchKernelGGL((pbas_step_kernel<NB, NMAX, false>), grid, dim3(kBlock), 0, s, b);
 }
 
