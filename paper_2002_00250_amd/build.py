@@ -74,6 +74,10 @@ REPORT_KERNELS = [
     ("gmm_kernels.hip", "gmm_step_kernelILi8ELi7ELi3ELb1ELb0ELi1E", "gmm_step_kernel<8,7,3,NT,0,1>"),
     ("pbas_kernels.hip", "pbas_step_kernelILi8ELi36ELb1E", "pbas_step_kernel<8,36,NT>"),
     ("pbas_kernels.hip", "pbas_step_kernelILi1ELi20ELb0E", "pbas_step_kernel<1,20,cached>"),
+    ("pbas_kernels.hip", "pbas_settle_kernelILb1E", "pbas_settle_kernel<export>"),
+    ("pbas_grad_kernels.hip", "pbas_grad_step_kernelILi20ELb0ELb1E", "pbas_grad_step_kernel<20,cached,two>"),
+    ("gmm_window.hip", "gmm_window_forward_kernelILi3ELb1ELb0E", "gmm_window_forward_kernel<3,saved,whole>"),
+    ("gmm_window.hip", "gmm_window_backward_kernelILi3ELb1ELb0E", "gmm_window_backward_kernel<3,saved,whole>"),
     ("serve_kernels.hip", "serve_kernelILi5ELi24ELb0E", "serve_kernel<5,24,cached>"),
     ("serve_kernels.hip", "serve_kernelILi5ELi24ELb1E", "serve_kernel<5,24,NT>"),
     ("eval_kernels.hip", "eval_count_kernel", "eval_count_kernel"),
@@ -128,7 +132,7 @@ def resource_report() -> str:
     ver = subprocess.run([hipcc(), "--version"], capture_output=True, text=True).stdout.splitlines()
     ver = "; ".join(v.strip() for v in ver if "HIP version" in v or "clang version" in v)
     return "\n".join([
-        "# Compiler resource usage of the step, serving, evaluation and median kernels (gfx950)", "",
+        "# Compiler resource usage of the step, window, serving, evaluation and median kernels (gfx950)", "",
         "sources: " + " ".join(paths),
         "sources_sha256_16: " + h.hexdigest()[:16],
         "compiler: " + ver, "",

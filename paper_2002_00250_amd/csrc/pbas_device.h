@@ -346,8 +346,9 @@ __device__ __forceinline__ void pbas_tile_m(const PbasStepArgs& a, int bx, int b
     // distance is below the threshold, so the two smallest are kept: 3 packed instructions
     // for a pair of channels and slot, where a count next to the smallest takes 4, and 5 with
     // the depth lane's cap.  128 fewer VALU instructions of 2,065 at N = 35, the registers the
-    // same.  640x480, N = 20: 20.3 -> 19.6 us a launch, N = 48: 37.6 -> 37.0; 1280x720, N = 35:
-    // 72.1 -> 71.7; four of those, bound by HBM, 334.8 -> 334.2.
+    // same.  640x480, N = 20: 20.3 -> 19.6 us a launch, N = 8: 14.6 -> 14.1, N = 48: 37.6 -> 37.0;
+    // 1280x720, N = 35: 72.1 -> 71.7.  Streaming launches are bound by HBM: four models of
+    // 1280x720, N = 35, with moving objects 207.4 -> 205.6, on a static background 340 either way.
     u16x2 sec_rb = {0xFFFF, 0xFFFF}, sec_gd = {0xFFFF, 0xFFFF};
 #pragma unroll
     for (int k = 0; k < NMAX; ++k) {
