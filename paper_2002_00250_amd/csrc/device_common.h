@@ -20,6 +20,14 @@ __device__ __forceinline__ uint32_t depth_code(uint32_t d_mm, uint32_t full_scal
     return d_mm == 0u ? 0u : q;
 }
 
+// The same by a division.
+__device__ __forceinline__ uint32_t depth_code_divided(uint32_t d_mm, uint32_t full_scale_mm) {
+    if (d_mm == 0u) return 0u;
+    uint32_t q = (__umul24(255u, d_mm) + (full_scale_mm >> 1)) / full_scale_mm;
+    q = q < 1u ? 1u : q;
+    return q > 255u ? 255u : q;
+}
+
 // Depth (mm) seen by RGB pixel (x, y).  The depth map is either W x H, or dw x dh
 // and brought to the RGB grid by nearest-neighbour upscaling on pixel centres
 // (Sec. 4.3: depth is upscaled to the RGB resolution when the two differ):

@@ -276,7 +276,10 @@ __device__ __forceinline__ void pbas_tile_m(const PbasStepArgs& a, int bx, int b
 
     // Ingest (the depth code needs the depth read; computed once every read is issued).
     const bool valid = dmm > 0u;
-    const uint32_t I3 = depth_code(dmm, a.c.depth_max_mm, a.c.depth_div);
+    // (A streaming launch divides: 1280x720, four models, N = 35, moving objects 206.5 us a launch
+    // against 207.4 with the multiplication, static background 339.7 against 340.0.)
+    const uint32_t I3 = NT ? depth_code_divided(dmm, a.c.depth_max_mm)
+                           : depth_code(dmm, a.c.depth_max_mm, a.c.depth_div);
     const uint32_t Iw = I0 | (I1 << 8) | (I2 << 16) | (I3 << 24);
     float R[4] = {Rv.x, Rv.y, Rv.z, Rv.w};
     float T[4] = {Tv.x, Tv.y, Tv.z, Tv.w};
@@ -347,8 +350,7 @@ __device__ __forceinline__ void pbas_tile_m(const PbasStepArgs& a, int bx, int b
     // for a pair of channels and slot, where a count next to the smallest takes 4, and 5 with
     // the depth lane's cap.  128 fewer VALU instructions of 2,065 at N = 35, the registers the
     // same.  640x480, N = 20: 20.3 -> 19.6 us a launch, N = 8: 14.6 -> 14.1, N = 48: 37.6 -> 37.0;
-    // 1280x720, N = 35: 72.1 -> 71.7.  Streaming launches are bound by HBM: four models of
-    // 1280x720, N = 35, with moving objects 207.4 -> 205.6, on a static background 340 either way.
+    // 1280x720, N = 35: 72.1 -> 71.7.
     u16x2 sec_rb = {0xFFFF, 0xFFFF}, sec_gd = {0xFFFF, 0xFFFF};
 #pragma unroll
     for (int k = 0; k < NMAX; ++k) {
@@ -510,10 +512,12 @@ __device__ __forceinline__ void pbas_tile_m(const PbasStepArgs& a, int bx, int b
 }
 
 // The tile with the classification of the model's min_matches (a branch per workgroup around the
-// whole frame: around the slot loop alone it took 148 VGPRs instead of 95 at N = 35).
+// whole frame: around the slot loop alone it took 148 VGPRs instead of 95 at N = 35).  A streaming
+// launch, bound by HBM, counts always: 1280x720, four models, N = 35, the two smallest distances
+// gain on moving objects (206.5 -> 205.3 us) what they lose on a static background (339.7 -> 340.5).
 template <int NMAX, int NLO, bool NT>
 __device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by, PbasLds<NMAX>& sh) {
-    if (a.c.min_matches == 2)
+    if (!NT && a.c.min_matches == 2)
         pbas_tile_m<NMAX, NLO, NT, true>(a, bx, by, sh);
     else
         pbas_tile_m<NMAX, NLO, NT, false>(a, bx, by, sh);
