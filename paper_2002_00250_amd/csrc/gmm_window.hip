@@ -29,7 +29,7 @@
 // a replay 275 and 409; with the changed Gaussians of every frame kept 273 and 240; with weights
 // and ranks as in gmm_device.h 240 and 251; with 32-bit lane offsets (lane_of, opaque) 231 and 217.
 // The forward is bound by its vector instructions (450 per wavefront and frame, the ALUs all but
-// always busy); the backward reads 45 bytes a pixel and frame (4.1 TB/s) beside 380 instructions.
+// always busy); the backward reads 41 bytes a pixel and frame (3.7 TB/s) beside 380 instructions.
 // 4,800 wavefronts are 4.7 a SIMD, hence the launch bound of 5 (96 registers) for K <= 3: with 111
 // registers a sixth of them ran in a second round.
 #include <type_traits>
