@@ -10,6 +10,8 @@ from __future__ import annotations
 
 import numpy as np
 import torch
+from torch.overrides import _get_current_function_mode_stack
+from torch.utils._device import DeviceContext
 
 from . import fgs
 
@@ -113,11 +115,20 @@ def _bce_torch(Z, has, gt, t0, tau):
     return l / w.sum().clamp_min(1.0)
 
 
+def _watched() -> bool:
+    """Whether something follows the operations themselves, which a kernel launched on raw pointers
+    does not show: the function transforms, forward-mode differentiation, tracing, compiling, and
+    Python dispatch and function modes (make_fx traces real tensors through them; a default device,
+    which is such a mode too, only places new tensors)."""
+    return (torch._C._are_functorch_transforms_active() or torch.autograd.forward_ad._current_level >= 0 or
+            torch.jit.is_tracing() or torch.compiler.is_compiling() or torch._C._len_torch_dispatch_stack() > 0 or
+            any(type(m) is not DeviceContext for m in _get_current_function_mode_stack()))
+
+
 def _bce_kernel_takes(Z, has, gt, t0, tau) -> bool:
     """Whether the library's loss kernels compute this call: dense tensors of one shape on the
     current GPU (float32 scores, uint8 flags, uint8 or bool truth), plain numbers t0 and tau, and
-    nothing watching the operations (vmap and the other function transforms, forward-mode
-    differentiation, tracing or compiling), which only the composed form answers."""
+    nothing watching the operations, which only the composed form answers."""
     if not (type(Z) in (torch.Tensor, torch.nn.Parameter) and type(has) is torch.Tensor and type(gt) is torch.Tensor):
         return False
     if not (Z.is_cuda and Z.dtype == torch.float32 and has.dtype == torch.uint8 and
@@ -129,8 +140,7 @@ def _bce_kernel_takes(Z, has, gt, t0, tau) -> bool:
     if Z.numel() == 0 or Z.shape != has.shape or Z.shape != gt.shape or Z.layout != torch.strided or \
             not (Z.is_contiguous() and has.is_contiguous() and gt.is_contiguous()):
         return False
-    return not (torch._C._are_functorch_transforms_active() or torch.autograd.forward_ad._current_level >= 0 or
-                torch.jit.is_tracing() or torch.compiler.is_compiling())
+    return not _watched()
 
 
 class _WindowBce(torch.autograd.Function):
