@@ -98,9 +98,12 @@ fgs_status device_fail(fgs_model* m, hipError_t e, const char* what) {
     } while (0)
 
 // The model's next work goes to stream s: after its last work, wherever that was queued.  Kernels
-// and copies are then queued on m->at.
+// and copies are then queued on m->at.  Only m->stream is known to be the stream that the last work
+// went to where the handles are equal: another handle can stand for one stream per thread
+// (hipStreamPerThread), or for a stream made where a destroyed one was, so the event is waited for
+// there too (an event of the same stream: 0.1 us of the host, push and mask copy at 320x240 21.8 -> 22.0).
 fgs_status run_on(fgs_model* m, hipStream_t s) {
-    if (m->at == s) return FGS_OK;
+    if (m->at == s && s == m->stream) return FGS_OK;
     if (m->at == m->stream) FGS_HIP(m, hipEventRecord(m->done, m->stream));
     FGS_HIP(m, hipStreamWaitEvent(s, m->done, 0));
     m->at = s;
