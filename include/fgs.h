@@ -521,13 +521,21 @@ fgs_status fgs_gmm_window_destroy(fgs_gmm_window* w);
  *   fgs_window_bce_grad  dZ[i] = (sigmoid(x) - y) * w * gloss / max(sum w, 1) / tau; 0 for i < i0
  * All arrays are device memory, dense: Z, dZ float[n]; has, gt uint8[n]; loss, gloss float[1];
  * work double[FGS_WINDOW_BCE_WORK], written by fgs_window_bce and read by the gradient, which
- * must be given the same Z, has, gt, i0, n and tau.  Sums are fp64 in a fixed order
- * (deterministic).  Both run on hip_stream (NULL: the null stream) and return after enqueueing.
+ * must be given the same Z, has, gt, i0, n and tau, unchanged.  fgs_window_bce_keep is fgs_window_bce
+ * and keeps what a gradient needs, slope[i] = (sigmoid(x) - y) * w (float[n]) and weight[i] = w
+ * (uint8[n]), both 0 for i < i0: fgs_window_bce_kept_grad then gives dZ without reading Z, has and
+ * gt again, which the caller may have changed.  Sums are fp64 in a fixed order (deterministic, the
+ * same in both).  All run on hip_stream (NULL: the null stream) and return after enqueueing.
  * INVALID_ARG for NULL or misaligned buffers or i0 outside 0..n-1; DEVICE if a launch fails.
  */
 #define FGS_WINDOW_BCE_WORK 4098
 fgs_status fgs_window_bce(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n,
                           float tau, double* work, float* loss, void* hip_stream);
+fgs_status fgs_window_bce_keep(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n,
+                               float tau, double* work, float* loss, float* slope, uint8_t* weight,
+                               void* hip_stream);
+fgs_status fgs_window_bce_kept_grad(const float* slope, int64_t i0, int64_t n, float tau, const double* work,
+                                    const float* gloss, float* dZ, void* hip_stream);
 fgs_status fgs_window_bce_grad(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n,
                                float tau, const double* work, const float* gloss, float* dZ,
                                void* hip_stream);

@@ -143,41 +143,71 @@ def _bce_kernel_takes(Z, has, gt, t0, tau) -> bool:
     return not _watched()
 
 
+def _bce_forward(Z, has, gt, t0, tau, keep):
+    """The loss and, to keep, the slopes, the weights and the sums."""
+    loss = torch.empty((), dtype=torch.float32, device=Z.device)
+    work = torch.empty(fgs.FGS_WINDOW_BCE_WORK, dtype=torch.float64, device=Z.device)
+    i0 = t0 * (Z.numel() // Z.shape[0])
+    args = Z.data_ptr(), has.data_ptr(), gt.data_ptr(), i0, Z.numel(), tau, work.data_ptr(), loss.data_ptr()
+    stream = torch.cuda.current_stream(Z.device).cuda_stream
+    if not keep:
+        fgs.fgs_window_bce(*args, stream)
+        return loss
+    slope = torch.empty(Z.shape, dtype=torch.float32, device=Z.device)
+    weight = torch.empty(Z.shape, dtype=torch.uint8, device=Z.device)
+    fgs.fgs_window_bce_keep(*args, slope.data_ptr(), weight.data_ptr(), stream)
+    return loss, slope, weight, work, i0
+
+
 class _WindowBce(torch.autograd.Function):
-    """The loss in one pass over the scores, its gradient in another (fgs_window_bce, _grad)."""
+    """loss, slope = apply(Z, has, gt, t0, tau): the loss in one pass over the scores, which keeps its
+    slope (sigmoid(Z / tau) - y) w for the gradient's pass.  Nothing of Z, has and gt is kept: the
+    caller may refill them before the backward.  The slope is an output so that a gradient can be
+    differentiated again (its own slope is p (1 - p) w / tau, p = |slope| / w)."""
 
     @staticmethod
     def forward(ctx, Z, has, gt, t0, tau):
-        loss = torch.empty((), dtype=torch.float32, device=Z.device)
-        work = torch.empty(fgs.FGS_WINDOW_BCE_WORK, dtype=torch.float64, device=Z.device)
-        i0 = t0 * (Z.numel() // Z.shape[0])
-        fgs.fgs_window_bce(Z.data_ptr(), has.data_ptr(), gt.data_ptr(), i0, Z.numel(), tau, work.data_ptr(),
-                           loss.data_ptr(), torch.cuda.current_stream(Z.device).cuda_stream)
-        ctx.save_for_backward(Z, has, gt, work)
-        ctx.i0, ctx.t0, ctx.tau = i0, t0, tau
-        return loss
+        loss, slope, weight, work, i0 = _bce_forward(Z, has, gt, t0, tau, True)
+        ctx.save_for_backward(slope, weight, work)
+        ctx.i0, ctx.tau, ctx.device = i0, tau, Z.device
+        ctx.set_materialize_grads(False)
+        return loss, slope
 
     @staticmethod
-    def backward(ctx, g):
-        Z, has, gt, work = ctx.saved_tensors
-        plain = type(g) is torch.Tensor and g.is_cuda and g.dtype == torch.float32 and g.numel() == 1 and \
-            torch._C._has_storage(g)          # (a batch of gradients has none of its own)
-        if not plain or torch.is_grad_enabled() or torch._C._are_functorch_transforms_active() or \
-                not _bce_kernel_takes(Z, has, gt, ctx.t0, ctx.tau):
-            # a gradient that is itself differentiated, or batched
-            w = has.to(Z.dtype)
-            d = (torch.sigmoid(Z / ctx.tau) - (gt != 0).to(Z.dtype)) * w
-            d = d * (torch.arange(Z.shape[0], device=Z.device) >= ctx.t0).reshape((-1,) + (1,) * (Z.dim() - 1))
-            return d * (g / w[ctx.t0:].sum().clamp_min(1.0)) / ctx.tau, None, None, None, None
-        dZ = torch.empty_like(Z)
-        fgs.fgs_window_bce_grad(Z.data_ptr(), has.data_ptr(), gt.data_ptr(), ctx.i0, Z.numel(), ctx.tau,
-                                work.data_ptr(), g.data_ptr(), dZ.data_ptr(),
-                                torch.cuda.current_stream(Z.device).cuda_stream)
+    def backward(ctx, g, g_slope):
+        slope, weight, work = ctx.saved_tensors
+        if g is not None and g_slope is None and _kept_kernel_takes(ctx, g, slope, work):
+            dZ = torch.empty_like(slope)
+            fgs.fgs_window_bce_kept_grad(slope.data_ptr(), ctx.i0, slope.numel(), ctx.tau, work.data_ptr(),
+                                         g.data_ptr(), dZ.data_ptr(),
+                                         torch.cuda.current_stream(dZ.device).cuda_stream)
+            return dZ, None, None, None, None
+        # a gradient that is itself differentiated, or batched, or watched
+        dZ = None
+        if g is not None:
+            dZ = slope * (g / work[1].to(g.dtype)) / ctx.tau
+        if g_slope is not None:
+            d = g_slope * (slope.abs() - slope * slope / weight.clamp(min=1)) / ctx.tau
+            dZ = d if dZ is None else dZ + d
         return dZ, None, None, None, None
+
+
+def _kept_kernel_takes(ctx, g, slope, work) -> bool:
+    """Whether the library's gradient kernel computes this backward: a plain gradient (a batch of
+    gradients has no storage of its own) and what the forward kept, as it was (a saved-tensor hook
+    may give back something else), on the current GPU."""
+    def same(x, dtype):
+        return type(x) is torch.Tensor and x.device == ctx.device and x.dtype == dtype and x.is_contiguous() and \
+            torch._C._has_storage(x)
+    return ctx.device.index == torch.cuda.current_device() and not torch.is_grad_enabled() and not _watched() and \
+        same(g, torch.float32) and g.numel() == 1 and same(slope, torch.float32) and \
+        same(work, torch.float64) and work.numel() == fgs.FGS_WINDOW_BCE_WORK
 
 
 def window_bce_loss(Z: torch.Tensor, has: torch.Tensor, gt: torch.Tensor, t0: int = 1, tau: float = 1.0):
     """Mean BCE of sigmoid(Z/tau) against 0/255 ground truth over frames t >= t0 where Z has a term."""
-    if _bce_kernel_takes(Z, has, gt, t0, tau):
-        return _WindowBce.apply(Z, has, gt, t0, tau)
-    return _bce_torch(Z, has, gt, t0, tau)
+    if not _bce_kernel_takes(Z, has, gt, t0, tau):
+        return _bce_torch(Z, has, gt, t0, tau)
+    if torch.is_grad_enabled() and Z.requires_grad:
+        return _WindowBce.apply(Z, has, gt, t0, tau)[0]
+    return _bce_forward(Z, has, gt, t0, tau, False)

@@ -164,9 +164,12 @@ hipError_t gmm_window_launch_forward(const GmmWindowArgs& a, int K, hipStream_t 
 hipError_t gmm_window_launch_backward(const GmmWindowArgs& a, int K, hipStream_t s);
 
 // The window's loss (window_loss.hip): scores i0 .. n - 1; work holds 2 + 2 kBceBlocks doubles.
+// slope, weight [n]: kept for window_bce_kept_grad_launch (nullptr: not kept).
 constexpr int kBceBlocks = (FGS_WINDOW_BCE_WORK - 2) / 2;
 hipError_t window_bce_launch(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
-                             double* work, float* loss, hipStream_t s);
+                             double* work, float* loss, float* slope, uint8_t* weight, hipStream_t s);
+hipError_t window_bce_kept_grad_launch(const float* slope, int64_t i0, int64_t n, float tau, const double* work,
+                                       const float* gloss, float* dZ, hipStream_t s);
 hipError_t window_bce_grad_launch(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
                                   const double* work, const float* gloss, float* dZ, hipStream_t s);
 

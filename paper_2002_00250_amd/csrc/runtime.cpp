@@ -1641,15 +1641,42 @@ fgs_status fgs_gmm_window_destroy(fgs_gmm_window* w) {
     return FGS_OK;
 }
 
-fgs_status fgs_window_bce(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
-                          double* work, float* loss, void* hip_stream) {
+namespace {
+
+fgs_status window_bce(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
+                      double* work, float* loss, float* slope, uint8_t* weight, void* hip_stream) {
     if (!Z || !has || !gt || !work || !loss) return fail(FGS_ERR_INVALID_ARG, "NULL argument");
-    if (((uintptr_t)Z & 3) || ((uintptr_t)loss & 3) || ((uintptr_t)work & 7))
+    if (((uintptr_t)Z & 3) || ((uintptr_t)loss & 3) || ((uintptr_t)work & 7) || ((uintptr_t)slope & 3))
         return fail(FGS_ERR_INVALID_ARG, "misaligned device buffer");
     if (i0 < 0 || i0 >= n || n > ((int64_t)1 << 40))
         return fail(FGS_ERR_INVALID_ARG, "bad score range %lld..%lld", (long long)i0, (long long)n);
-    hipError_t e = window_bce_launch(Z, has, gt, i0, n, tau, work, loss, (hipStream_t)hip_stream);
+    hipError_t e = window_bce_launch(Z, has, gt, i0, n, tau, work, loss, slope, weight, (hipStream_t)hip_stream);
     if (e != hipSuccess) return fail(FGS_ERR_DEVICE, "window loss: %s", hipGetErrorString(e));
+    return FGS_OK;
+}
+
+}  // namespace
+
+fgs_status fgs_window_bce(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
+                          double* work, float* loss, void* hip_stream) {
+    return window_bce(Z, has, gt, i0, n, tau, work, loss, nullptr, nullptr, hip_stream);
+}
+
+fgs_status fgs_window_bce_keep(const float* Z, const uint8_t* has, const uint8_t* gt, int64_t i0, int64_t n, float tau,
+                               double* work, float* loss, float* slope, uint8_t* weight, void* hip_stream) {
+    if (!slope || !weight) return fail(FGS_ERR_INVALID_ARG, "NULL argument");
+    return window_bce(Z, has, gt, i0, n, tau, work, loss, slope, weight, hip_stream);
+}
+
+fgs_status fgs_window_bce_kept_grad(const float* slope, int64_t i0, int64_t n, float tau, const double* work,
+                                    const float* gloss, float* dZ, void* hip_stream) {
+    if (!slope || !work || !gloss || !dZ) return fail(FGS_ERR_INVALID_ARG, "NULL argument");
+    if (((uintptr_t)slope & 3) || ((uintptr_t)gloss & 3) || ((uintptr_t)dZ & 3) || ((uintptr_t)work & 7))
+        return fail(FGS_ERR_INVALID_ARG, "misaligned device buffer");
+    if (i0 < 0 || i0 >= n || n > ((int64_t)1 << 40))
+        return fail(FGS_ERR_INVALID_ARG, "bad score range %lld..%lld", (long long)i0, (long long)n);
+    hipError_t e = window_bce_kept_grad_launch(slope, i0, n, tau, work, gloss, dZ, (hipStream_t)hip_stream);
+    if (e != hipSuccess) return fail(FGS_ERR_DEVICE, "window loss gradient: %s", hipGetErrorString(e));
     return FGS_OK;
 }
 

@@ -127,6 +127,10 @@ def _load():
         "fgs_gmm_window_destroy": (S, [c_void_p]),
         "fgs_window_bce": (S, [c_void_p, c_void_p, c_void_p, c_int64, c_int64, ctypes.c_float, c_void_p, c_void_p,
                                c_void_p]),
+        "fgs_window_bce_keep": (S, [c_void_p, c_void_p, c_void_p, c_int64, c_int64, ctypes.c_float, c_void_p,
+                                    c_void_p, c_void_p, c_void_p, c_void_p]),
+        "fgs_window_bce_kept_grad": (S, [c_void_p, c_int64, c_int64, ctypes.c_float, c_void_p, c_void_p, c_void_p,
+                                         c_void_p]),
         "fgs_window_bce_grad": (S, [c_void_p, c_void_p, c_void_p, c_int64, c_int64, ctypes.c_float, c_void_p,
                                     c_void_p, c_void_p, c_void_p]),
         "fgs_server_now": (ctypes.c_double, []),
@@ -425,6 +429,18 @@ def fgs_window_bce(Z: int, has: int, gt: int, i0: int, n: int, tau: float, work:
                    hip_stream: int | None = None) -> None:
     _check(_load().fgs_window_bce(c_void_p(Z), c_void_p(has), c_void_p(gt), i0, n, tau, c_void_p(work),
                                   c_void_p(loss), c_void_p(hip_stream or 0)))
+
+
+def fgs_window_bce_keep(Z: int, has: int, gt: int, i0: int, n: int, tau: float, work: int, loss: int, slope: int,
+                        weight: int, hip_stream: int | None = None) -> None:
+    _check(_load().fgs_window_bce_keep(c_void_p(Z), c_void_p(has), c_void_p(gt), i0, n, tau, c_void_p(work),
+                                       c_void_p(loss), c_void_p(slope), c_void_p(weight), c_void_p(hip_stream or 0)))
+
+
+def fgs_window_bce_kept_grad(slope: int, i0: int, n: int, tau: float, work: int, gloss: int, dZ: int,
+                             hip_stream: int | None = None) -> None:
+    _check(_load().fgs_window_bce_kept_grad(c_void_p(slope), i0, n, tau, c_void_p(work), c_void_p(gloss),
+                                            c_void_p(dZ), c_void_p(hip_stream or 0)))
 
 
 def fgs_window_bce_grad(Z: int, has: int, gt: int, i0: int, n: int, tau: float, work: int, gloss: int, dZ: int,
