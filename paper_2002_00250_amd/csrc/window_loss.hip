@@ -2,8 +2,8 @@
 // weighted by the term flags, and its gradient with respect to Z.  Composed of elementwise
 // operations it takes some fifteen passes over the scores (64 frames of 640x480: about 600 us of
 // a training step, as much as the window's two kernels).  Here, back to back on that window: the loss
-// alone is one pass that reads 6 bytes a score (24.6 us, 4.8 TB/s, bound by some 50 vector
-// instructions a score); with a gradient to follow it also writes 5 (37.8 us, 5.7 TB/s), and the
+// alone is one pass that reads 6 bytes a score (29.5 us, 4.0 TB/s, bound by some 60 vector
+// instructions a score); with a gradient to follow it also writes 5 (39.4 us, 5.5 TB/s), and the
 // gradient's pass reads 4 and writes 4 (24.3 us, 6.5 TB/s, the copy rate).  A gradient from Z, has
 // and gt themselves, 26.3 + 28.6 us, needs them unchanged until the backward.
 //
@@ -75,20 +75,21 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double (*sh)[2]
         }
 }
 
-// log(1 + e) for 0 <= e <= 1 to about 2 ulp: log(1 + e) = 2 atanh(s), s = e / (2 + e) <= 1/3, by
-// its series to s^17 (the library's log1p serves every argument at three times the
-// instructions: the pass took 67 us with it).
+// log(1 + e) for 0 <= e <= 1 to 0.63 ulp (over all of it, with a reciprocal up to an ulp off):
+// log(1 + e) = 2 atanh(s), s = e / (2 + e) <= 1/3, with s in two parts (2 + e and the quotient
+// corrected by what their rounding lost) and (2 atanh(s) / s - 2) / s^2 by its Chebyshev interpolation
+// of degree 4 in s^2 on [0, 1/9], 2e-8 off at most.  The quotient in one part and a series gave 2.4 to
+// 3.7 ulp; the library's log1p, which serves every argument, three times the instructions.
 __device__ __forceinline__ float log1p_unit(float e) {
-    const float s = e * __builtin_amdgcn_rcpf(2.0f + e), q = s * s;
-    float p = 2.0f / 17.0f;
-    p = __builtin_fmaf(p, q, 2.0f / 15.0f);
-    p = __builtin_fmaf(p, q, 2.0f / 13.0f);
-    p = __builtin_fmaf(p, q, 2.0f / 11.0f);
-    p = __builtin_fmaf(p, q, 2.0f / 9.0f);
-    p = __builtin_fmaf(p, q, 2.0f / 7.0f);
-    p = __builtin_fmaf(p, q, 2.0f / 5.0f);
-    p = __builtin_fmaf(p, q, 2.0f / 3.0f);
-    return __builtin_fmaf(s * q, p, s + s);
+    const float t = 2.0f + e, te = e - (t - 2.0f), r = __builtin_amdgcn_rcpf(t), s0 = e * r;
+    const float lo = __builtin_fmaf(-s0, te, __builtin_fmaf(-s0, t, e)) * r;
+    const float s = s0 + lo, q = s * s;
+    float p = 0.2322433f;
+    p = __builtin_fmaf(p, q, 0.21706575f);
+    p = __builtin_fmaf(p, q, 0.28592357f);
+    p = __builtin_fmaf(p, q, 0.39999706f);
+    p = __builtin_fmaf(p, q, 0.6666667f);
+    return (s0 + s0) + __builtin_fmaf(s, q * p, lo + lo);
 }
 
 // sigmoid(x) by e = exp(-|x|): 1 / (1 + e) or e / (1 + e), the quotient corrected by its remainder.
