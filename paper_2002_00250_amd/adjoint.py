@@ -49,6 +49,14 @@ class GmmWindow:
                 or not depth.is_contiguous():
             raise ValueError("depth must be a contiguous 16-bit tensor [T, H, W]")
 
+    @staticmethod
+    def _used_on(cur, *tensors):
+        """`cur`, the current stream, waits for the window's from here on, so that memory taken from it
+        is reused only behind the kernel.  A tensor made on another stream is marked as used on `cur`:
+        its own stream does not wait for the kernel."""
+        for x in tensors:
+            x.record_stream(cur)              # (nothing to do for a tensor of `cur` itself)
+
     def forward(self, theta: torch.Tensor, rgb: torch.Tensor, depth: torch.Tensor):
         self._check(rgb, depth)
         theta = theta.detach().to(torch.float32).contiguous()
@@ -58,9 +66,8 @@ class GmmWindow:
         self._order.enter(cur)
         fgs.fgs_gmm_window_forward(self.handle, theta.data_ptr(), rgb.data_ptr(), depth.data_ptr(),
                                    Z.data_ptr(), has.data_ptr())
-        # The current stream waits for the window's here, so the tensors' memory is free for work
-        # queued after this call only once the kernel is done with it (no record_stream needed).
         self._order.leave(cur)
+        self._used_on(cur, theta, rgb, depth)
         self.forwards += 1
         return Z, has
 
@@ -73,7 +80,8 @@ class GmmWindow:
         self._order.enter(cur)
         fgs.fgs_gmm_window_backward(self.handle, theta.data_ptr(), rgb.data_ptr(), depth.data_ptr(),
                                     dZ.data_ptr(), out.data_ptr())
-        self._order.leave(cur)                # (as in forward)
+        self._order.leave(cur)
+        self._used_on(cur, theta, rgb, depth, dZ)
         return out
 
     def records(self) -> np.ndarray:
