@@ -130,6 +130,7 @@ def _watched() -> bool:
     which is such a mode too, only places new tensors)."""
     return (torch._C._are_functorch_transforms_active() or torch.autograd.forward_ad._current_level >= 0 or
             torch.jit.is_tracing() or torch.compiler.is_compiling() or torch._C._len_torch_dispatch_stack() > 0 or
+            torch._C._len_torch_function_stack() > 0 and
             any(type(m) is not DeviceContext for m in _get_current_function_mode_stack()))
 
 
@@ -161,8 +162,7 @@ def _bce_forward(Z, has, gt, t0, tau, keep):
     if not keep:
         fgs.fgs_window_bce(*args, stream)
         return loss
-    slope = torch.empty(Z.shape, dtype=torch.float32, device=Z.device)
-    weight = torch.empty(Z.shape, dtype=torch.uint8, device=Z.device)
+    slope, weight = torch.empty_like(Z), torch.empty_like(has)
     fgs.fgs_window_bce_keep(*args, slope.data_ptr(), weight.data_ptr(), stream)
     return loss, slope, weight, work, i0
 
