@@ -407,13 +407,16 @@ fgs_status static_after_push(fgs_model* m) {
     return FGS_OK;
 }
 
-// A mask plane of the model to the caller's rows.  Host rows are reached through pinned memory
-// that the copy kernel writes: a copy of rows straight to pageable memory goes row by row (3.3 ms
-// for 480 rows of 640 bytes).  At most kMaskStage bytes are pinned; larger planes go in parts.
+// A mask plane of the model to the caller's rows.  Pageable host rows are reached through pinned
+// memory that the copy kernel writes: a copy of rows straight to pageable memory goes row by row (3.3 ms
+// for 480 rows of 640 bytes, 7.4 ms for 1080 of 1920, against 26 and 118 us).  At most kMaskStage bytes
+// are pinned; larger planes go in parts.  Rows that the caller has pinned take the runtime's copy where
+// they are of whole words (14 and 47 us); it goes row by row through others (3.1 and 7.7 ms).
 constexpr size_t kMaskStage = (size_t)16 << 20;
 
-// What the runtime knows of a caller's pointer: device memory (and whose), or nothing.
-enum class Place { kUnknown, kThisDevice, kOtherDevice };
+// What the runtime knows of a caller's pointer: device memory (and whose), pinned or managed memory, or
+// nothing.
+enum class Place { kUnknown, kHost, kThisDevice, kOtherDevice };
 Place place_of(const void* p, int device) {
     hipPointerAttribute_t at;
     std::memset(&at, 0, sizeof at);
@@ -421,6 +424,7 @@ Place place_of(const void* p, int device) {
         (void)hipGetLastError();
         return Place::kUnknown;
     }
+    if (at.type == hipMemoryTypeHost || at.type == hipMemoryTypeManaged) return Place::kHost;
     if (at.type != hipMemoryTypeDevice) return Place::kUnknown;
     return at.device == device ? Place::kThisDevice : Place::kOtherDevice;
 }
@@ -442,8 +446,8 @@ fgs_status read_plane(fgs_model* m, const uint8_t* plane, uint8_t* out, int64_t 
     if (where != FGS_MEM_HOST && where != FGS_MEM_DEVICE)
         return fail(FGS_ERR_INVALID_ARG, "bad memory kind %d", (int)where);
     const int64_t n = m->npix, W = m->W;
-    // The runtime's own copy, which checks what it is given: for memory that is not where `where`
-    // says, of another device or shorter than the rows, and where no memory can be pinned.
+    // The runtime's own copy, which checks what it is given: for pinned and managed rows, for memory that
+    // is not where `where` says, of another device or shorter than the rows, and where none can be pinned.
     auto copy = [&](hipMemcpyKind kind) {
         FGS_HIP(m, hipMemcpy2DAsync(out, (size_t)stride, plane, (size_t)W, (size_t)W, (size_t)m->H, kind, m->at));
         if (where == FGS_MEM_HOST) FGS_HIP(m, hipStreamSynchronize(m->at));
@@ -455,7 +459,9 @@ fgs_status read_plane(fgs_model* m, const uint8_t* plane, uint8_t* out, int64_t 
         FGS_HIP(m, mask_launch_copy(plane, m->W, out, stride, 0, n, m->at));
         return FGS_OK;
     }
-    if (place_of(out, m->device) != Place::kUnknown) return copy(hipMemcpyDeviceToHost);
+    const Place place = place_of(out, m->device);
+    const bool words = (((uintptr_t)out | (uintptr_t)stride | (uintptr_t)W) & 3) == 0;
+    if (place != Place::kUnknown && (place != Place::kHost || words)) return copy(hipMemcpyDeviceToHost);
     if (!m->mask_stage) {
         const size_t bytes = std::min((size_t)n, kMaskStage);
         if (hipHostMalloc((void**)&m->mask_stage, bytes, hipHostMallocDefault) != hipSuccess) {
