@@ -87,7 +87,29 @@ __device__ __forceinline__ uint4 merge_quad(uint4 v, uint32_t val, uint32_t bits
                       (v.w & ~b3) | (val & b3));
 }
 
-template <bool EXPORT>
+// The writes into pixel p looked up by its own lane: each of its 8 neighbours that fired recomputes its
+// draws and counts if it aimed the opposite way, 7 - d (the direction table is point symmetric).
+__device__ __forceinline__ void pull_fired(PbasLds<64>& sh, const uint8_t* fire, int x, int y, int H, int W, int N,
+                                           uint32_t t_prev, uint32_t k0, uint32_t k1) {
+    for (int d = 0; d < 8; ++d) {
+        const int qx = x + nb_dx(d), qy = y + nb_dy(d);
+        if (qx < 0 || qx >= W || qy < 0 || qy >= H) continue;
+        const uint32_t fb = fire[(int64_t)qy * W + qx] & 0xFu;  // (the high nibble: R flags)
+        if (fb == 0u) continue;
+        const U32x4 w1 = philox4x32_10((uint32_t)(qy * W + qx), t_prev, 1u, 0u, k0, k1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            int dq, slot;
+            intent_of(w1.v[j], N, dq, slot);
+            if (((fb >> j) & 1u) && dq == 7 - d)
+                sh.pend[(slot >> 3) * kBlock + threadIdx.x] |= 1u << (8 * j + (slot & 7));
+        }
+    }
+}
+
+// TILED: workgroups 0 .. tiles - 1 take the step's tiles; else 256 consecutive pixels each (frames
+// that fill too little of their tiles, settle_of).
+template <bool EXPORT, bool TILED>
 __global__ __launch_bounds__(kBlock) void pbas_settle_kernel(PbasPlanes m, int H, int W, int N, int apply,
                                                              uint32_t t_prev, uint32_t k0, uint32_t k1, int tiles_x,
                                                              int tiles, uint32_t* __restrict__ out, int wide,
@@ -102,22 +124,29 @@ __global__ __launch_bounds__(kBlock) void pbas_settle_kernel(PbasPlanes m, int H
             return;
         }
     }
-    const int x0 = ((int)blockIdx.x % tiles_x) * kTileW, y0 = ((int)blockIdx.x / tiles_x) * kTileH;
+    const int x0 = TILED ? ((int)blockIdx.x % tiles_x) * kTileW : 0, y0 = TILED ? ((int)blockIdx.x / tiles_x) * kTileH : 0;
     const int lx = tid % kTileW, ly = tid / kTileW;
-    const bool inside = x0 + lx < W && y0 + ly < H;
-    const int64_t p = inside ? (int64_t)(y0 + ly) * W + x0 + lx : (int64_t)y0 * W + x0;
+    const int64_t first = TILED ? (int64_t)y0 * W + x0 : (int64_t)blockIdx.x * kBlock;
+    const bool inside = TILED ? x0 + lx < W && y0 + ly < H : first + tid < n;
+    const int64_t p = !inside ? first : TILED ? (int64_t)(y0 + ly) * W + x0 + lx : first + tid;
     const int nq = (N + 3) / 4;
     uint4* quads = reinterpret_cast<uint4*>(m.samples);
     QuadBatch b;
     if (EXPORT) b = load_quads(quads, n, p, 0, nq);  // on their way during the scatter
     uint32_t lastw = 0u;
     if (apply) {
-        const FireIn fin = load_fire(m.fire[t_prev & 1u], x0, y0, H, W);
+        FireIn fin;
+        if (TILED) fin = load_fire(m.fire[t_prev & 1u], x0, y0, H, W);
         lastw = m.last_in_pad ? *reinterpret_cast<const uint32_t*>(sample_byte(m.samples, n, N, (int)p, 0)) : m.last[p];
         for (int w = 0; w < (N + 7) / 8; ++w) sh.pend[w * kBlock + tid] = 0u;
-        __syncthreads();
-        scatter_fired<64>(sh, fin, N, t_prev, k0, k1);
-        __syncthreads();
+        if (TILED) {
+            __syncthreads();
+            scatter_fired<64>(sh, fin, N, t_prev, k0, k1);
+            __syncthreads();
+        } else {  // (each lane its own words)
+            const int y = (int)p / W;
+            pull_fired(sh, m.fire[t_prev & 1u], (int)p - y * W, y, H, W, N, t_prev, k0, k1);
+        }
     }
     if (!inside) return;
     const uint32_t keep = (lastw >> 24) != 0u ? 0xFFFFFFFFu : 0x00FFFFFFu;  // depth at t_prev?
@@ -329,31 +358,52 @@ namespace {
 int64_t copy_blocks(int64_t words) { return (words + kCopyWords - 1) / kCopyWords; }
 bool wide_copy(const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; }
 
+// Workgroups of a settle launch: tiles (each fire byte read once, an LDS scatter) where the frame fills
+// at least 3/8 of them, else consecutive pixels (eight fire bytes each).  307,200 pixels, N = 20, export
+// and flush in us with their calls, by tiles: 640 wide 30.1 and 26.0, 24 wide (3/8) 31.7 and 27.6, 16 wide
+// 35.8 and 29.1, 5 wide 68.3 and 51.6; by pixels 31.9 to 32.4 and 28.7 to 29.2 at every width.
+struct Settle {
+    bool tiled;
+    int tiles_x;
+    int64_t groups;
+};
+Settle settle_of(int H, int W) {
+    const int tiles_x = (W + kTileW - 1) / kTileW;
+    const int64_t tiles = (int64_t)tiles_x * ((H + kTileH - 1) / kTileH), n = (int64_t)H * W;
+    const bool tiled = 8 * n >= 3 * tiles * kTileW * kTileH;
+    return Settle{tiled, tiles_x, tiled ? tiles : (n + kBlock - 1) / kBlock};
+}
+
+template <bool EXPORT>
+hipError_t launch_settle(const PbasPlanes& m, int H, int W, bool apply, uint32_t t_prev, const PbasConsts& c, uint32_t* out,
+                         int wide, const StateWords* header, hipStream_t s) {
+    const Settle l = settle_of(H, W);
+    const int64_t grid = l.groups + (EXPORT ? copy_blocks((int64_t)H * W * c.N) : 0);
+    if (grid > 0x7fffffff) return hipErrorInvalidValue;
+    const StateWords h = header ? *header : StateWords();
+    if (l.tiled)
+        hipLaunchKernelGGL((pbas_settle_kernel<EXPORT, true>), dim3((unsigned)grid), dim3(kBlock), 0, s, m, H, W, c.N,
+                           apply ? 1 : 0, t_prev, c.key0, c.key1, l.tiles_x, (int)l.groups, out, wide, header ? 1 : 0, h);
+    else
+        hipLaunchKernelGGL((pbas_settle_kernel<EXPORT, false>), dim3((unsigned)grid), dim3(kBlock), 0, s, m, H, W, c.N,
+                           apply ? 1 : 0, t_prev, c.key0, c.key1, l.tiles_x, (int)l.groups, out, wide, header ? 1 : 0, h);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t pbas_launch_flush(const PbasPlanes& m, int H, int W, uint32_t t_prev, const PbasConsts& c,
                              hipStream_t s) {
-    const int tiles_x = (W + kTileW - 1) / kTileW;
-    const int64_t tiles = (int64_t)tiles_x * ((H + kTileH - 1) / kTileH);
-    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(pbas_settle_kernel<false>, dim3((unsigned)tiles), dim3(kBlock), 0, s, m, H, W, c.N, 1, t_prev,
-                       c.key0, c.key1, tiles_x, (int)tiles, (uint32_t*)nullptr, 0, 0, StateWords());
-    return hipGetLastError();
+    return launch_settle<false>(m, H, W, true, t_prev, c, nullptr, 0, nullptr, s);
 }
 
 // Canonical payload: samples[N] u32, dhist[N] u32, R[4] f32, T[4] f32, S[4] u16
 // (out and in are 4-byte aligned device buffers).
 hipError_t pbas_launch_export(const PbasPlanes& m, int H, int W, bool pending, uint32_t t_prev, const PbasConsts& c,
                               uint8_t* out, const StateWords* header, hipStream_t s) {
-    const int tiles_x = (W + kTileW - 1) / kTileW;
-    const int64_t tiles = (int64_t)tiles_x * ((H + kTileH - 1) / kTileH), words = (int64_t)H * W * c.N;
-    const int64_t grid = tiles + copy_blocks(words);
-    if (grid > 0x7fffffff) return hipErrorInvalidValue;
     uint32_t* o = reinterpret_cast<uint32_t*>(out);
-    hipLaunchKernelGGL(pbas_settle_kernel<true>, dim3((unsigned)grid), dim3(kBlock), 0, s, m, H, W, c.N,
-                       pending ? 1 : 0, t_prev, c.key0, c.key1, tiles_x, (int)tiles, o,
-                       wide_copy(m.dhist, o + words) ? 1 : 0, header ? 1 : 0, header ? *header : StateWords());
-    return hipGetLastError();
+    const bool wide = wide_copy(m.dhist, o + (int64_t)H * W * c.N);
+    return launch_settle<true>(m, H, W, pending, t_prev, c, o, wide ? 1 : 0, header, s);
 }
 
 hipError_t pbas_launch_import(const PbasPlanes& m, int npix, int N, const uint8_t* in, const StateCheck& check,
