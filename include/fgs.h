@@ -484,16 +484,20 @@ fgs_status fgs_set_cache_policy(fgs_model* m, int32_t policy);
  * D > 0; Z_t = 0 and has_term = 0 where neither exists) -- the quantity the mask
  * thresholds at zero.  fgs_gmm_window_forward records the discrete choices of
  * every step (background Gaussian attaining delta, matched Gaussian or
- * replacement, variance floor, ranking) and checkpoints the means and variances
- * every `checkpoint_every` frames.  fgs_gmm_window_backward holds those choices
- * fixed and returns dtheta[i] = sum over t, pixels of dZ[t] * dZ_t/dtheta_i,
- * replaying each segment from its checkpoint; the sum is reduced in a fixed
- * order (deterministic).
+ * replacement, variance floor, ranking); fgs_gmm_window_backward holds those choices
+ * fixed and returns dtheta[i] = sum over t, pixels of dZ[t] * dZ_t/dtheta_i, reduced in a
+ * fixed order (deterministic).
+ *
+ * `checkpoint_every` (>= 1) bounds the window's memory: per pixel 8 T bytes of records and
+ * 24 K (ceil(T / E) + E), E = min(checkpoint_every, T), for states and what the steps changed
+ * (block sums and flags, under 1 byte a pixel, aside).  Within that the library keeps what
+ * every step changed, or else what those of one segment of frames changed and replays the
+ * segments before it from checkpoints; scores and gradients do not depend on it.
  *
  * All arrays are device memory, dense, in the window's stream order:
  * theta float[3]; rgb uint8[T][H][W][3]; depth uint16[T][H][W]; Z float[T][H][W];
  * has_term uint8[T][H][W]; dZ float[T][H][W]; dtheta double[3].  A window holds the
- * records and checkpoints of its most recent forward only: backward differentiates that
+ * records and states of its most recent forward only: backward differentiates that
  * forward, so it must be given the same theta and frames, unchanged since (a caller that
  * runs several forwards on one window reruns the one it differentiates first).  `hip_stream` as in
  * fgs_create.  Errors: INVALID_ARG, UNSUPPORTED (K, or rho_mode, decision or var_mode

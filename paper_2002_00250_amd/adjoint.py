@@ -17,8 +17,9 @@ from . import fgs
 
 
 class GmmWindow:
-    """Device buffers (records, checkpoints, scratch) for T frames of H x W.  The records and
-    checkpoints belong to the most recent forward; ``forwards`` counts them."""
+    """Device buffers (records, checkpoints, scratch) for T frames of H x W, bounded by
+    ``checkpoint_every`` (fgs_gmm_window_create).  The records and checkpoints belong to the most
+    recent forward; ``forwards`` counts them."""
 
     def __init__(self, T: int, H: int, W: int, params=None, checkpoint_every: int = 16, device=None):
         self.T, self.H, self.W = T, H, W

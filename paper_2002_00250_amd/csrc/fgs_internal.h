@@ -135,8 +135,8 @@ hipError_t gmm_launch_import(float4* state, const float* in, int Kc, int Kd, int
                              const StateCheck& check, hipStream_t s);
 
 // --------------------------------------------------------- GMM adjoint ----
-// A window of T frames from a fresh model; checkpoints every E frames.  Frames
-// are dense device arrays rgb[T][npix][3], depth[T][npix].  Snapshot planes hold
+// A window of T frames from a fresh model, in nseg segments: the last ones E frames each, the first what
+// is left.  Frames are dense device arrays rgb[T][npix][3], depth[T][npix].  Snapshot planes hold
 // means and variances only (6K floats per pixel).
 struct GmmWindowArgs {
     int32_t T, H, W, npix, E, nseg;
@@ -147,16 +147,20 @@ struct GmmWindowArgs {
     float* Z;               // [T][npix] pre-update scores (0 where no term)
     uint8_t* has;           // [T][npix] 1 where Z has a term
     uint64_t* rec;          // [T][npix] recorded discrete choices
-    int32_t saved;          // 1: scratch holds every frame, written by the forward
-    float* ckpt;            // [nseg][6K][npix]; saved: [6K][npix], before the last frame
-    float* scratch;         // [rows][npix] float4, then [rows][npix] float2, rows = E (saved: T)
+    float* ckpt;            // [nseg][6K][npix]: 0: before the last frame, i: before segment i's first
+    float* scratch;         // [E][npix] float4, then [E][npix] float2: a segment's changed Gaussians
+    uint32_t* kept;         // [blocks] 1: the last segment's are there from the forward (keeps)
     const float* dZ;        // [T][npix]
     double* partial;        // [blocks][3]
     double* dtheta;         // [3]
     __host__ __device__ float4* scratch4() const { return reinterpret_cast<float4*>(scratch); }
-    __host__ __device__ float2* scratch2() const {
-        return reinterpret_cast<float2*>(scratch + 4 * (int64_t)(saved ? T : E) * npix);
-    }
+    __host__ __device__ float2* scratch2() const { return reinterpret_cast<float2*>(scratch + 4 * (int64_t)E * npix); }
+    // Whether the forward keeps what the last segment's steps changed: where that is half the window or
+    // more (a smaller part costs the forward as much as it saves the backward).
+    __host__ __device__ bool keeps() const { return nseg <= 2; }
+    __host__ __device__ int first_of(int seg) const { return seg == 0 ? 0 : T - (nseg - seg) * E; }
+    // (a kept last segment of one frame begins before the last frame)
+    __host__ __device__ int ckpt_of(int seg) const { return keeps() && E == 1 && seg == nseg - 1 ? 0 : seg; }
 };
 bool gmm_window_supported(int K);
 int gmm_window_blocks(int K, int npix);  // of the backward: rows of `partial`

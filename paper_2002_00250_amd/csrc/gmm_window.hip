@@ -9,25 +9,28 @@
 // Forward: one lane per pixel runs all T frames with the state in registers,
 // writing Z_t, the term flags, a 64-bit record of the step's discrete choices
 // (argmin of delta, matched Gaussian or replacement, variance floor, ranking)
-// for both mixtures, and a checkpoint of the means and variances every E frames.
+// for both mixtures, the means and variances before each segment of frames but the
+// first and before the last frame, and what the last segment's steps changed.
 //
 // Backward: with the recorded choices held fixed the weights reach Z only through
 // discrete choices, so their adjoints vanish; alpha's gradient flows through the
 // matched Gaussian's mean and variance updates.  A step changes one Gaussian of each
 // mixture and reorders them, so the reverse sweep undoes it from the recorded ranking and
 // the changed Gaussian's mean and variance before the step (16 bytes of the colour mixture,
-// 8 of the depth mixture).  Where the memory allows (SAVED) the forward keeps those for every
-// frame, beside the state before the last frame.  Otherwise it keeps checkpoints, and each
-// lane walks the segments in reverse: it replays a segment's means and variances from its
-// checkpoint (the forward's operations, so the same values) into a scratch buffer of the
-// same 24 bytes a frame, then sweeps it.  Per-lane gradients accumulate in fp64 and are
-// reduced in a fixed order (wavefront and block tree, then one block over the block
-// partials), so the result is deterministic.
+// 8 of the depth mixture).  The forward has kept those of the last segment where that is the whole
+// window (ALL) or one of two segments.  For the others each lane replays the
+// segment's means and variances from its checkpoint (the forward's operations, so the same
+// values) into the same buffer, then sweeps it; a backward after that replays the last segment too
+// (`kept`, in device memory: a captured backward may run again without its forward).  Per-lane
+// gradients accumulate in fp64 and are reduced in a fixed order (wavefront and block tree, then
+// one block over the block partials), so the result is deterministic.
 //
 // Measured, 64 frames of 640x480, K = 3 (forward, backward): with the whole state stored to
 // scratch per frame (72 bytes a pixel and frame) 310 and 657 us; with the changed Gaussians and
 // a replay 275 and 409; with the changed Gaussians of every frame kept 273 and 240; with weights
 // and ranks as in gmm_device.h 240 and 251; with 32-bit lane offsets (lane_of, opaque) 231 and 217.
+// That takes 2,120 bytes a pixel; within the 1,952 that checkpoint_every = 16 asks for, 54 frames are
+// kept and 10 replayed: 237 and 222 (both passes 459 us against 434).
 // The forward is bound by its vector instructions (450 per wavefront and frame, the ALUs all but
 // always busy); the backward reads 41 bytes a pixel and frame (3.7 TB/s) beside 380 instructions.
 // 4,800 wavefronts are 4.7 a SIMD, hence the launch bound of 5 (96 registers) for K <= 3: with 111
@@ -133,7 +136,7 @@ __device__ __forceinline__ Input input_of(const GmmWindowArgs& a, const Raw& raw
 // SPLIT: the mixtures of a pixel run on two wavefronts of a workgroup of 128 pixels, the depth
 // mixture's handing its term to the colour mixture's through LDS once a frame.  A small window
 // leaves SIMDs idle while each wavefront walks its chain of T frames through both mixtures.
-template <int K, bool SAVED, bool SPLIT>
+template <int K, bool ALL, bool SPLIT>
 __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_kernel(GmmWindowArgs a) {
     constexpr int kPixels = SPLIT ? kBlock / 2 : kBlock;
     __shared__ float term_of[SPLIT ? 2 : 1][SPLIT ? kPixels : 1];  // by frame parity: w_d (delta_d - lambda^2)
@@ -160,25 +163,29 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_ker
         md.v[k] = a.c.v_init_d;
     }
     const int64_t F = 6 * K;
+    auto snapshot = [&](int slot, uint32_t up) __attribute__((always_inline)) {
+        if (!inside) return;
+        MV<K> s;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) s.muc[k][c] = mc.mu[k][c];
+            s.vc[k] = mc.v[k];
+            s.mud[k] = md.mu[k][0];
+            s.vd[k] = md.v[k];
+        }
+        store_mv<K>(s, a.ckpt + (int64_t)slot * F * a.npix, a.npix, up, do_c, do_d);
+    };
+    const int kept_from = ALL ? 0 : a.keeps() ? a.T - a.E : a.T;
     Raw next = read_input(a, 0, p);
-#pragma unroll 1
-    for (int t = 0, e = 0; t < a.T; ++t, e = e + 1 == a.E ? 0 : e + 1) {
+    auto frame = [&](int t, auto keep) __attribute__((always_inline)) {
+        constexpr bool KEEP = decltype(keep)::value;
         const Raw raw = next;
         const uint32_t up = opaque(p);
         next = read_input(a, min(t + 1, a.T - 1), up);
         __builtin_amdgcn_sched_barrier(0);
-        if ((SAVED ? t + 1 == a.T : e == 0) && inside) {
-            MV<K> s;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) s.muc[k][c] = mc.mu[k][c];
-                s.vc[k] = mc.v[k];
-                s.mud[k] = md.mu[k][0];
-                s.vd[k] = md.v[k];
-            }
-            store_mv<K>(s, a.ckpt + (int64_t)(SAVED ? 0 : t / a.E) * F * a.npix, a.npix, up, do_c, do_d);
-        }
+        if (KEEP && t + 1 == a.T) snapshot(0, up);
+        const int64_t row = (int64_t)(t - kept_from) * a.npix;
         const Input in = input_of(a, raw);
         const int64_t o = (int64_t)t * a.npix;
         bool used_c = false, used_d = false;
@@ -188,12 +195,12 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_ker
         if (do_c) {
             mixture_step_rec(mc, in.Xc, true, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_c, a.c.v_min_c, sane,
                              used_c, dc, rc);
-            if (SAVED && inside) lane_of(a.scratch4() + o, up) = make_float4(rc.mu[0], rc.mu[1], rc.mu[2], rc.v);
+            if (KEEP && inside) lane_of(a.scratch4() + row, up) = make_float4(rc.mu[0], rc.mu[1], rc.mu[2], rc.v);
         }
         if (do_d) {
             mixture_step_rec(md, in.Xd, in.valid, alpha, lam2, a.c.T_bg, a.c.w_init, a.c.v_init_d, a.c.v_min_d, sane,
                              used_d, dd, rd);
-            if (SAVED && inside) lane_of(a.scratch2() + o, up) = make_float2(rd.mu[0], rd.v);
+            if (KEEP && inside) lane_of(a.scratch2() + row, up) = make_float2(rd.mu[0], rd.v);
         }
         const bool term_c = used_c;
         bool term_d = in.valid && used_d;
@@ -207,10 +214,10 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_ker
                 if (inside) lane_of(halves + 1, 2 * up) = pack_rec(rd, term_d, in.valid);
             }
             __syncthreads();  // (the other parity's slots are written while these are read)
-            if (!do_c) continue;
+            if (!do_c) return;
             td = term_of[t & 1][lane];
             term_d = used_of[t & 1][lane] != 0;
-            if (!inside) continue;
+            if (!inside) return;
             lane_of(halves, 2 * up) = pack_rec(rc, term_c, true);
         } else {
             lane_of(a.rec + o, up) =
@@ -219,7 +226,20 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_forward_ker
         const float Z = term_c ? (term_d ? tc + td : tc) : (term_d ? td : 0.0f);
         lane_of(a.Z + o, up) = Z;
         lane_of(a.has + o, up) = (term_c || term_d) ? 1 : 0;
+    };
+    if (!ALL) {
+        const int replayed = a.keeps() ? a.nseg - 1 : a.nseg;
+        for (int seg = 0; seg < replayed; ++seg) {
+            if (seg > 0) snapshot(seg, opaque(p));
+            const int t1 = a.first_of(seg + 1);
+#pragma unroll 1
+            for (int t = a.first_of(seg); t < t1; ++t) frame(t, std::false_type{});
+        }
+        if (a.keeps() && a.E > 1) snapshot(a.nseg - 1, opaque(p));
     }
+#pragma unroll 1
+    for (int t = kept_from; t < a.T; ++t) frame(t, std::true_type{});
+    if (!ALL && threadIdx.x == 0) a.kept[blockIdx.x] = a.keeps() ? 1u : 0u;
 }
 
 // A recorded choice, unpacked.
@@ -419,7 +439,7 @@ struct BackRead {
 };
 
 // SPLIT: the mixtures on wavefronts of their own, as in the forward (they share nothing here).
-template <int K, bool SAVED, bool SPLIT>
+template <int K, bool ALL, bool SPLIT>
 __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_kernel(GmmWindowArgs a) {
     __shared__ double sh[kBlock / 64][3];
     constexpr int kPixels = SPLIT ? kBlock / 2 : kBlock;
@@ -441,13 +461,21 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_ke
             amd[k][0] = 0.f;
             avd[k] = 0.f;
         }
-        for (int seg = SAVED ? 0 : a.nseg - 1; seg >= 0; --seg) {
-            const int t0 = SAVED ? 0 : seg * a.E;
-            const int t1 = SAVED ? a.T : min(a.T, t0 + a.E);
+        const bool kept = ALL || a.kept[blockIdx.x] != 0u;
+        for (int seg = ALL ? 0 : a.nseg - 1; seg >= 0; --seg) {
+            const bool there = ALL || (kept && seg == a.nseg - 1);  // the forward's, and the state before t1 - 1
+            const int t0 = ALL ? 0 : a.first_of(seg), t1 = ALL ? a.T : a.first_of(seg + 1);
             float muc[K][3], vc[K], mud[K][1], vd[K];
-            {
+            if (!ALL && !there && seg == 0) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    muc[k][0] = muc[k][1] = muc[k][2] = mud[k][0] = 0.f;
+                    vc[k] = a.c.v_init_c;
+                    vd[k] = a.c.v_init_d;
+                }
+            } else {
                 MV<K> s;
-                load_mv<K>(s, a.ckpt + (int64_t)seg * F * npix, npix, opaque(p));
+                load_mv<K>(s, a.ckpt + (int64_t)(there ? 0 : a.ckpt_of(seg)) * F * npix, npix, opaque(p));
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
 #pragma unroll
@@ -457,7 +485,7 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_ke
                     vd[k] = s.vd[k];
                 }
             }
-            if (!SAVED) {
+            if (!ALL && !there) {
                 Raw nraw = read_input(a, t0, p);
                 uint64_t nrec = lane_of(a.rec + (int64_t)t0 * npix, p);
 #pragma unroll 1
@@ -511,9 +539,11 @@ __global__ __launch_bounds__(kBlock, K <= 3 ? 5 : 3) void gmm_window_backward_ke
         }
     }
     block_sum3(acc, sh);
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) a.partial[3 * blockIdx.x + i] = acc[i];
+        if (!ALL) a.kept[blockIdx.x] = 0u;  // (read before block_sum3's barrier)
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void gmm_window_reduce_kernel(const double* partial, int nblocks, double* out) {
@@ -552,36 +582,36 @@ int gmm_window_blocks(int K, int npix) {
 
 namespace {
 
-template <int K, bool SAVED>
+template <int K, bool ALL>
 void launch_forward_of(const GmmWindowArgs& a, hipStream_t s) {
     if constexpr (splits(K, 1)) {
         if (splits(K, a.npix)) {
-            hipLaunchKernelGGL((gmm_window_forward_kernel<K, SAVED, true>), dim3((unsigned)gmm_window_blocks(K, a.npix)),
+            hipLaunchKernelGGL((gmm_window_forward_kernel<K, ALL, true>), dim3((unsigned)gmm_window_blocks(K, a.npix)),
                                dim3(kBlock), 0, s, a);
             return;
         }
     }
-    hipLaunchKernelGGL((gmm_window_forward_kernel<K, SAVED, false>), dim3((unsigned)gmm_window_blocks(K, a.npix)),
+    hipLaunchKernelGGL((gmm_window_forward_kernel<K, ALL, false>), dim3((unsigned)gmm_window_blocks(K, a.npix)),
                        dim3(kBlock), 0, s, a);
 }
 template <int K>
 void launch_forward(const GmmWindowArgs& a, hipStream_t s) {
-    if (a.saved) launch_forward_of<K, true>(a, s);
+    if (a.nseg == 1) launch_forward_of<K, true>(a, s);
     else launch_forward_of<K, false>(a, s);
 }
-template <int K, bool SAVED>
+template <int K, bool ALL>
 void launch_backward_of(const GmmWindowArgs& a, int blocks, hipStream_t s) {
     if constexpr (splits(K, 1)) {
         if (splits(K, a.npix)) {
-            hipLaunchKernelGGL((gmm_window_backward_kernel<K, SAVED, true>), dim3(blocks), dim3(kBlock), 0, s, a);
+            hipLaunchKernelGGL((gmm_window_backward_kernel<K, ALL, true>), dim3(blocks), dim3(kBlock), 0, s, a);
             return;
         }
     }
-    hipLaunchKernelGGL((gmm_window_backward_kernel<K, SAVED, false>), dim3(blocks), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL((gmm_window_backward_kernel<K, ALL, false>), dim3(blocks), dim3(kBlock), 0, s, a);
 }
 template <int K>
 void launch_backward(const GmmWindowArgs& a, int blocks, hipStream_t s) {
-    if (a.saved) launch_backward_of<K, true>(a, blocks, s);
+    if (a.nseg == 1) launch_backward_of<K, true>(a, blocks, s);
     else launch_backward_of<K, false>(a, blocks, s);
 }
 

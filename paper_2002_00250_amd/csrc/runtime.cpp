@@ -1492,9 +1492,9 @@ struct fgs_gmm_window {
     GmmConsts c;
     hipStream_t stream;
     bool own_stream;
-    bool saved;  // GmmWindowArgs::saved
     uint8_t* dev;
     uint64_t* rec;
+    uint32_t* kept;
     float* ckpt;
     float* scratch;
     double* partial;
@@ -1525,24 +1525,38 @@ fgs_status fgs_gmm_window_create(int32_t T, int32_t H, int32_t W, const fgs_gmm_
     w->W = W;
     w->npix = H * W;
     w->K = p.Kc;
-    w->E = checkpoint_every < T ? checkpoint_every : T;
-    w->nseg = (T + w->E - 1) / w->E;
     w->c = gmm_consts(p);
     const size_t n = (size_t)w->npix, F = 6 * (size_t)w->K;
-    // Bytes for `rows` frames of changed Gaussians (24 bytes a pixel) and `ckpts` states.
-    size_t o_ckpt = 0, o_scr = 0, o_par = 0, total = 0;
-    auto lay_out = [&](size_t ckpts, size_t rows) {
+    const size_t blocks = (size_t)gmm_window_blocks(w->K, w->npix);
+    const int32_t every = checkpoint_every < T ? checkpoint_every : T, asked = (T + every - 1) / every;
+    // A plan: nseg segments of up to E frames (GmmWindowArgs), a state for each and the changed Gaussians
+    // of one (24 bytes a pixel and frame).
+    size_t o_ckpt = 0, o_scr = 0, o_par = 0, o_kept = 0, total = 0;
+    auto plan = [&](int32_t nseg, int32_t E) {
+        w->nseg = nseg;
+        w->E = E;
         o_ckpt = align256((size_t)T * n * 8);  // the records come first
-        o_scr = o_ckpt + align256(ckpts * F * n * 4);
-        o_par = o_scr + align256(rows * 6 * n * 4);
-        total = o_par + align256((size_t)gmm_window_blocks(w->K, w->npix) * 3 * 8);
+        o_scr = o_ckpt + align256((size_t)nseg * F * n * 4);
+        o_par = o_scr + align256((size_t)E * 6 * n * 4);
+        o_kept = o_par + align256(blocks * 3 * 8);
+        total = o_kept + align256(blocks * 4);
+        return o_kept;                         // (the flags, 4 bytes per 128 or 256 pixels, aside)
     };
-    // Every frame's changed Gaussians are kept (no replay in the backward) where that takes at
-    // most a quarter more than a state per checkpoint and per frame of a segment, the most
-    // that `checkpoint_every` asks for, and can be had; else checkpoints and one segment.
-    const size_t full = (size_t)T * n * 8 + ((size_t)w->nseg + (size_t)w->E) * F * n * 4;
-    lay_out(1, (size_t)T);
-    w->saved = total <= full + full / 4;
+    // checkpoint_every bounds the memory: a state per checkpoint and one per frame of a segment.  Within
+    // that, the fewest segments and the longest: the backward replays all but the last one.
+    const size_t bound = align256((size_t)T * n * 8) + align256((size_t)asked * F * n * 4) +
+                         align256((size_t)every * F * n * 4) + align256((n + 255) / 256 * 3 * 8);
+    for (int32_t nseg = 1; nseg <= asked; ++nseg) {
+        const size_t least = plan(nseg, 1);
+        const int64_t room = least > bound ? 0 : 1 + (int64_t)((bound - least) / (6 * n * 4));
+        int32_t E = (int32_t)std::min<int64_t>(room, T);
+        while (E > 0 && plan(nseg, E) > bound) --E;  // (once: the parts are rounded up)
+        if ((int64_t)E * nseg >= T) {
+            plan((T + E - 1) / E, E);
+            break;
+        }
+        plan(asked, every);
+    }
     hipError_t e = hipSuccess;
     if (hip_stream) {
         w->stream = (hipStream_t)hip_stream;
@@ -1550,17 +1564,10 @@ fgs_status fgs_gmm_window_create(int32_t T, int32_t H, int32_t W, const fgs_gmm_
         e = hipStreamCreateWithFlags(&w->stream, hipStreamNonBlocking);
         w->own_stream = e == hipSuccess;
     }
-    if (e == hipSuccess && w->saved) {
-        e = hipMalloc((void**)&w->dev, total);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            w->dev = nullptr;
-            w->saved = false;
-            e = hipSuccess;
-        }
-    }
-    if (e == hipSuccess && !w->saved) {
-        lay_out((size_t)w->nseg, (size_t)w->E);
+    if (e == hipSuccess) e = hipMalloc((void**)&w->dev, total);
+    if (e == hipErrorOutOfMemory && w->E > every) {
+        (void)hipGetLastError();
+        plan(asked, every);  // (fewer bytes than the bound)
         e = hipMalloc((void**)&w->dev, total);
     }
     if (e != hipSuccess) {
@@ -1572,6 +1579,7 @@ fgs_status fgs_gmm_window_create(int32_t T, int32_t H, int32_t W, const fgs_gmm_
     w->ckpt = reinterpret_cast<float*>(w->dev + o_ckpt);
     w->scratch = reinterpret_cast<float*>(w->dev + o_scr);
     w->partial = reinterpret_cast<double*>(w->dev + o_par);
+    w->kept = reinterpret_cast<uint32_t*>(w->dev + o_kept);
     *out = w;
     return FGS_OK;
 }
@@ -1590,11 +1598,11 @@ static GmmWindowArgs window_args(fgs_gmm_window* w, const float* theta, const ui
     a.theta = theta;
     a.rgb = rgb;
     a.depth = depth;
-    a.saved = w->saved ? 1 : 0;
     a.rec = w->rec;
     a.ckpt = w->ckpt;
     a.scratch = w->scratch;
     a.partial = w->partial;
+    a.kept = w->kept;
     return a;
 }
 
