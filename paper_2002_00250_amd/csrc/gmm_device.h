@@ -459,8 +459,14 @@ template <int K, int C>
 __device__ __forceinline__ void mixture_step_rec(Mix<K, C>& m, const float (&X)[C], bool active, float alpha, float lam2,
                                                  float T_bg, float w_init, float v_init, float v_min, bool sane,
                                                  bool& used, float& delta, MixRec<C>& rec) {
-    MixClass r = classify_approx<K, C, 1, true>(m, X, lam2, T_bg);
-    const bool plain = sane && !any_lane(!r.sure);
+    // One Gaussian is one division either way, and the approximate choices only add to it (131x93, 24
+    // frames, K = 1: forward 14.9 us, with them 19.5; 320x240, 64 frames: 44.3 and 53.5).
+    MixClass r;
+    bool plain = false;
+    if constexpr (K > 1) {
+        r = classify_approx<K, C, 1, true>(m, X, lam2, T_bg);
+        plain = sane && !any_lane(!r.sure);
+    }
     if (!plain) {
         r = classify_rounded(m, X, lam2, T_bg);
     } else {
