@@ -25,9 +25,11 @@
  *  - Memory: fgs_mem tells whether a caller pointer is host or device memory.
  *    The caller owns every buffer it passes; the library owns the model.
  *    Device pointers are read/written in the model's stream order.
- *  - Streams: a model runs on one HIP stream (hipStream_t passed as void*),
+ *  - Streams: a model has one HIP stream (hipStream_t passed as void*),
  *    either the caller's or, when NULL is passed, one the library creates at
- *    default priority.  A model is not thread-safe; distinct models are.
+ *    default priority.  Its calls run there in the order they are made; the
+ *    fgs_*_on calls run in the order of a stream they name as well, and may run on
+ *    that one.  A model is not thread-safe; distinct models are.
  *  - Device errors poison the model: later calls on it return FGS_ERR_DEVICE
  *    until fgs_destroy.
  */
@@ -41,7 +43,7 @@
 extern "C" {
 #endif
 
-#define FGS_ABI_VERSION 6
+#define FGS_ABI_VERSION 7
 
 typedef enum fgs_status {
     FGS_OK = 0,

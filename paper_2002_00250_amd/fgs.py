@@ -31,7 +31,7 @@ FGS_CACHE_AUTO = 0
 FGS_CACHE_KEEP = 1
 FGS_CACHE_STREAM = 2
 STATE_HEADER_BYTES = 64
-ABI_VERSION = 6          # FGS_ABI_VERSION of include/fgs.h this binding is written against
+ABI_VERSION = 7          # FGS_ABI_VERSION of include/fgs.h this binding is written against
 
 
 class FgsError(RuntimeError):
@@ -85,6 +85,11 @@ def _load():
     if not os.path.exists(LIB_PATH):
         raise FgsError(-1, f"{LIB_PATH} is not built (run python -m paper_2002_00250_amd.build)")
     lib = ctypes.CDLL(LIB_PATH)
+    # (before the entry points: a library of another version may lack some)
+    version = lib.fgs_abi_version() if hasattr(lib, "fgs_abi_version") else None
+    if version != ABI_VERSION:
+        raise FgsError(-1, f"{LIB_PATH} has ABI version {version}, the binding expects "
+                           f"{ABI_VERSION}: rebuild it (python -m paper_2002_00250_amd.build)")
     S = c_int32
     sig = {
         "fgs_abi_version": (c_int32, []),
@@ -153,9 +158,6 @@ def _load():
         f = getattr(lib, name)
         f.restype = res
         f.argtypes = args
-    if lib.fgs_abi_version() != ABI_VERSION:
-        raise FgsError(-1, f"{LIB_PATH} has ABI version {lib.fgs_abi_version()}, the binding expects "
-                           f"{ABI_VERSION}: rebuild it (python -m paper_2002_00250_amd.build)")
     _lib = lib
     return lib
 
