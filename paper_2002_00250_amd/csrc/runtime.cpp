@@ -20,6 +20,7 @@
 #include "fgs_internal.h"
 #include "model.h"
 #include "postfilter.h"
+#include "ranges.h"
 
 using namespace fgs;
 
@@ -438,8 +439,7 @@ bool kernel_may_write(void* p, size_t bytes, int device) {
         (void)hipGetLastError();
         return false;
     }
-    const size_t at = (size_t)((uintptr_t)p - (uintptr_t)base);
-    return at <= size && bytes <= size - at;
+    return range_within((uintptr_t)base, size, (uintptr_t)p, bytes);
 }
 
 fgs_status read_plane(fgs_model* m, const uint8_t* plane, uint8_t* out, int64_t stride, fgs_mem where) {
@@ -454,7 +454,7 @@ fgs_status read_plane(fgs_model* m, const uint8_t* plane, uint8_t* out, int64_t 
         return FGS_OK;
     };
     if (where == FGS_MEM_DEVICE) {
-        if (!kernel_may_write(out, (size_t)(m->H - 1) * (size_t)stride + (size_t)W, m->device))
+        if (!kernel_may_write(out, rows_extent(m->H, stride, (size_t)W), m->device))
             return copy(hipMemcpyDeviceToDevice);
         FGS_HIP(m, mask_launch_copy(plane, m->W, out, stride, 0, n, m->at));
         return FGS_OK;
