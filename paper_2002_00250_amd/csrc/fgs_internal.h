@@ -334,10 +334,9 @@ hipError_t static_launch_update(const uint8_t* mask, uint16_t* count, uint8_t* o
 hipError_t static_launch_clear(uint16_t* count, uint8_t* out, int64_t npix, hipStream_t s);
 
 // --------------------------------------------------------------- masks ----
-// Bytes first .. first + count - 1 of a mask plane (W bytes a row, contiguous, 16-byte aligned;
-// first a multiple of 16, first + count <= 2^28) to rows `stride` bytes apart at dst.
-hipError_t mask_launch_copy(const uint8_t* plane, int W, uint8_t* dst, int64_t stride, int64_t first, int64_t count,
-                            hipStream_t s);
+// The first `count` bytes of a mask plane (W bytes a row, contiguous, 16-byte aligned; count <= 2^28) to
+// rows `stride` bytes apart at dst.
+hipError_t mask_launch_copy(const uint8_t* plane, int W, uint8_t* dst, int64_t stride, int64_t count, hipStream_t s);
 
 // -------------------------------------------------------- diagnostics ----
 hipError_t diag_launch_philox(uint64_t seed, const uint32_t* ctr, uint32_t* out, int64_t n,

@@ -2,7 +2,7 @@
 // host memory that the host reads after the stream is done.  A lane reads 16 consecutive bytes of
 // the plane and stores them as wide as the destination allows.  Bound by its launch at camera sizes.
 // The runtime's two-dimensional copy to pageable memory goes row by row: reading a 640x480 mask
-// took 3,270 us, through pinned memory 25.
+// took 3,270 us, through pinned memory 26.
 #include "device_common.h"
 #include "fgs_internal.h"
 
@@ -10,14 +10,13 @@ namespace fgs {
 
 namespace {
 
-// Bytes first .. first + count - 1 of the plane (first a multiple of 16) to rows of W bytes
-// `stride` apart, the plane's byte i being row i / W, column i % W.
+// The first `count` bytes of the plane to rows of W bytes `stride` apart, byte i being row i / W,
+// column i % W.
 __global__ __launch_bounds__(256) void mask_copy_kernel(const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
-                                                        int64_t stride, uint32_t W, FastDiv by_w, uint32_t first,
-                                                        uint32_t count) {
-    const uint32_t g = (blockIdx.x * 256u + threadIdx.x) * 16u;
-    if (g >= count) return;
-    const uint32_t i = first + g, n = min(16u, count - g);
+                                                        int64_t stride, uint32_t W, FastDiv by_w, uint32_t count) {
+    const uint32_t i = (blockIdx.x * 256u + threadIdx.x) * 16u;
+    if (i >= count) return;
+    const uint32_t n = min(16u, count - i);
     uint32_t y = div_by(i, by_w);
     uint32_t x = i - y * W;
     uint32_t w[4];
@@ -59,12 +58,11 @@ __global__ __launch_bounds__(256) void mask_copy_kernel(const uint8_t* __restric
 
 }  // namespace
 
-hipError_t mask_launch_copy(const uint8_t* plane, int W, uint8_t* dst, int64_t stride, int64_t first, int64_t count,
-                            hipStream_t s) {
+hipError_t mask_launch_copy(const uint8_t* plane, int W, uint8_t* dst, int64_t stride, int64_t count, hipStream_t s) {
     if (count <= 0) return hipSuccess;
     const int64_t groups = (count + 15) / 16;
     hipLaunchKernelGGL(mask_copy_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s, plane, dst, stride,
-                       (uint32_t)W, fast_div((uint32_t)W), (uint32_t)first, (uint32_t)count);
+                       (uint32_t)W, fast_div((uint32_t)W), (uint32_t)count);
     return hipGetLastError();
 }
 

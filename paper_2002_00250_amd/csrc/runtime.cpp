@@ -456,7 +456,7 @@ fgs_status read_plane(fgs_model* m, const uint8_t* plane, uint8_t* out, int64_t 
     if (where == FGS_MEM_DEVICE) {
         if (!kernel_may_write(out, rows_extent(m->H, stride, (size_t)W), m->device))
             return copy(hipMemcpyDeviceToDevice);
-        FGS_HIP(m, mask_launch_copy(plane, m->W, out, stride, 0, n, m->at));
+        FGS_HIP(m, mask_launch_copy(plane, m->W, out, stride, n, m->at));
         return FGS_OK;
     }
     const Place place = place_of(out, m->device);
@@ -474,7 +474,7 @@ fgs_status read_plane(fgs_model* m, const uint8_t* plane, uint8_t* out, int64_t 
     for (int64_t at = 0; at < n; at += (int64_t)m->mask_stage_bytes) {
         const int64_t part = std::min(n - at, (int64_t)m->mask_stage_bytes);
         // (as one row: the staging holds the part's bytes without gaps)
-        FGS_HIP(m, mask_launch_copy(plane + at, (int)part, m->mask_stage, part, 0, part, m->at));
+        FGS_HIP(m, mask_launch_copy(plane + at, (int)part, m->mask_stage, part, part, m->at));
         FGS_HIP(m, hipStreamSynchronize(m->at));
         if (stride == W) {
             std::memcpy(out + at, m->mask_stage, (size_t)part);
