@@ -1,6 +1,6 @@
 """Masks read into host memory that the caller has pinned are copied there directly: in a fraction of the
-time that pageable memory takes (a staging copy and one of the host; 1080x1920: 47 against 115 to 140 us); rows that are not of whole
-words, where that copy goes row by row (7.7 ms), as fast as pageable ones."""
+time that pageable memory takes (a staging copy and one of the host; 1080x1920: 47 against 115 to 140 us); rows
+that are not of whole words, where that copy goes row by row (7.7 ms), as fast as pageable ones."""
 import time
 
 import numpy as np
@@ -10,7 +10,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("pad", [0, 64, 1])
+@pytest.mark.parametrize("pad", [0, 32, 64, 1])
 def test_rows_in_pinned_memory(pad):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -29,7 +29,7 @@ def test_rows_in_pinned_memory(pad):
     times = {}
     for name, ptr in (("plain", plain.ctypes.data), ("pinned", pinned.data_ptr())):
         t = []
-        for _ in range(25):
+        for _ in range(400):               # (a fresh pinned block may be slow for some 50 ms)
             a = time.perf_counter()
             fgs.fgs_get_mask(m.handle, ptr, W + pad, fgs.FGS_MEM_HOST)
             t.append(time.perf_counter() - a)
@@ -37,5 +37,5 @@ def test_rows_in_pinned_memory(pad):
     for out in (plain, pinned.numpy()):
         assert np.array_equal(out[:, :W], want) and (out[:, W:] == 9).all()
     print({k: round(v * 1e6, 1) for k, v in times.items()})
-    assert times["pinned"] < (0.7 if pad % 4 == 0 else 1.5) * times["plain"], times
+    assert times["pinned"] < (0.8 if pad % 4 == 0 else 1.5) * times["plain"], times
     m.close()
