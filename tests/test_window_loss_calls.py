@@ -188,3 +188,29 @@ def test_with_and_without_a_gradient(T, H, W, shift):
         # (a sigmoid of a few roundings and one subtraction, times a weight of 2)
         assert bool(((slope - want).abs()[t0:] <= 5e-7).all())
         assert work[1].item() == max(1.0, has[t0:].double().sum().item())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("reentrant", [False, True])
+def test_recomputed_by_a_checkpoint(case, reentrant):
+    from paper_2002_00250_amd import adjoint
+    from torch.utils.checkpoint import checkpoint
+    Z, has, gt = case
+    want, grad = _grad(adjoint._bce_torch, Z, has, gt, 1, 1.0)
+    for f in (lambda z: adjoint.window_bce_loss(z, has, gt), lambda z: adjoint.window_bce_loss(z * 2, has, gt, 1, 2.0)):
+        loss, g = _grad(lambda z: checkpoint(f, z, use_reentrant=reentrant), Z)
+        assert torch.allclose(loss, want, **CLOSE) and torch.allclose(g, grad, **CLOSE)
+
+
+@pytest.mark.gpu
+def test_a_graph_kept_for_more_gradients(case):
+    from paper_2002_00250_amd import adjoint
+    Z, has, gt = case
+    _, grad = _grad(adjoint._bce_torch, Z, has, gt, 1, 1.0)
+    z = Z.clone().requires_grad_()
+    loss = adjoint.window_bce_loss(z, has, gt)
+    for k in range(3):
+        (g,) = torch.autograd.grad(loss * (k + 1), z, retain_graph=True)
+        assert torch.allclose(g, grad * (k + 1), **CLOSE)
+    (loss + 2 * adjoint.window_bce_loss(z, has, gt)).backward()
+    assert torch.allclose(z.grad, 3 * grad, **CLOSE)
