@@ -28,13 +28,15 @@ namespace {
 
 // 256 lanes per workgroup, and where the state is streamed three workgroups per CU: HBM serves
 // a few pages of every plane better than many.  Measured on 8 models of 1280x720, K = 5, non-
-// temporal, us per launch by waves per CU: 8 288, 12 269.4, 16 283, 20 and more 294 (512-lane
-// workgroups 277 with 16 waves, 286 with 24; 192 lanes 282-294; 128 lanes 272 at best).  Against
-// the 512-lane kernel without the approximate decisions and scalar plane addresses (gmm_device.h):
-// K = 5 280.4 -> 269.4 (6.5 TB/s of HBM traffic), 8 x K = 3 186 -> 177, 6 x 7/3 228 -> 220, one
-// 7/3 1920x1080 91.5 -> 88.4.  Two planes a pixel (K = 1) are too few bytes per wave for that
-// (76 -> 91 us with the limit), so it holds from six planes (K = 3) on.  A cache-resident state
-// wants every wave it can get: K = 3 per-channel variances at 853x487, 17.6 -> 16.1 us.
+// temporal, a static background with moving objects, us per launch by waves per CU: 8 288, 12 269.4,
+// 16 283, 20 and more 294 (512-lane workgroups 277 with 16 waves, 286 with 24; 192 lanes 282-294; 128
+// lanes 272 at best).  Against the 512-lane kernel without the approximate decisions and scalar plane
+// addresses (gmm_device.h): K = 5 280.4 -> 269.4, 8 x K = 3 186 -> 177, 6 x 7/3 228 -> 220, one 7/3
+// 1920x1080 91.5 -> 88.4; the benchmark's scene, whose objects change more sectors, 300 -> 287 (6.1 TB/s
+// of measured HBM traffic).  Two planes a pixel (K = 1) and four (K = 2) are too few bytes per wave for
+// the limit (76 -> 91 us; 8 models 134.4 -> 141.7, 12 206.5 -> 215.8, 3840x2160 152.3 -> 160.2), so it holds
+// from six planes (K = 3) on; without it they are within 3 % of the 512-lane kernel either way.  A
+// cache-resident state wants every wave it can get: K = 3 per-channel variances at 853x487, 17.6 -> 16.1.
 constexpr int kBlock = 256;
 constexpr int kStreamPlanes = 6;
 constexpr unsigned kStreamLds = 48u << 10;  // 3 of these fit a CU's 160 KiB; nothing is kept there

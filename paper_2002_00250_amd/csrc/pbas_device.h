@@ -276,8 +276,9 @@ __device__ __forceinline__ void pbas_tile_m(const PbasStepArgs& a, int bx, int b
 
     // Ingest (the depth code needs the depth read; computed once every read is issued).
     const bool valid = dmm > 0u;
-    // (A streaming launch divides: 1280x720, four models, N = 35, moving objects 206.5 us a launch
-    // against 207.4 with the multiplication, static background 339.7 against 340.0.)
+    // (A streaming launch, bound by HBM, gains nothing from the multiplication and keeps the division:
+    // 1280x720, four models, N = 35, moving objects 206.5 us a launch against 207.4, static background
+    // 339.7 against 340.0; launches differ by 0.4 % between runs.)
     const uint32_t I3 = NT ? depth_code_divided(dmm, a.c.depth_max_mm)
                            : depth_code(dmm, a.c.depth_max_mm, a.c.depth_div);
     const uint32_t Iw = I0 | (I1 << 8) | (I2 << 16) | (I3 << 24);
@@ -513,8 +514,9 @@ __device__ __forceinline__ void pbas_tile_m(const PbasStepArgs& a, int bx, int b
 
 // The tile with the classification of the model's min_matches (a branch per workgroup around the
 // whole frame: around the slot loop alone it took 148 VGPRs instead of 95 at N = 35).  A streaming
-// launch, bound by HBM, counts always: 1280x720, four models, N = 35, the two smallest distances
-// gain on moving objects (206.5 -> 205.3 us) what they lose on a static background (339.7 -> 340.5).
+// launch, bound by HBM, counts always: 1280x720, four models, N = 35, the two smallest distances take
+// 205.3 us for 206.5 on moving objects and 340.5 for 339.7 on a static background, no difference that
+// outlasts the 0.4 % between runs.
 template <int NMAX, int NLO, bool NT>
 __device__ __forceinline__ void pbas_tile(const PbasStepArgs& a, int bx, int by, PbasLds<NMAX>& sh) {
     if (!NT && a.c.min_matches == 2)

@@ -714,8 +714,8 @@ fgs_status fgs_create(fgs_algo algo, int32_t H, int32_t W, const void* params, v
         delete m;
         return fail(FGS_ERR_DEVICE, "model initialisation: %s", hipGetErrorString(e));
     }
-    // (made here: an allocation during fgs_set_state would break another thread's stream capture;
-    // without it a device header is copied to the host first)
+    // (made here, so that a restore from device memory allocates nothing; without it a device header is
+    // copied to the host first)
     if (hipHostMalloc((void**)&m->header_seen, kHeaderBytes, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         m->header_seen = nullptr;
