@@ -76,8 +76,11 @@ REPORT_KERNELS = [
     ("pbas_kernels.hip", "pbas_step_kernelILi1ELi20ELb0E", "pbas_step_kernel<1,20,cached>"),
     ("pbas_kernels.hip", "pbas_settle_kernelILb1E", "pbas_settle_kernel<export>"),
     ("pbas_grad_kernels.hip", "pbas_grad_step_kernelILi20ELb0ELb1E", "pbas_grad_step_kernel<20,cached,two>"),
-    ("gmm_window.hip", "gmm_window_forward_kernelILi3ELb1ELb0E", "gmm_window_forward_kernel<3,saved,whole>"),
-    ("gmm_window.hip", "gmm_window_backward_kernelILi3ELb1ELb0E", "gmm_window_backward_kernel<3,saved,whole>"),
+    ("gmm_window.hip", "gmm_window_forward_kernelILi3ELb1ELb0E", "gmm_window_forward_kernel<3,all,whole>"),
+    ("gmm_window.hip", "gmm_window_forward_kernelILi3ELb0ELb0E", "gmm_window_forward_kernel<3,segments,whole>"),
+    ("gmm_window.hip", "gmm_window_backward_kernelILi3ELb1ELb0E", "gmm_window_backward_kernel<3,all,whole>"),
+    ("gmm_window.hip", "gmm_window_backward_kernelILi3ELb0ELb0E", "gmm_window_backward_kernel<3,segments,whole>"),
+    ("window_loss.hip", "bce_sum_kernelILb1ELb1E", "bce_sum_kernel<aligned,kept>"),
     ("serve_kernels.hip", "serve_kernelILi5ELi24ELb0E", "serve_kernel<5,24,cached>"),
     ("serve_kernels.hip", "serve_kernelILi5ELi24ELb1E", "serve_kernel<5,24,NT>"),
     ("eval_kernels.hip", "eval_count_kernel", "eval_count_kernel"),
@@ -132,7 +135,7 @@ def resource_report() -> str:
     ver = subprocess.run([hipcc(), "--version"], capture_output=True, text=True).stdout.splitlines()
     ver = "; ".join(v.strip() for v in ver if "HIP version" in v or "clang version" in v)
     return "\n".join([
-        "# Compiler resource usage of the step, window, serving, evaluation and median kernels (gfx950)", "",
+        "# Compiler resource usage of the step, window, loss, serving, evaluation and median kernels (gfx950)", "",
         "sources: " + " ".join(paths),
         "sources_sha256_16: " + h.hexdigest()[:16],
         "compiler: " + ver, "",
