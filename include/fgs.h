@@ -227,8 +227,9 @@ fgs_status fgs_push_frame_scaled(fgs_model* m, const uint8_t* rgb, int64_t rgb_s
  * what is queued on hip_stream (NULL: the null stream) and before what is queued there later, and
  * after the model's earlier work wherever that ran.  The result is that of the model's stream
  * waiting for hip_stream, the call, and hip_stream waiting for the model's stream; a model whose
- * stream the library made and fgs_stream never gave out runs on hip_stream itself.  Also inside a
- * graph that hip_stream records.  Errors as the calls named; UNSUPPORTED if another device is
+ * stream the library made and fgs_stream never gave out runs on hip_stream itself.  hip_stream may
+ * be hipStreamPerThread, another stream on each thread, and may be destroyed after the call.  Also
+ * inside a graph that hip_stream records.  Errors as the calls named; UNSUPPORTED if another device is
  * current than the model's (nothing is queued then).
  */
 fgs_status fgs_push_frame_on(fgs_model* m, const uint8_t* rgb, int64_t rgb_stride, const uint16_t* depth,
